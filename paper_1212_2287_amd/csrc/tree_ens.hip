@@ -148,7 +148,7 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
              const float4 *__restrict__ leaf_vec, int32_t vec_stride4, int32_t n_out,
              int32_t chunk, double out_scale, int32_t pk_recs, const uint2 *__restrict__ big,
              int32_t n_small, uint32_t big_off0, const uint32_t *__restrict__ cleaf,
-             const int32_t *__restrict__ cleaf_id) {
+             const int32_t *__restrict__ cleaf_id, uint16_t *__restrict__ leaf_pos) {
     // Static allocation: the LDS base is address 0, so feature and node addresses need no add.
     // HALF = half a CU's LDS, so that two workgroups share a CU. CODED = documents arrive as
     // 16-bit threshold codes (rows of n_features codes) instead of floats. Layout:
@@ -494,14 +494,17 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
                 // a leaf's link is its own LDS record index; minus that of its tree's
                 // first record, it is the leaf's position in the tree
                 const int2 tr = tree_of(i);
-                if (tr.x >= 0 && doc < n_docs) {
+                if (tr.x >= 0 && (leaf_pos || doc < n_docs)) {
                     const int gt = tr.x;
                     // complete trees: the leaf's record index is the address the last step
                     // read (their leaf records carry no link); else the leaf's own link
                     const uint32_t rec = kComplete ? (complete_depth > 0 ? addr[i] / 8u : uint32_t(tr.y))
                                                    : rec_w(nd[i]) >> kShift;
                     const uint32_t self = rec - uint32_t(tr.y);
-                    leaf_ids[doc * n_trees + tree_orig[gt]] = orig_id[tree_node_off[gt] + self];
+                    if (leaf_pos)
+                        leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(self);
+                    else
+                        leaf_ids[doc * n_trees + tree_orig[gt]] = orig_id[tree_node_off[gt] + self];
                 }
             }
         } else if constexpr (VEC) {
@@ -736,9 +739,13 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
 #pragma unroll
                             for (int i = 0; i < K; ++i) {
                                 const int gt = (first_group + j * treeens::kPacketWalkers) * K + i;
-                                if (gt < n_trees && doc < n_docs)
-                                    leaf_ids[doc * n_trees + tree_orig[gt]] =
-                                        __builtin_amdgcn_raw_buffer_load_b32(id_rsrc, voff[i], soff, 0);
+                                if (gt >= n_trees)
+                                    continue; // an idle slot
+                                const int id = __builtin_amdgcn_raw_buffer_load_b32(id_rsrc, voff[i], soff, 0);
+                                if (leaf_pos)
+                                    leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(id);
+                                else if (doc < n_docs)
+                                    leaf_ids[doc * n_trees + tree_orig[gt]] = id;
                             }
                         } else if constexpr (VEC) {
 #pragma unroll
@@ -845,9 +852,11 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
             }
             if constexpr (LEAVES) {
                 const int64_t doc = doc0 + dl;
-                if (doc < n_docs)
-                    leaf_ids[doc * n_trees + tree_orig[gt]] =
-                        orig_id[tree_node_off[gt] + (r.y >> treeens::kBigLinkShift)];
+                const uint32_t self = r.y >> treeens::kBigLinkShift;
+                if (leaf_pos)
+                    leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(self);
+                else if (doc < n_docs)
+                    leaf_ids[doc * n_trees + tree_orig[gt]] = orig_id[tree_node_off[gt] + self];
             } else if constexpr (VEC) {
                 const float4 v = leaf_vec[int64_t(r.x - 1u) * vec_stride4 + chunk];
                 accv[0] += double(v.x);
@@ -1070,12 +1079,73 @@ code_kernel(const float *__restrict__ X, int64_t n_docs, int32_t n_features, int
     }
 }
 
+// Leaf ids of whole document blocks from the packed-order leaf positions the walk left in
+// pos[block][packed tree][DL documents] (16 bits each): out[doc][input tree]. A workgroup takes
+// one block and kIdTrees consecutive input trees: reads DL positions of each tree (one row,
+// coalesced), maps them to input node ids (orig_id is null when the walk stored ids already) and
+// writes them transposed through LDS, 64 consecutive trees of a document per wave store.
+// Bound by memory: 2 bytes read, 4 written per (document, tree). The walk's lanes hold documents,
+// and its trees are packed in another order than the output's, so storing ids from the walk
+// writes single 4-byte pieces of 64 rows per instruction, most lines leaving L2 before they are
+// full.
+constexpr int kIdThreads = 256;
+constexpr int kIdTrees = 64;
+template <int DL>
+__global__ void __launch_bounds__(kIdThreads)
+leaf_ids_kernel(const uint16_t *__restrict__ pos, int64_t n_docs, int32_t n_trees,
+                const int32_t *__restrict__ tree_pos, const uint32_t *__restrict__ tree_node_off,
+                const int32_t *__restrict__ orig_id, int32_t *__restrict__ out) {
+    // row stride DL + 2: an odd number of dwords, so a column of 64 trees spreads over the banks
+    __shared__ uint16_t tile[kIdTrees * (DL + 2)];
+    // all tree tiles of a block on one XCD (workgroups are dealt to them in index order): the
+    // lines two neighbouring tiles share are completed in one L2
+    const int64_t L = blockIdx.x;
+    const int n_tiles = (n_trees + kIdTrees - 1) / kIdTrees;
+    const int64_t per = int64_t(kXcds) * n_tiles;
+    const int64_t block = (L / per) * kXcds + L % kXcds;
+    const int t0 = int((L % per) / kXcds) * kIdTrees;
+    if (block * DL >= n_docs)
+        return;
+    const int nt = min(kIdTrees, n_trees - t0);
+    constexpr int kRows = kIdThreads / DL; // trees read at a time
+    const int d = int(threadIdx.x) % DL;
+    // eight rows at a time: their loads (tree, position, id) are in flight together
+    constexpr int kBatch = 8;
+    const bool live = block * DL + d < n_docs; // documents past the last one hold no position
+    for (int r0 = int(threadIdx.x) / DL; r0 < nt; r0 += kRows * kBatch) {
+        int pt[kBatch];
+        uint32_t id[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            pt[u] = tree_pos[t0 + min(r0 + u * kRows, nt - 1)];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            id[u] = live ? uint32_t(pos[(block * n_trees + pt[u]) * DL + d]) : 0u;
+        if (orig_id) {
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+                id[u] = uint32_t(orig_id[tree_node_off[pt[u]] + id[u]]);
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+            if (r0 + u * kRows < nt)
+                tile[(r0 + u * kRows) * (DL + 2) + d] = uint16_t(id[u]);
+    }
+    __syncthreads();
+    const int lane = int(threadIdx.x) % kIdTrees;
+    if (lane < nt) {
+        const int64_t n_here = min<int64_t>(DL, n_docs - block * DL);
+        for (int k = int(threadIdx.x) / kIdTrees; k < n_here; k += kIdThreads / kIdTrees)
+            out[(block * DL + k) * n_trees + t0 + lane] = tile[lane * (DL + 2) + k];
+    }
+}
+
 using ScoreFn = void (*)(const void *, int64_t, int32_t, int32_t, const uint2 *, int32_t,
                          const uint32_t *, int32_t, int32_t, int32_t, int32_t, int32_t, double *,
                          float *, int32_t *, const int32_t *, const uint32_t *, const int32_t *,
                          int32_t, uint32_t *, int32_t, int32_t, const float4 *, int32_t,
                          int32_t, int32_t, double, int32_t, const uint2 *, int32_t, uint32_t,
-                         const uint32_t *, const int32_t *);
+                         const uint32_t *, const int32_t *, uint16_t *);
 
 template <int DL, bool HALF, bool NARROW, bool CODED, int MODE>
 ScoreFn pick_k(int k) {
@@ -1181,6 +1251,7 @@ struct tree_ens {
     // leaf-id output: packed tree -> input tree, packed node -> input node id
     uint32_t *d_tree_node_off = nullptr;
     int32_t *d_tree_orig = nullptr;
+    int32_t *d_tree_pos = nullptr; // input tree -> packed tree
     int32_t *d_orig_id = nullptr;
     // vector-valued leaves and bagging: outputs per document, the table of leaf rows, and the
     // factor 1 / n_bags applied to every sum
@@ -1267,6 +1338,7 @@ void free_device(tree_ens *h) {
     (void)hipFree(h->d_tile_recs);
     (void)hipFree(h->d_tree_node_off);
     (void)hipFree(h->d_tree_orig);
+    (void)hipFree(h->d_tree_pos);
     (void)hipFree(h->d_orig_id);
     (void)hipFree(h->d_leaf_vec);
     (void)hipFree(h->d_code_search);
@@ -1460,7 +1532,8 @@ enum class ScratchSource {
 template <int MODE>
 int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs,
                    int32_t n_features, float *scores, int32_t *leaf_ids, uint32_t *masks = nullptr,
-                   int32_t mask_words = 0, ScratchSource source = ScratchSource::kHandle) {
+                   int32_t mask_words = 0, ScratchSource source = ScratchSource::kHandle,
+                   uint16_t *leaf_pos = nullptr) {
     constexpr bool kScores = MODE == kModeScore || MODE == kModeVector; // split partial sums
     // entries per document in the partial sums, and launches (four outputs each)
     const int comps = MODE == kModeVector ? kVecPerLaunch : 1;
@@ -1659,7 +1732,7 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
                            h->d_tree_orig, h->n_trees, masks, mask_words, usage_off,
                            reinterpret_cast<const float4 *>(h->d_leaf_vec), h->vec_stride / 4, n_out,
                            chunk, scale, cp ? treeens::kCompactPacketBytes / 8 : pk ? h->pk_recs : 0,
-                           h->d_big, h->n_small, h->big_off0, h->d_cleaf, h->d_cleaf_id);
+                           h->d_big, h->n_small, h->big_off0, h->d_cleaf, h->d_cleaf_id, leaf_pos);
         e = hipGetLastError();
         if (e == hipSuccess && t1)
             e = hipEventRecord(t1, stream);
@@ -1691,6 +1764,68 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
     if (e != hipSuccess)
         return hip_fail(e, "kernel launch");
     return TREE_ENS_OK;
+}
+
+// Leaf ids. Large outputs: the walk stores 16-bit leaf positions in its own (block, packed tree)
+// order and leaf_ids_kernel turns them into the output's rows, in chunks of documents whose
+// positions take at most kLeafScratchBytes (they stay in the last-level cache). 1,000 trees of 32
+// leaves, 30,011 documents: 383 us with ids stored by the walk, 103 us this way (62 us the walk,
+// 37 us the second kernel at 4.8 TB/s).
+// The walk stores ids directly where that is as fast: outputs of at most kLeafDirectBytes (the
+// L2s hold them until their lines are full; 1,000 trees x 1,000 documents 16.5 us against 28 us,
+// x 2,500 39 against 28), twice that below 256 trees (128 x 30,000: 26.8 against 28.7 us), and
+// rows of fewer than kLeafDirectTrees ids at any size (the L2s then hold the rows of all resident
+// blocks; 100 x 30,000: 22.6 against 26.8 us; 128 x 100,000: 79.8 against 59.3). Calls captured
+// into a graph store ids directly too (they then hold no buffer), as does a call whose scratch
+// cannot be allocated.
+constexpr int32_t kLeafDirectTrees = 128;
+constexpr int64_t kLeafDirectBytes = int64_t(8) << 20;
+constexpr int64_t kLeafScratchBytes = int64_t(128) << 20;
+
+bool leaves_direct(int32_t n_trees, int64_t n_docs) {
+    const int64_t most = n_trees < 2 * kLeafDirectTrees ? 2 * kLeafDirectBytes : kLeafDirectBytes;
+    return n_trees < kLeafDirectTrees || n_docs <= most / 4 / n_trees;
+}
+
+int launch_leaves(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs,
+                  int32_t n_features, int32_t *leaf_ids) {
+    const int dl = h->plan.docs_per_block;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess)
+        cap = hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    const int64_t n_blocks = (n_docs + dl - 1) / dl;
+    const int64_t block_bytes = int64_t(h->n_trees) * dl * int64_t(sizeof(uint16_t));
+    const int64_t per = std::min(n_blocks, std::max<int64_t>(1, kLeafScratchBytes / block_bytes));
+    void *pos = nullptr;
+    if (cap == hipStreamCaptureStatusNone && !leaves_direct(h->n_trees, n_docs) &&
+        hipMallocAsync(&pos, size_t(per * block_bytes), stream) != hipSuccess) {
+        pos = nullptr;
+        (void)hipGetLastError();
+    }
+    if (!pos)
+        return launch_predict<kModeLeaves>(h, stream, X, n_docs, n_features, nullptr, leaf_ids);
+    // compact packets store input node ids, the other records positions in the packed tree
+    const int32_t *map = h->cp_k > 0 ? nullptr : h->d_orig_id;
+    auto *fn = dl == 64 ? leaf_ids_kernel<64> : dl == 32 ? leaf_ids_kernel<32> : dl == 16 ? leaf_ids_kernel<16> : leaf_ids_kernel<8>;
+    const int64_t tiles = (h->n_trees + kIdTrees - 1) / kIdTrees;
+    int rc = TREE_ENS_OK;
+    for (int64_t b = 0; b < n_blocks && rc == TREE_ENS_OK; b += per) {
+        const int64_t doc0 = b * dl, nb = std::min(per, n_blocks - b);
+        const int64_t nd = std::min(nb * dl, n_docs - doc0);
+        rc = launch_predict<kModeLeaves>(h, stream, X + doc0 * n_features, nd, n_features, nullptr, nullptr,
+                                         nullptr, 0, ScratchSource::kHandle, static_cast<uint16_t *>(pos));
+        if (rc != TREE_ENS_OK)
+            break;
+        hipLaunchKernelGGL(fn, dim3(unsigned((nb + kXcds - 1) / kXcds * kXcds * tiles)), dim3(kIdThreads), 0, stream,
+                           static_cast<const uint16_t *>(pos), nd, h->n_trees, h->d_tree_pos,
+                           h->d_tree_node_off, map, leaf_ids + doc0 * h->n_trees);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess)
+            rc = hip_fail(e, "leaf id launch");
+    }
+    const hipError_t e = hipFreeAsync(pos, stream);
+    return rc != TREE_ENS_OK ? rc : e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "hipFreeAsync");
 }
 
 } // namespace
@@ -1802,6 +1937,12 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
         e = upload(&h->d_tree_node_off, p.tree_node_off);
     if (e == hipSuccess)
         e = upload(&h->d_tree_orig, p.tree_orig);
+    if (e == hipSuccess) {
+        std::vector<int32_t> pos(p.tree_orig.size());
+        for (size_t t = 0; t < pos.size(); t++)
+            pos[size_t(p.tree_orig[t])] = int32_t(t);
+        e = upload(&h->d_tree_pos, pos);
+    }
     if (e == hipSuccess)
         e = upload(&h->d_orig_id, p.orig_id);
     if (e == hipSuccess)
@@ -1898,8 +2039,7 @@ int tree_ens_predict_leaves(const tree_ens_t *h, void *stream, const float *X, i
     DeviceGuard g(h->device);
     if (g.err != hipSuccess)
         return hip_fail(g.err, "hipSetDevice");
-    return launch_predict<kModeLeaves>(h, reinterpret_cast<hipStream_t>(stream), X, n_docs,
-                                       n_features, nullptr, leaf_ids);
+    return launch_leaves(h, reinterpret_cast<hipStream_t>(stream), X, n_docs, n_features, leaf_ids);
 }
 
 int tree_ens_predict_topk(const tree_ens_t *h, void *stream, const float *X, int64_t n_docs,
