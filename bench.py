@@ -50,7 +50,8 @@ HBM_PEAK_GBS = 8000.0
 # cycles per CU whatever the byte width allows.
 LDS_CLK_PER_INSTR = 2.2
 LDS_ISSUE_NODE_GBS = N_CU * CLOCK_HZ * 64 * 8 / (2 * LDS_CLK_PER_INSTR) / 1e9  # 71,494 GB/s
-KERNEL_SRC = os.path.join(ROOT, "paper_1212_2287_amd", "csrc", "tree_ens.hip")
+CSRC = os.path.join(ROOT, "paper_1212_2287_amd", "csrc")
+KERNEL_SRC = [os.path.join(CSRC, n) for n in ("tree_ens.hip", "score.hip", "score.hpp", "pack.cpp", "pack.hpp")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 
@@ -63,8 +64,7 @@ def kernel_hash() -> str:
     counter results stay valid across comment edits and lapse on any code change."""
     import re
     h = hashlib.sha256()
-    for p in (KERNEL_SRC, os.path.join(ROOT, "paper_1212_2287_amd", "csrc", "pack.cpp"),
-              os.path.join(ROOT, "paper_1212_2287_amd", "csrc", "pack.hpp")):
+    for p in KERNEL_SRC:
         with open(p) as fh:
             text = fh.read()
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)

@@ -21,6 +21,10 @@ HIP_FLAGS = [
 ]
 
 
+SCORE_MODES = 5  # modes of score.hip (score.hpp)
+HIP_SOURCES = ("tree_ens", "topk")
+
+
 def _hipcc() -> str:
     for cand in (shutil.which("hipcc"), "/opt/rocm/bin/hipcc"):
         if cand and os.path.exists(cand):
@@ -29,20 +33,23 @@ def _hipcc() -> str:
 
 
 def build(out: str = LIB, verbose: bool = False) -> str:
-    """Compile the packer and the code generator (host C++) and the kernels + C ABI (HIP) into
-    one shared library (linked with hiprtc for the model-specialised kernels)."""
+    """Compile the packer and the code generator (host C++), the kernels and the C ABI (HIP; the
+    scoring kernels once per mode, all at the same time) and link them into one shared library
+    (with hiprtc for the model-specialised kernels)."""
     tmp = out + ".tmp"
-    run = (lambda c: subprocess.run(c, check=True)) if verbose else \
-        (lambda c: subprocess.run(c, check=True, stdout=subprocess.DEVNULL))
-    objs = []
-    for name in ("pack", "codegen"):
-        o = f"{out}.{name}.o"
-        run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-Werror", "-c",
-             os.path.join(CSRC, f"{name}.cpp"), "-o", o])
-        objs.append(o)
-    run([_hipcc(), *HIP_FLAGS, "-I", INCLUDE, "-I", CSRC, "-shared",
-         os.path.join(CSRC, "tree_ens.hip"), os.path.join(CSRC, "topk.hip"), "-x", "none", *objs,
-         "-lhiprtc", "-o", tmp])
+    sink = None if verbose else subprocess.DEVNULL
+    hip = [_hipcc(), *HIP_FLAGS, "-I", INCLUDE, "-I", CSRC, "-c"]
+    gxx = ["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-Werror", "-c"]
+    jobs = [(f"score{m}", [*hip, f"-DTREE_ENS_SCORE_MODE={m}", os.path.join(CSRC, "score.hip")])
+            for m in range(SCORE_MODES)]
+    jobs += [(n, [*hip, os.path.join(CSRC, f"{n}.hip")]) for n in HIP_SOURCES]
+    jobs += [(n, [*gxx, os.path.join(CSRC, f"{n}.cpp")]) for n in ("pack", "codegen")]
+    objs = [f"{out}.{name}.o" for name, _ in jobs]
+    running = [subprocess.Popen([*cmd, "-o", o], stdout=sink) for (_, cmd), o in zip(jobs, objs)]
+    failed = [p.args for p in running if p.wait() != 0]
+    if failed:
+        raise subprocess.CalledProcessError(1, failed[0])
+    subprocess.run([_hipcc(), *HIP_FLAGS, "-shared", *objs, "-lhiprtc", "-o", tmp], check=True, stdout=sink)
     os.replace(tmp, out)
     for o in objs:
         os.remove(o)
