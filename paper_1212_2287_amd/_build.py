@@ -22,7 +22,7 @@ HIP_FLAGS = [
 
 
 SCORE_MODES = 5  # modes of score.hip (score.hpp)
-HIP_SOURCES = ("tree_ens", "topk")
+HIP_SOURCES = ("tree_ens", "uniform", "topk")
 
 
 def _hipcc() -> str:

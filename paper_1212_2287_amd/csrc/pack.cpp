@@ -210,28 +210,41 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
     // ---- coded features: per-feature sorted distinct thresholds -----------------------------
     // Possible when every feature's thresholds fit one coding workgroup and 16-bit codes; used
     // when float documents leave too few per block for the model's trees (below).
-    std::vector<std::vector<float>> thr_of;
-    int code_ok = -1; // -1: not computed yet
-    auto can_code = [&]() {
-        if (code_ok < 0) {
-            code_ok = 1;
-            thr_of.assign(size_t(n_cols), {});
-            for (int64_t i = 0; i < n_nodes; i++) {
-                if (feature[i] < 0)
-                    continue;
-                const float v = canon(threshold[i]);
-                if (!std::isnan(v))
-                    thr_of[size_t(feature[i])].push_back(v);
-            }
-            for (auto &tv : thr_of) {
-                std::sort(tv.begin(), tv.end());
-                tv.erase(std::unique(tv.begin(), tv.end()), tv.end());
-                if (tv.size() > kMaxCode || tv.size() >= size_t(kCodeTableFloats))
-                    code_ok = 0;
-            }
+    // thr_of: every feature's distinct thresholds in ascending order (NaN left out: a strict +inf
+    // split never sends right); thr_below: how many of its thresholds, repeats counted, lie below
+    // each, and at the end their number; thr_rank: a node's place in its feature's list.
+    std::vector<std::vector<float>> thr_of(static_cast<size_t>(n_cols));
+    std::vector<std::vector<uint32_t>> thr_below(static_cast<size_t>(n_cols));
+    std::vector<uint32_t> thr_rank(static_cast<size_t>(n_nodes), 0u);
+    for (int64_t i = 0; i < n_nodes; i++) {
+        const float v = feature[i] >= 0 ? canon(threshold[i]) : 0.0f;
+        if (feature[i] >= 0 && !std::isnan(v))
+            thr_of[size_t(feature[i])].push_back(v);
+    }
+    for (size_t f = 0; f < thr_of.size(); f++) {
+        std::vector<float> &tv = thr_of[f];
+        std::sort(tv.begin(), tv.end());
+        size_t n = 0;
+        for (size_t i = 0; i < tv.size(); i++) {
+            if (i > 0 && tv[i] == tv[n - 1])
+                continue;
+            thr_below[f].push_back(uint32_t(i));
+            tv[n++] = tv[i];
         }
-        return code_ok == 1;
-    };
+        thr_below[f].push_back(uint32_t(tv.size()));
+        tv.resize(n);
+    }
+    for (int64_t i = 0; i < n_nodes; i++) {
+        if (feature[i] < 0)
+            continue;
+        const auto &tv = thr_of[size_t(feature[i])];
+        const float v = canon(threshold[i]);
+        // a NaN threshold compares below everything: rank 0 (its users test for NaN first)
+        thr_rank[size_t(i)] = uint32_t(std::lower_bound(tv.begin(), tv.end(), v) - tv.begin());
+    }
+    bool codes_fit = true;
+    for (const auto &tv : thr_of)
+        codes_fit &= tv.size() <= kMaxCode && tv.size() < size_t(kCodeTableFloats);
 
     // ---- LDS plan and the trees too large for one tile ---------------------------------------
     // A tree whose records (plus a tile's header and K root copies) exceed the plan's tile slot
@@ -254,7 +267,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         // Coding pays when float documents leave too few per block for the model's trees: when
         // a float tile cannot hold one tree for each walker, most walkers would idle.
         coded = plan.docs_per_block > 0 && plan.docs_per_block < 64 &&
-                avg_tree_bytes * (1024 / plan.docs_per_block) > plan.tile_bytes && can_code();
+                avg_tree_bytes * (1024 / plan.docs_per_block) > plan.tile_bytes && codes_fit;
         if (coded)
             plan = plan_lds(n_cols, avg_tree_bytes, 2);
         if (plan.docs_per_block == 0)
@@ -303,14 +316,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
     std::vector<double> lock_key(size_t(n_trees), 0.0);
     std::vector<uint8_t> complete_tree(size_t(n_trees), 0);
     {
-        std::vector<std::vector<float>> thr_sorted(static_cast<size_t>(n_cols));
-        for (int64_t i = 0; i < n_nodes; i++) {
-            const float v = feature[i] >= 0 ? canon(threshold[i]) : 0.0f;
-            if (feature[i] >= 0 && !std::isnan(v)) // NaN: a strict +inf split, never right
-                thr_sorted[size_t(feature[i])].push_back(v);
-        }
-        for (auto &v : thr_sorted)
-            std::sort(v.begin(), v.end());
         std::vector<double> reach, at_depth;
         for (int32_t t = 0; t < n_trees; t++) {
             const int64_t a = tree_offsets[t];
@@ -328,10 +333,10 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                     at_depth[size_t(level[size_t(i)])] += reach[size_t(i)];
                     continue;
                 }
-                const auto &ts = thr_sorted[size_t(feature[a + i])];
-                const float v = canon(threshold[a + i]);
-                const size_t below = size_t(std::lower_bound(ts.begin(), ts.end(), v) - ts.begin());
-                const double p_right = std::isnan(v) ? 0.0 : 1.0 - double(below) / double(ts.size());
+                const auto &below = thr_below[size_t(feature[a + i])];
+                const double p_right = std::isnan(canon(threshold[a + i]))
+                                           ? 0.0
+                                           : 1.0 - double(below[thr_rank[size_t(a + i)]]) / double(below.back());
                 const int32_t l = left[a + i], r = right[a + i];
                 reach[size_t(r)] = reach[size_t(i)] * p_right;
                 reach[size_t(l)] = reach[size_t(i)] * (1.0 - p_right);
@@ -417,11 +422,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                 const float th = strict ? strict_to_inclusive(threshold[a + i]) : threshold[a + i];
                 r.thr_bits = float_bits(th);
                 if (plan.coded) {
-                    const float v = canon(threshold[a + i]);
-                    const auto &tv = thr_of[size_t(feature[a + i])];
-                    r.thr_bits = std::isnan(v) ? 0xFFFFu
-                                               : uint32_t(std::lower_bound(tv.begin(), tv.end(), v) -
-                                                          tv.begin()) + 1u;
+                    r.thr_bits = std::isnan(canon(threshold[a + i])) ? 0xFFFFu : thr_rank[size_t(a + i)] + 1u;
                 }
                 const uint32_t col = big_tree ? uint32_t(feature[a + i] + 1)
                                               : uint32_t(feature[a + i] + 1) * uint32_t(plan.docs_per_block) *
@@ -846,6 +847,57 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         }
     }
 
+    // ---- uniform evaluation (shallow trees; see UniformPlan) --------------------------------------
+    {
+        UniformPlan u{};
+        for (int32_t docs = 512; docs >= 128 && u.docs_per_block == 0; docs /= 2)
+            if (int64_t(n_cols) * docs * 2 <= kLdsPerCu - kUniformDocBase)
+                u.docs_per_block = docs;
+        bool ok = !vec && !plan.coded && n_small == n_trees && n_cols > 0 && u.docs_per_block > 0 &&
+                  p.max_depth >= 2 && p.max_depth <= kUniformMaxDepth && codes_fit;
+        for (size_t f = 0; ok && f < thr_of.size(); f++)
+            ok = thr_of[f].size() < kUniformNeverRight;
+        if (ok) {
+            u.depth = p.max_depth;
+            const int32_t D = u.depth, per = uniform_trees(D), L = 1 << D;
+            u.n_chunks = (n_trees + per - 1) / per;
+            auto column = [&](uint32_t col) { return (uint32_t(kUniformDocBase) + col * uint32_t(u.docs_per_block) * 2u) / 64u; };
+            const size_t total = size_t(u.n_chunks) * size_t(per) * size_t(L);
+            p.uniform_nodes.assign(total, kUniformNeverRight << 16 | column(0));
+            p.uniform_leaves.assign(total, 0.0);
+            const int shift_u = plan.narrow ? 16 : kWideChildShift;
+            const uint32_t cmask = plan.narrow ? kNarrowColMask : kWideColMask;
+            for (int32_t t = 0; t < n_trees; t++) {
+                const size_t base = p.tree_node_off[size_t(t)];
+                const NodeRec *tree = p.nodes.data() + base;
+                const int64_t flat = tree_offsets[p.tree_orig[size_t(t)]]; // the tree in the input arrays
+                uint32_t *nodes = p.uniform_nodes.data() + size_t(t) * size_t(L);
+                double *leaves = p.uniform_leaves.data() + size_t(t) * size_t(L);
+                // at[s]: the packed tree's node at slot s of the complete tree, level by level
+                uint32_t at[2 << kUniformMaxDepth];
+                at[0] = 0;
+                for (int32_t s = 0; s < 2 * L - 1; s++) {
+                    const NodeRec r = tree[at[s]];
+                    const bool leaf = (r.w & cmask) == 0; // stays put: both children are the leaf
+                    if (s >= L - 1) {
+                        float v;
+                        std::memcpy(&v, &r.thr_bits, 4);
+                        leaves[2 * L - 2 - s] = double(v); // leaf L - 1 places from the left: no "left"
+                        continue;
+                    }
+                    if (!leaf) {
+                        const size_t i = size_t(flat + p.orig_id[base + at[s]]);
+                        const uint32_t code = std::isnan(canon(threshold[i])) ? kUniformNeverRight : thr_rank[i] + 1u;
+                        nodes[s] = code << 16 | column(uint32_t(feature[i]));
+                    }
+                    at[2 * s + 1] = leaf ? at[s] : r.w >> shift_u;
+                    at[2 * s + 2] = leaf ? at[s] : (r.w >> shift_u) + 1;
+                }
+            }
+            p.uniform = u;
+        }
+    }
+
     if (plan.lds_bytes == kLdsPerCu / 2) {
         const int64_t used = p.pk_recs > 0 ? int64_t(kPacketWalkers) * p.pk_recs : int64_t(p.level_slot_recs[0]);
         const int64_t off = (int64_t(plan.xs_bytes) + used * 8 + 15) & ~int64_t(15);
@@ -859,7 +911,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
     p.images.resize(p.images.size() + size_t(kPrefetchFull / 2) * 1024, NodeRec{0u, 0u});
 
     // ---- coded models: threshold table and coding chunks ------------------------------------
-    if (plan.coded) {
+    if (plan.coded || p.uniform.depth > 0) {
         p.code_table_off.assign(size_t(n_cols) + 1, 0);
         for (int32_t f = 0; f < n_cols; f++) {
             p.code_table_off[size_t(f)] = uint32_t(p.code_table.size());
@@ -873,7 +925,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                 s++;
             return s;
         };
-        std::vector<float> sorted;
         int32_t fb = 0;
         while (fb < n_cols) {
             int32_t fe = fb + 1, steps = bits(fb);
@@ -888,26 +939,15 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             const int32_t begin = int32_t(p.code_search.size());
             p.code_search.resize(p.code_search.size() + size_t(fe - fb) * size_t(slots - 1), std::nanf(""));
             for (int32_t f = fb; f < fe; f++) {
-                // in-order walk of the complete tree of slots 1 .. slots - 1 takes the sorted list
-                sorted.assign(p.code_table.begin() + p.code_table_off[size_t(f)],
-                              p.code_table.begin() + p.code_table_off[size_t(f) + 1]);
-                sorted.resize(size_t(slots - 1), std::nanf(""));
+                // slot i at level l of the complete tree of slots 1 .. slots - 1 takes the in-order
+                // place ((2 (i - 2^l) + 1) << (steps - 1 - l)) - 1 of the sorted list
+                const float *tv = p.code_table.data() + p.code_table_off[size_t(f)];
+                const int32_t len = int32_t(p.code_table_off[size_t(f) + 1] - p.code_table_off[size_t(f)]);
                 float *dst = p.code_search.data() + begin + size_t(f - fb) * size_t(slots - 1) - 1; // slot i
-                size_t next = 0;
-                std::vector<std::pair<int32_t, bool>> stack; // (slot, children done)
-                stack.push_back({1, false});
-                while (!stack.empty()) {
-                    auto [i, done] = stack.back();
-                    stack.pop_back();
-                    if (i >= slots)
-                        continue;
-                    if (done) {
-                        dst[i] = sorted[next++];
-                        stack.push_back({2 * i + 1, false});
-                    } else {
-                        stack.push_back({i, true});
-                        stack.push_back({2 * i, false});
-                    }
+                for (int32_t l = 0; l < steps; l++) {
+                    const int32_t width = 1 << (steps - 1 - l);
+                    for (int32_t k = 0, at = width - 1; k < 1 << l && at < len; k++, at += 2 * width)
+                        dst[(1 << l) + k] = tv[at];
                 }
             }
             p.code_chunks.push_back(CodeChunk{fb, fe, begin, int32_t(p.code_search.size()), steps});

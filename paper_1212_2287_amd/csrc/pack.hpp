@@ -131,6 +131,31 @@ constexpr int kCompactCodeShift = 5;
 // LDS byte address of the first window (windows are aligned to their size, at most 2 KiB)
 inline int32_t compact_window_base(int32_t xs_bytes) { return (xs_bytes + 2047) & ~2047; }
 
+constexpr int kLdsPerCu = 160 * 1024; // gfx950 LDS per compute unit
+
+// Uniform evaluation: models whose trees have depth at most 3, one value per leaf and at most
+// 2,046 distinct thresholds per feature (11-bit codes). Every tree is padded to a complete tree of
+// depth D (2 or 3; a leaf above depth D becomes a node that never sends right, with the leaf's
+// value below it) and all its nodes are evaluated for every document (uniform.hip). A chunk holds
+// uniform_trees(D) trees (the last one padded with trees of value 0):
+//   nodes   [tree][2^D][2] words: the threshold code in both halves, the LDS address of the
+//           feature's column; node n's children are 2n + 1 (left) and 2n + 2, the last pair is
+//           unused. A document goes right iff its code >= the threshold code (kUniformNeverRight:
+//           never).
+//   leaves  [tree][2^D] doubles, at the place whose bits say "left" from the root (highest bit) on.
+// The LDS of a workgroup: each wave's leaf tables of one chunk, then the document tile,
+// [column][docs_per_block] codes.
+struct UniformPlan {
+    int32_t depth;          // D; 0: the model is not evaluated this way
+    int32_t docs_per_block; // 512, 256 or 128: the widest whose tile fits
+    int32_t n_chunks;
+};
+constexpr int kUniformMaxDepth = 3;
+constexpr uint32_t kUniformNeverRight = 2047u;
+constexpr int kUniformLeafBytes = 1024;               // leaf tables of a chunk
+constexpr int kUniformDocBase = 16 * kUniformLeafBytes; // LDS address of the document tile (16 waves)
+constexpr int uniform_trees(int depth) { return kUniformLeafBytes / (8 << depth); }
+
 // Launch plan fixed at create time from the model's feature range.
 struct LdsPlan {
     int32_t docs_per_block; // documents a workgroup stages (power of two, 8..64)
@@ -174,7 +199,6 @@ constexpr int kCodeTableFloats = 16384;  // LDS table slots per coding workgroup
 constexpr int kCodeChunkFeatures = 256;  // features per coding workgroup at most
 constexpr uint32_t kMaxCode = 0xFFFEu;    // codes are 16-bit; 0xFFFF = "never right"
 
-constexpr int kLdsPerCu = 160 * 1024;  // gfx950 LDS per compute unit
 // The kernels prefetch tiles into registers (1,024 threads x kPrefetch records): at most 6
 // records per thread (one tile) when two workgroups share a CU (64 VGPRs each); 16 when one
 // owns it, as two tiles of up to 8 records per thread each (64 KiB) in flight at once.
@@ -232,13 +256,17 @@ struct Packed {
     std::vector<uint32_t> cp_packets;
     std::vector<uint32_t> cp_leaf;
     std::vector<int32_t> cp_leaf_id;
+    // uniform evaluation (see UniformPlan)
+    UniformPlan uniform{};
+    std::vector<uint32_t> uniform_nodes;
+    std::vector<double> uniform_leaves;
     // vector-valued leaves (n_outputs > 1): a leaf's threshold slot holds 2 + its packed node
     // index instead of a value, and row (thr - 1) of leaf_vec holds its n_outputs values,
     // padded to vec_stride (a multiple of 4) floats; row 0 is zero (the all-zero record's row)
     int32_t n_outputs = 1;
     int32_t vec_stride = 0;
     std::vector<float> leaf_vec;
-    // coded models only
+    // coded models and uniform evaluation only
     std::vector<float> code_table;         // T_0, T_1, ... concatenated
     std::vector<uint32_t> code_table_off;  // [n_cols + 1] start of T_f in code_table
     std::vector<CodeChunk> code_chunks;    // features grouped for the coding kernel

@@ -637,6 +637,72 @@ int emu_walk_compact(int32_t n_trees, const int64_t *tree_offsets, const int32_t
     return 0;
 }
 
+// All documents through the tables of uniform evaluation (every node of a shallow tree, padded to a
+// complete one, evaluated in the kernel's arithmetic: 16-bit differences whose sign bits select and
+// then form the leaf's place). Scores as emu_walk; returns 2 when the model has no such tables, else
+// 0 or 1 with a message, or a negative packer status. plan_out: depth, documents per block, chunks.
+int emu_uniform(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feature, const float *threshold,
+                const int32_t *left, const int32_t *right, const float *value, uint32_t flags, const float *X,
+                int64_t n_docs, int32_t n_features, double *scores, int32_t *plan_out) {
+    treeens::Packed p;
+    std::string err;
+    const int rc = treeens::pack_model(n_trees, tree_offsets, feature, threshold, left, right, value, 1, flags, p, err);
+    if (rc != treeens::kOk) {
+        g_msg = err;
+        return rc;
+    }
+    const treeens::UniformPlan &u = p.uniform;
+    if (u.depth == 0) {
+        g_msg = "no uniform tables";
+        return 2;
+    }
+    plan_out[0] = u.depth;
+    plan_out[1] = u.docs_per_block;
+    plan_out[2] = u.n_chunks;
+    const int D = u.depth, L = 1 << D, per = treeens::uniform_trees(D);
+    const int64_t tile = int64_t(p.n_cols) * u.docs_per_block * 2;
+    if (treeens::kUniformDocBase + tile > treeens::kLdsPerCu || (u.docs_per_block < 512 && tile * 2 + treeens::kUniformDocBase <= treeens::kLdsPerCu))
+        return bad("uniform: the document tile is not the widest that fits");
+    if (16 * u.docs_per_block * 8 + treeens::kUniformDocBase > treeens::kLdsPerCu)
+        return bad("uniform: the reduction does not fit the LDS");
+    const size_t total = size_t(u.n_chunks) * size_t(per) * size_t(L);
+    if (int64_t(u.n_chunks) * per < n_trees || int64_t(u.n_chunks - 1) * per >= n_trees || p.uniform_nodes.size() != total ||
+        p.uniform_leaves.size() != total)
+        return bad("uniform: wrong table sizes");
+    std::vector<uint16_t> codes(static_cast<size_t>(p.n_cols));
+    for (int64_t doc = 0; doc < n_docs; doc++) {
+        for (int f = 0; f < p.n_cols; f++) {
+            codes[size_t(f)] = code_of(p, f, X[doc * n_features + f]);
+            if (codes[size_t(f)] >= treeens::kUniformNeverRight)
+                return bad("uniform: a code reaches the never-right threshold");
+        }
+        double sum = 0.0;
+        for (int64_t t = 0; t < int64_t(u.n_chunks) * per; t++) {
+            const uint32_t *nodes = p.uniform_nodes.data() + t * L;
+            uint16_t d[7];
+            for (int n = 0; n < L - 1; n++) {
+                const int64_t addr = int64_t(nodes[n] & 0xFFFFu) * 64 - treeens::kUniformDocBase;
+                const int64_t col = addr / (u.docs_per_block * 2);
+                if (addr < 0 || addr % (u.docs_per_block * 2) || col >= p.n_cols)
+                    return bad("uniform: a node reads outside the document tile");
+                d[n] = uint16_t(codes[size_t(col)] - (nodes[n] >> 16));
+            }
+            auto select = [](uint32_t m, uint32_t a, uint32_t b) { return (m & a) | (~m & b); };
+            const uint32_t s1 = select(d[0], d[1], d[2]);
+            uint32_t place;
+            if (D == 3) {
+                const uint32_t s2 = select(s1, select(d[0], d[3], d[5]), select(d[0], d[4], d[6]));
+                place = (select(0x8000u, d[0], select(0x4000u, s1, s2)) & 0xE000u) >> 13;
+            } else {
+                place = (select(0x4000u, d[0], s1) & 0x6000u) >> 13;
+            }
+            sum += p.uniform_leaves[size_t(t * L + place)];
+        }
+        scores[doc] = sum;
+    }
+    return 0;
+}
+
 // Every coded feature's search table against a plain count: at each of its thresholds, just
 // below each, at +-inf, +-0 and NaN, the descent must give |{t : x >= t}|. Returns 2 when the
 // model is not coded, else 0 or 1 with a message.
