@@ -98,8 +98,11 @@ int tree_ens_create(tree_ens_t **out, int32_t n_trees, const int64_t *tree_offse
  *              the mean of their sums, i.e. the sum over all trees divided by n_bags.
  * Other arguments, ownership and errors as tree_ens_create (tree_ens_create is this call with
  * n_outputs = n_bags = 1). With n_outputs > 1 the leaf rows live in a device table of
- * n_nodes + 1 rows of ceil(n_outputs / 4) * 4 floats, and a predict makes one pass over the
- * trees per four outputs.
+ * one row per leaf (and one of zeros) of ceil(n_outputs / 4) * 4 floats. A predict makes one pass
+ * over the trees per four outputs. With more than four outputs, at most 4,096 trees and enough
+ * documents (4,096, and 4 per tree) it makes one pass that stores each leaf's row in a
+ * stream-ordered buffer (2 bytes per document and tree, at most 256 MiB:
+ * larger batches go in chunks) and one reading of it per eight outputs.
  */
 int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree_offsets,
                           const int32_t *feature, const float *threshold, const int32_t *left,
@@ -160,7 +163,9 @@ int tree_ens_predict_noalloc(const tree_ens_t *h, void *stream, const float *X, 
  *
  *   leaf_ids  device, int32 [n_docs][n_trees] row-major: the tree-local id, in the caller's
  *             input numbering, of the leaf that document d reaches in tree t.
- * Other arguments and behaviour as tree_ens_predict.
+ * Other arguments and behaviour as tree_ens_predict. Large outputs take a stream-ordered buffer of
+ * 2 bytes per document and tree (at most 256 MiB: larger batches go in chunks) for the duration of the
+ * call, in calls that are not captured into a graph.
  */
 int tree_ens_predict_leaves(const tree_ens_t *h, void *stream, const float *X, int64_t n_docs,
                             int32_t n_features, int32_t *leaf_ids);

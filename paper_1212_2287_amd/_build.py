@@ -21,7 +21,7 @@ HIP_FLAGS = [
 ]
 
 
-SCORE_MODES = 5  # modes of score.hip (score.hpp)
+SCORE_MODES = 6  # modes of score.hip (score.hpp)
 HIP_SOURCES = ("tree_ens", "uniform", "topk")
 
 

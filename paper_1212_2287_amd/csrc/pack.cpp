@@ -367,6 +367,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
     if (vec) {
         p.vec_stride = (n_outputs + 3) / 4 * 4;
         p.leaf_vec.assign(size_t(n_nodes + 1) * size_t(p.vec_stride), 0.0f);
+        p.tree_row0.resize(size_t(n_trees));
     }
     p.tree_orig.resize(size_t(n_trees));
     std::iota(p.tree_orig.begin(), p.tree_orig.end(), 0);
@@ -384,7 +385,8 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
     p.orig_id.reserve(size_t(n_nodes));
     p.tree_node_off.resize(size_t(n_trees) + 1, 0);
     p.tree_depth.resize(size_t(n_trees), 0);
-    std::vector<int32_t> new_id;
+    std::vector<int32_t> new_id, node_of_new;
+    uint32_t next_row = 1; // leaf-vector rows
     for (int32_t pt = 0; pt < n_trees; pt++) {
         const int32_t t = p.tree_orig[size_t(pt)];
         // big trees (packed last) take the big-tree record format (see kBigLinkShift)
@@ -414,6 +416,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         p.tree_node_off[size_t(pt)] = uint32_t(base);
         p.nodes.resize(base + size_t(n));
         p.orig_id.resize(base + size_t(n));
+        node_of_new.assign(vec ? size_t(n) : 0u, -1);
         for (int64_t i = 0; i < n; i++) {
             const int32_t ni = new_id[size_t(i)];
             NodeRec &r = p.nodes[base + size_t(ni)];
@@ -429,12 +432,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                                                     uint32_t(plan.elem_bytes);
                 r.w = link(uint32_t(new_id[size_t(left[a + i])])) | col;
             } else if (vec) {
-                // never 0: a coded leaf (code 0 >= thr is false) stays put as well
-                const size_t packed = base + size_t(ni);
-                r.thr_bits = uint32_t(packed) + 2u;
-                for (int32_t c = 0; c < n_outputs; c++)
-                    p.leaf_vec[(packed + 1) * size_t(p.vec_stride) + size_t(c)] =
-                        value[(a + i) * n_outputs + c];
+                node_of_new[size_t(ni)] = int32_t(i); // its row: below, in packed order
                 r.w = link(uint32_t(ni));
             } else {
                 r.thr_bits = float_bits(value[a + i]);
@@ -443,10 +441,24 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                 r.w = link(uint32_t(ni));
             }
         }
+        if (vec) {
+            p.tree_row0[size_t(pt)] = next_row;
+            for (size_t ni = 0; ni < size_t(n); ni++) {
+                if (node_of_new[ni] < 0)
+                    continue;
+                // never 0: a coded leaf (code 0 >= thr is false) stays put as well
+                p.nodes[base + ni].thr_bits = next_row + 1u;
+                for (int32_t c = 0; c < n_outputs; c++)
+                    p.leaf_vec[size_t(next_row) * size_t(p.vec_stride) + size_t(c)] =
+                        value[(a + node_of_new[ni]) * n_outputs + c];
+                next_row++;
+            }
+        }
         p.tree_depth[size_t(pt)] = uint32_t(depth_of[size_t(t)]);
         p.max_depth = std::max(p.max_depth, depth_of[size_t(t)]);
     }
     p.tree_node_off[size_t(n_trees)] = uint32_t(p.nodes.size());
+    p.leaf_rows = int64_t(next_row);
 
     // ---- pass 3: tilings at budget / 2^k -------------------------------------------------
     // A tile is a run of whole trees whose image (header + records) fits the byte budget. When

@@ -260,12 +260,15 @@ struct Packed {
     UniformPlan uniform{};
     std::vector<uint32_t> uniform_nodes;
     std::vector<double> uniform_leaves;
-    // vector-valued leaves (n_outputs > 1): a leaf's threshold slot holds 2 + its packed node
-    // index instead of a value, and row (thr - 1) of leaf_vec holds its n_outputs values,
-    // padded to vec_stride (a multiple of 4) floats; row 0 is zero (the all-zero record's row)
+    // vector-valued leaves (n_outputs > 1): a leaf's threshold slot holds 1 + its row of leaf_vec
+    // instead of a value. Rows hold n_outputs values padded to vec_stride (a multiple of 4) floats;
+    // row 0 is zero (the all-zero record's row), then come the leaves of packed tree 0, 1, ..., the
+    // first of tree t in row tree_row0[t]; leaf_rows rows are used.
     int32_t n_outputs = 1;
     int32_t vec_stride = 0;
     std::vector<float> leaf_vec;
+    std::vector<uint32_t> tree_row0;
+    int64_t leaf_rows = 0;
     // coded models and uniform evaluation only
     std::vector<float> code_table;         // T_0, T_1, ... concatenated
     std::vector<uint32_t> code_table_off;  // [n_cols + 1] start of T_f in code_table

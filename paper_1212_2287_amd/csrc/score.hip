@@ -125,6 +125,7 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
     constexpr bool LEAVES = MODE == kModeLeaves;
     constexpr bool USAGE = MODE == kModeUsage || MODE == kModeUsageSlot;
     constexpr bool VEC = MODE == kModeVector;
+    constexpr bool ROWS = MODE == kModeRows;
     constexpr int kLds = HALF ? treeens::kLdsPerCu / 2 + (MODE == kModeUsage ? treeens::kUsageHalfBytes : 0)
                               : treeens::kLdsPerCu;
     __shared__ __align__(16) unsigned char lds[kLds];
@@ -332,7 +333,7 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
     if (!COMPACT && tid == 0) {
         // value 0 (as -0.0 for codes, whose leaves never hold zero bits; the all-zero row 0 of
         // the leaf-vector table for vector-valued leaves), column 0, self link
-        const uint32_t thr = VEC ? 1u : CODED ? 0x80000000u : 0u;
+        const uint32_t thr = VEC || ROWS ? 1u : CODED ? 0x80000000u : 0u;
         *reinterpret_cast<uint2 *>(lds + zero_rec) = make_uint2(thr, (uint32_t(zero_rec) / 8u) << kShift);
     }
 
@@ -452,18 +453,26 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
                 // a leaf's link is its own LDS record index; minus that of its tree's
                 // first record, it is the leaf's position in the tree
                 const int2 tr = tree_of(i);
-                if (tr.x >= 0 && (leaf_pos || doc < n_docs)) {
-                    const int gt = tr.x;
-                    // complete trees: the leaf's record index is the address the last step
-                    // read (their leaf records carry no link); else the leaf's own link
-                    const uint32_t rec = kComplete ? (complete_depth > 0 ? addr[i] / 8u : uint32_t(tr.y))
-                                                   : rec_w(nd[i]) >> kShift;
-                    const uint32_t self = rec - uint32_t(tr.y);
-                    if (leaf_pos)
+                const int gt = tr.x;
+                // complete trees: the leaf's record index is the address the last step
+                // read (their leaf records carry no link); else the leaf's own link
+                const uint32_t rec = kComplete ? (complete_depth > 0 ? addr[i] / 8u : uint32_t(tr.y))
+                                               : rec_w(nd[i]) >> kShift;
+                const uint32_t self = rec - uint32_t(tr.y);
+                if (leaf_pos) {
+                    if (gt >= 0)
                         leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(self);
-                    else
-                        leaf_ids[doc * n_trees + tree_orig[gt]] = orig_id[tree_node_off[gt] + self];
+                } else if (gt >= 0 && doc < n_docs) {
+                    leaf_ids[doc * n_trees + tree_orig[gt]] = orig_id[tree_node_off[gt] + self];
                 }
+            }
+        } else if constexpr (ROWS) {
+            // a leaf's threshold slot holds its table row + 1
+#pragma unroll
+            for (int i = 0; i < K; ++i) {
+                const int gt = tree_of(i).x;
+                if (gt >= 0)
+                    leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(rec_thr(nd[i]) - 1u);
             }
         } else if constexpr (VEC) {
             // a leaf's threshold slot holds its table row + 1 (idle slots: row 0, zeros);
@@ -705,6 +714,14 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
                                 else if (doc < n_docs)
                                     leaf_ids[doc * n_trees + tree_orig[gt]] = id;
                             }
+                        } else if constexpr (ROWS) {
+#pragma unroll
+                            for (int i = 0; i < K; ++i) {
+                                const int gt = (first_group + j * treeens::kPacketWalkers) * K + i;
+                                const uint32_t row = __builtin_amdgcn_raw_buffer_load_b32(leaf_rsrc, voff[i], soff, 0);
+                                if (gt < n_trees)
+                                    leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(row - 1u);
+                            }
                         } else if constexpr (VEC) {
 #pragma unroll
                             for (int i = 0; i < K; ++i) {
@@ -815,6 +832,8 @@ score_kernel(const void *__restrict__ Xv, int64_t n_docs, int32_t n_features, in
                     leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(self);
                 else if (doc < n_docs)
                     leaf_ids[doc * n_trees + tree_orig[gt]] = orig_id[tree_node_off[gt] + self];
+            } else if constexpr (ROWS) {
+                leaf_pos[(block * n_trees + gt) * DL + dl] = uint16_t(r.x - 1u);
             } else if constexpr (VEC) {
                 const float4 v = leaf_vec[int64_t(r.x - 1u) * vec_stride4 + chunk];
                 accv[0] += double(v.x);
@@ -928,7 +947,7 @@ template <int MODE>
 ScoreFn pick_kernel(const treeens::LdsPlan &p, bool compact) {
     if (compact) {
         // compact packets: coded 64-document blocks, one workgroup per CU (not the trace)
-        if constexpr (MODE == kModeScore || MODE == kModeLeaves || MODE == kModeVector)
+        if constexpr (MODE == kModeScore || MODE == kModeLeaves || MODE == kModeVector || MODE == kModeRows)
             return p.coded && p.docs_per_block == 64 && p.lds_bytes == treeens::kLdsPerCu
                        ? score_kernel<64, treeens::kCompactTrees, false, false, true, MODE, true>
                        : nullptr;

@@ -23,6 +23,7 @@ constexpr int kModeLeaves = 1; // leaf ids
 constexpr int kModeUsage = 2;  // per-document feature bitmasks and their popcounts
 constexpr int kModeUsageSlot = 4; // the same with the bitmasks in the unused end of the tile slot
 constexpr int kModeVector = 3; // four components of vector-valued scores
+constexpr int kModeRows = 5;   // the lower 16 bits of each leaf's row of the leaf-vector table
 constexpr int kVecPerLaunch = 4;
 
 using ScoreFn = void (*)(const void *, int64_t, int32_t, int32_t, const uint2 *, int32_t,

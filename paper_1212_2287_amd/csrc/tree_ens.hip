@@ -311,6 +311,7 @@ struct tree_ens {
     int32_t n_bags = 1;
     int32_t vec_stride = 0;
     float *d_leaf_vec = nullptr;
+    uint32_t *d_tree_row0 = nullptr; // each packed tree's first row
     // coded models
     float *d_code_search = nullptr; // the coding chunks' search tables
     treeens::CodeChunk *d_code_chunks = nullptr;
@@ -397,6 +398,7 @@ void free_device(tree_ens *h) {
     (void)hipFree(h->d_tree_pos);
     (void)hipFree(h->d_orig_id);
     (void)hipFree(h->d_leaf_vec);
+    (void)hipFree(h->d_tree_row0);
     (void)hipFree(h->d_uniform_nodes);
     (void)hipFree(h->d_uniform_leaves);
     (void)hipFree(h->d_code_search);
@@ -576,6 +578,87 @@ int check_predict_args(const tree_ens *h, const float *X, int64_t n_docs, int32_
     return TREE_ENS_OK;
 }
 
+// Sums of leaf vectors from the rows the walk left in pos[block][packed tree][DL documents] (the lower
+// 16 bits of each): up to 4 * NV outputs in one pass over the trees. A workgroup takes 64 documents
+// (lanes), each of its waves a run of trees; kRowTrees trees' rows load together, their positions
+// while the trees before them are summed. Waves' sums are added in wave order.
+// Bound by the texture addresser, 96% busy with the gathers of the rows (26 cycles per 16-byte gather
+// of a wave): 50,000 documents, 1,000 trees, 8 outputs in 95 us, against 137 us for each of the two
+// walks it replaces, next to one walk of 101 us that stores the rows.
+constexpr int kRowThreads = 1024;
+constexpr int kRowTrees = 4;
+template <int DL, int NV>
+__global__ void __launch_bounds__(kRowThreads, 8)
+sum_rows_kernel(const uint16_t *__restrict__ pos, int64_t n_docs, int32_t n_trees, const uint32_t *__restrict__ tree_row0,
+                const float4 *__restrict__ leaf_vec, int32_t stride4, int32_t chunk, int32_t n_out, double scale,
+                float *__restrict__ scores) {
+    constexpr int kWaves = kRowThreads / 64;
+    __shared__ double red[4 * NV][kWaves][64];
+    const int lane = int(threadIdx.x) & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+    const int64_t doc = min<int64_t>(int64_t(blockIdx.x) * 64 + lane, n_docs - 1);
+    const uint16_t *my = pos + (doc / DL) * n_trees * DL + doc % DL;
+    const int lo = int(int64_t(n_trees) * wave / kWaves), hi = int(int64_t(n_trees) * (wave + 1) / kWaves);
+    double acc[4 * NV];
+#pragma unroll
+    for (int c = 0; c < 4 * NV; ++c)
+        acc[c] = 0.0;
+    uint32_t next[kRowTrees], first[kRowTrees];
+    auto fetch = [&](int t) { // past the last tree: the last one again, not used
+#pragma unroll
+        for (int u = 0; u < kRowTrees; ++u) {
+            next[u] = my[int64_t(min(t + u, n_trees - 1)) * DL];
+            first[u] = tree_row0[min(t + u, n_trees - 1)];
+        }
+    };
+    auto add = [&](const float4 (&v)[NV]) {
+#pragma unroll
+        for (int c = 0; c < NV; ++c) {
+            acc[4 * c] += double(v[c].x);
+            acc[4 * c + 1] += double(v[c].y);
+            acc[4 * c + 2] += double(v[c].z);
+            acc[4 * c + 3] += double(v[c].w);
+        }
+    };
+    auto load_row = [&](float4 (&v)[NV], int u) {
+        const uint32_t row = first[u] + ((next[u] - first[u]) & 0xFFFFu);
+#pragma unroll
+        for (int c = 0; c < NV; ++c)
+            v[c] = leaf_vec[int64_t(row) * stride4 + chunk + c];
+    };
+    fetch(lo);
+    int t = lo;
+    for (; t + kRowTrees <= hi; t += kRowTrees) {
+        float4 v[kRowTrees][NV];
+#pragma unroll
+        for (int u = 0; u < kRowTrees; ++u)
+            load_row(v[u], u);
+        fetch(t + kRowTrees);
+#pragma unroll
+        for (int u = 0; u < kRowTrees; ++u)
+            add(v[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kRowTrees - 1; ++u) {
+        if (t + u < hi) {
+            float4 v[NV];
+            load_row(v, u);
+            add(v);
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 4 * NV; ++c)
+        red[c][wave][lane] = acc[c];
+    __syncthreads();
+    const int c = wave, oc = 4 * chunk + c; // one wave per output
+    if (c < 4 * NV && oc < n_out && int64_t(blockIdx.x) * 64 + lane < n_docs) {
+        double sum = 0.0;
+        for (int w = 0; w < kWaves; ++w)
+            sum += red[c][w][lane];
+        scores[doc * n_out + oc] = float(sum * scale);
+    }
+}
+
 // Threshold codes of all documents, rows of n_cols.
 void launch_coding(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features,
                    int32_t code_shift, uint16_t *codes) {
@@ -686,7 +769,7 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
             return fail(TREE_ENS_E_ARG, "too many documents for one launch");
     }
     // compact packets, where the model has them, for every mode but the feature trace
-    const bool cp = h->cp_k > 0 && (MODE == kModeScore || MODE == kModeLeaves || MODE == kModeVector);
+    const bool cp = h->cp_k > 0 && MODE != kModeUsage && MODE != kModeUsageSlot;
     ScoreFn fn = pick_kernel<MODE>(h->plan, cp);
     if (!fn)
         return fail(TREE_ENS_E_ARG, "unsupported document block size");
@@ -894,7 +977,7 @@ int launch_uniform_predict(const tree_ens *h, hipStream_t stream, const float *X
 
 // Leaf ids. Large outputs: the walk stores 16-bit leaf positions in its own (block, packed tree)
 // order and leaf_ids_kernel turns them into the output's rows, in chunks of documents whose
-// positions take at most kLeafScratchBytes (they stay in the last-level cache). 1,000 trees of 32
+// positions take at most kPositionBytes (they stay in the last-level cache). 1,000 trees of 32
 // leaves, 30,011 documents: 383 us with ids stored by the walk, 103 us this way (62 us the walk,
 // 37 us the second kernel at 4.8 TB/s).
 // The walk stores ids directly where that is as fast: outputs of at most kLeafDirectBytes (the
@@ -906,52 +989,112 @@ int launch_uniform_predict(const tree_ens *h, hipStream_t stream, const float *X
 // cannot be allocated.
 constexpr int32_t kLeafDirectTrees = 128;
 constexpr int64_t kLeafDirectBytes = int64_t(8) << 20;
-constexpr int64_t kLeafScratchBytes = int64_t(128) << 20;
+constexpr int64_t kPositionBytes = int64_t(256) << 20;
 
 bool leaves_direct(int32_t n_trees, int64_t n_docs) {
     const int64_t most = n_trees < 2 * kLeafDirectTrees ? 2 * kLeafDirectBytes : kLeafDirectBytes;
     return n_trees < kLeafDirectTrees || n_docs <= most / 4 / n_trees;
 }
 
-int launch_leaves(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs,
-                  int32_t n_features, int32_t *leaf_ids) {
+// The walk's leaf positions in chunks of documents (MODE: kModeLeaves or kModeRows), each chunk
+// followed by `then(pos, first document, documents)`. `taken` is false (and nothing was launched) in
+// calls captured into a graph and when the scratch cannot be allocated.
+template <int MODE, typename Then>
+int walk_positions(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features,
+                   bool *taken, Then &&then) {
     const int dl = h->plan.docs_per_block;
+    const int64_t n_blocks = (n_docs + dl - 1) / dl;
+    const int64_t block_bytes = int64_t(h->n_trees) * dl * int64_t(sizeof(uint16_t));
+    const int64_t per = std::min(n_blocks, std::max<int64_t>(1, kPositionBytes / block_bytes / (64 / dl) * (64 / dl)));
+    *taken = false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess)
         cap = hipStreamCaptureStatusNone;
     (void)hipGetLastError();
-    const int64_t n_blocks = (n_docs + dl - 1) / dl;
-    const int64_t block_bytes = int64_t(h->n_trees) * dl * int64_t(sizeof(uint16_t));
-    const int64_t per = std::min(n_blocks, std::max<int64_t>(1, kLeafScratchBytes / block_bytes));
     void *pos = nullptr;
-    if (cap == hipStreamCaptureStatusNone && !leaves_direct(h->n_trees, n_docs) &&
-        hipMallocAsync(&pos, size_t(per * block_bytes), stream) != hipSuccess) {
-        pos = nullptr;
+    if (cap != hipStreamCaptureStatusNone || hipMallocAsync(&pos, size_t(per * block_bytes), stream) != hipSuccess) {
         (void)hipGetLastError();
+        return TREE_ENS_OK;
     }
-    if (!pos)
-        return launch_predict<kModeLeaves>(h, stream, X, n_docs, n_features, nullptr, leaf_ids);
-    // compact packets store input node ids, the other records positions in the packed tree
-    const int32_t *map = h->cp_k > 0 ? nullptr : h->d_orig_id;
-    auto *fn = dl == 64 ? leaf_ids_kernel<64> : dl == 32 ? leaf_ids_kernel<32> : dl == 16 ? leaf_ids_kernel<16> : leaf_ids_kernel<8>;
-    const int64_t tiles = (h->n_trees + kIdTrees - 1) / kIdTrees;
+    *taken = true;
     int rc = TREE_ENS_OK;
     for (int64_t b = 0; b < n_blocks && rc == TREE_ENS_OK; b += per) {
-        const int64_t doc0 = b * dl, nb = std::min(per, n_blocks - b);
-        const int64_t nd = std::min(nb * dl, n_docs - doc0);
-        rc = launch_predict<kModeLeaves>(h, stream, X + doc0 * n_features, nd, n_features, nullptr, nullptr,
-                                         nullptr, 0, ScratchSource::kHandle, static_cast<uint16_t *>(pos));
+        const int64_t doc0 = b * dl, nd = std::min(std::min(per, n_blocks - b) * dl, n_docs - doc0);
+        rc = launch_predict<MODE>(h, stream, X + doc0 * n_features, nd, n_features, nullptr, nullptr, nullptr, 0,
+                                  ScratchSource::kHandle, static_cast<uint16_t *>(pos));
         if (rc != TREE_ENS_OK)
             break;
-        hipLaunchKernelGGL(fn, dim3(unsigned((nb + kXcds - 1) / kXcds * kXcds * tiles)), dim3(kIdThreads), 0, stream,
-                           static_cast<const uint16_t *>(pos), nd, h->n_trees, h->d_tree_pos,
-                           h->d_tree_node_off, map, leaf_ids + doc0 * h->n_trees);
+        then(static_cast<const uint16_t *>(pos), doc0, nd);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
-            rc = hip_fail(e, "leaf id launch");
+            rc = hip_fail(e, "kernel launch");
     }
     const hipError_t e = hipFreeAsync(pos, stream);
     return rc != TREE_ENS_OK ? rc : e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "hipFreeAsync");
+}
+
+// The kernel for a plan's document blocks.
+template <typename Fn>
+Fn pick_block(int dl, Fn f64, Fn f32, Fn f16, Fn f8) {
+    return dl == 64 ? f64 : dl == 32 ? f32 : dl == 16 ? f16 : f8;
+}
+
+int launch_leaves(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs,
+                  int32_t n_features, int32_t *leaf_ids) {
+    bool taken = false;
+    if (!leaves_direct(h->n_trees, n_docs)) {
+        const int dl = h->plan.docs_per_block;
+        // compact packets store input node ids, the other records positions in the packed tree
+        const int32_t *map = h->cp_k > 0 ? nullptr : h->d_orig_id;
+        auto *fn = pick_block(dl, leaf_ids_kernel<64>, leaf_ids_kernel<32>, leaf_ids_kernel<16>, leaf_ids_kernel<8>);
+        const int64_t tiles = (h->n_trees + kIdTrees - 1) / kIdTrees;
+        const int rc = walk_positions<kModeLeaves>(
+            h, stream, X, n_docs, n_features, &taken, [&](const uint16_t *pos, int64_t doc0, int64_t nd) {
+                const int64_t nb = (nd + dl - 1) / dl;
+                hipLaunchKernelGGL(fn, dim3(unsigned((nb + kXcds - 1) / kXcds * kXcds * tiles)), dim3(kIdThreads), 0,
+                                   stream, pos, nd, h->n_trees, h->d_tree_pos, h->d_tree_node_off, map,
+                                   leaf_ids + doc0 * h->n_trees);
+            });
+        if (taken)
+            return rc;
+    }
+    return launch_predict<kModeLeaves>(h, stream, X, n_docs, n_features, nullptr, leaf_ids);
+}
+
+// Vector-valued scores. More than kVecPerLaunch outputs of enough documents: the walk stores each
+// leaf's row once, and sum_rows_kernel adds up to eight outputs per pass; else one walk per four.
+// Smaller batches do not pay for the second launch and the scratch (8 outputs, 1,000 trees: 2,000
+// documents 33 us by two walks against 40, 5,000 documents 51 against 47; 100 trees: 1,024 documents
+// 24 against 25, 10,000 documents 32 against 25), nor do many trees of few documents (4,000 trees of 8
+// leaves, 5,000 documents: 83 against 110, 20,000 documents of 2,000 trees: 161 against 139). Up to four outputs one walk does it all.
+// Nor do models whose chunks hold fewer than kRowDocs documents (64 of them fill a workgroup):
+// 10,000 trees of 8 leaves, 6 outputs, 50,000 documents in chunks of 6,500: 1,474 against 2,194 us.
+constexpr int64_t kRowDocs = 32768;
+bool rows_pay(const tree_ens *h, int64_t n_docs) {
+    return h->n_outputs > kVecPerLaunch && n_docs >= std::max<int64_t>(4096, 4 * int64_t(h->n_trees)) &&
+           h->n_trees * kRowDocs * int64_t(sizeof(uint16_t)) <= kPositionBytes;
+}
+
+int launch_vector(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features, float *scores) {
+    bool taken = false;
+    if (rows_pay(h, n_docs)) {
+        const int dl = h->plan.docs_per_block, n_out = h->n_outputs;
+        auto *two = pick_block(dl, sum_rows_kernel<64, 2>, sum_rows_kernel<32, 2>, sum_rows_kernel<16, 2>, sum_rows_kernel<8, 2>);
+        auto *one = pick_block(dl, sum_rows_kernel<64, 1>, sum_rows_kernel<32, 1>, sum_rows_kernel<16, 1>, sum_rows_kernel<8, 1>);
+        const double scale = 1.0 / double(h->n_bags);
+        const int rc = walk_positions<kModeRows>(
+            h, stream, X, n_docs, n_features, &taken, [&](const uint16_t *pos, int64_t doc0, int64_t nd) {
+                const int chunks = (n_out + kVecPerLaunch - 1) / kVecPerLaunch;
+                for (int c = 0; c < chunks; c += 2)
+                    hipLaunchKernelGGL(c + 1 < chunks ? two : one, dim3(unsigned((nd + 63) / 64)), dim3(kRowThreads), 0,
+                                       stream, pos, nd, h->n_trees, h->d_tree_row0,
+                                       reinterpret_cast<const float4 *>(h->d_leaf_vec), h->vec_stride / 4, c, n_out,
+                                       scale, scores + doc0 * n_out);
+            });
+        if (taken)
+            return rc;
+    }
+    return launch_predict<kModeVector>(h, stream, X, n_docs, n_features, scores, nullptr);
 }
 
 } // namespace
@@ -1075,8 +1218,12 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
         e = hipMalloc(reinterpret_cast<void **>(&h->d_scratch), kScratchDoubles * sizeof(double));
     if (e == hipSuccess)
         e = hipEventCreateWithFlags(&h->scratch_done, hipEventDisableTiming);
-    if (e == hipSuccess && p.n_outputs > 1)
+    if (e == hipSuccess && p.n_outputs > 1) {
+        p.leaf_vec.resize(size_t(p.leaf_rows) * size_t(p.vec_stride));
         e = upload(&h->d_leaf_vec, p.leaf_vec);
+        if (e == hipSuccess)
+            e = upload(&h->d_tree_row0, p.tree_row0);
+    }
     if (e == hipSuccess && !cg_code.empty()) {
         e = hipModuleLoadData(&h->cg_module, cg_code.data());
         if (e == hipSuccess)
@@ -1123,7 +1270,7 @@ int tree_ens_predict(const tree_ens_t *h, void *stream, const float *X, int64_t 
         return e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "kernel launch");
     }
     if (h->n_outputs > 1)
-        return launch_predict<kModeVector>(h, s, X, n_docs, n_features, scores, nullptr);
+        return launch_vector(h, s, X, n_docs, n_features, scores);
     if (h->cg_fn) {
         // the model's own kernel: one document per thread
         const float *x = X;
