@@ -51,7 +51,7 @@ HBM_PEAK_GBS = 8000.0
 LDS_CLK_PER_INSTR = 2.2
 LDS_ISSUE_NODE_GBS = N_CU * CLOCK_HZ * 64 * 8 / (2 * LDS_CLK_PER_INSTR) / 1e9  # 71,494 GB/s
 CSRC = os.path.join(ROOT, "paper_1212_2287_amd", "csrc")
-KERNEL_SRC = [os.path.join(CSRC, n) for n in ("tree_ens.hip", "score.hip", "score.hpp", "uniform.hip", "pack.cpp", "pack.hpp")]
+KERNEL_SRC = [os.path.join(CSRC, n) for n in ("tree_ens.hip", "score.hip", "score.hpp", "uniform.hip", "term.hip", "pack.cpp", "pack.hpp")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 

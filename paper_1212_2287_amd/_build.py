@@ -22,7 +22,7 @@ HIP_FLAGS = [
 
 
 SCORE_MODES = 6  # modes of score.hip (score.hpp)
-HIP_SOURCES = ("tree_ens", "uniform", "topk")
+HIP_SOURCES = ("tree_ens", "uniform", "term", "topk")
 
 
 def _hipcc() -> str:

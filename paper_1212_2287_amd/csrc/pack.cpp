@@ -45,6 +45,145 @@ NodeRec complete_leaf(NodeRec r, uint32_t col_mask) {
     return NodeRec{uint32_t(b), uint32_t(b >> 32)};
 }
 
+// A tree of terminal packets while it is cut and laid out. nodes: its packed records.
+class TermTree {
+public:
+    // what a record's splits become: column, threshold code (kCompactNeverRight: never right)
+    struct Split {
+        uint32_t col, code;
+        uint32_t record() const { return code << kCompactThrShift | col << kCompactColShift; }
+    };
+    struct Node { // of a piece
+        Split split{0, kCompactNeverRight};
+        int32_t left = -1, right = -1; // piece nodes; -1: a terminal
+        uint32_t slot[kTermSlotWords] = {};
+    };
+    using Piece = std::vector<Node>; // breadth first, the children of a node next to each other
+
+    // link(k): first child of packed node k (k itself for a leaf); split(k), value(k)
+    template <typename Link, typename SplitOf, typename Value>
+    TermTree(int32_t n, Link link, SplitOf split, Value value) : n_(n), link_(size_t(n)), split_(size_t(n)), value_(size_t(n)), cut_(size_t(n), 0) {
+        for (int32_t k = 0; k < n; k++) {
+            link_[size_t(k)] = link(k);
+            if (link_[size_t(k)] == k)
+                value_[size_t(k)] = value(k);
+            else
+                split_[size_t(k)] = split(k);
+        }
+        measure();
+    }
+
+    // Pieces of at most kTermMaxInner inner nodes each; false if one subtree cannot be cut.
+    bool pieces(std::vector<Piece> &out) {
+        while (inner_[0] > kTermMaxInner) {
+            // the largest subtree that fits a piece below its path
+            std::vector<int32_t> depth(size_t(n_), 0), parent(size_t(n_), -1);
+            int32_t best = -1;
+            for (int32_t k = 0; k < n_; k++) {
+                if (k > 0 && parent[size_t(k)] < 0)
+                    continue; // below a cut
+                if (k > 0 && inner_[size_t(k)] > 0 && inner_[size_t(k)] + depth[size_t(k)] <= kTermMaxInner &&
+                    (best < 0 || inner_[size_t(k)] > inner_[size_t(best)]))
+                    best = k;
+                if (!leaf(k))
+                    for (int32_t c : {link_[size_t(k)], link_[size_t(k)] + 1}) {
+                        depth[size_t(c)] = depth[size_t(k)] + 1;
+                        parent[size_t(c)] = k;
+                    }
+            }
+            if (best < 0)
+                return false;
+            std::vector<int32_t> path; // the root first, `best` last
+            for (int32_t k = best; k >= 0; k = parent[size_t(k)])
+                path.insert(path.begin(), k);
+            out.push_back(lay_out(path));
+            cut_[size_t(best)] = 1;
+            measure();
+        }
+        out.push_back(lay_out({0}));
+        return true;
+    }
+
+private:
+    int32_t n_;
+    std::vector<int32_t> link_;
+    std::vector<Split> split_;
+    std::vector<uint32_t> value_;
+    std::vector<uint8_t> cut_;
+    std::vector<int32_t> height_, inner_; // inner nodes: those of height above 2
+
+    bool leaf(int32_t k) const { return cut_[size_t(k)] || link_[size_t(k)] == k; }
+
+    void measure() { // children follow their parents in the packed order
+        height_.assign(size_t(n_), 0);
+        inner_.assign(size_t(n_), 0);
+        for (int32_t k = n_ - 1; k >= 0; k--) {
+            if (leaf(k))
+                continue;
+            const size_t l = size_t(link_[size_t(k)]);
+            height_[size_t(k)] = 1 + std::max(height_[l], height_[l + 1]);
+            if (height_[size_t(k)] > 2)
+                inner_[size_t(k)] = 1 + inner_[l] + inner_[l + 1];
+        }
+    }
+
+    // The piece below path.back(), under the path's splits with value 0 off the path.
+    Piece lay_out(const std::vector<int32_t> &path) const {
+        Piece piece(1);
+        std::vector<int32_t> from = {path.size() > 1 ? -2 : path[0]}; // packed node; -1: value 0; -2: the path
+        size_t on_path = 0;
+        for (size_t i = 0; i < piece.size(); i++) {
+            int32_t kids[2] = {-1, -1};
+            if (from[i] == -2) {
+                const int32_t k = path[on_path++];
+                piece[i].split = split_[size_t(k)];
+                const bool end = on_path + 1 == path.size();
+                kids[path[on_path] != link_[size_t(k)]] = end ? path[on_path] : -2;
+            } else if (from[i] < 0 || leaf(from[i]) || height_[size_t(from[i])] <= 2) {
+                terminal(from[i], piece[i].slot);
+                continue;
+            } else {
+                const int32_t k = from[i];
+                piece[i].split = split_[size_t(k)];
+                kids[0] = link_[size_t(k)];
+                kids[1] = kids[0] + 1;
+            }
+            piece[i].left = int32_t(piece.size());
+            piece[i].right = piece[i].left + 1;
+            for (int32_t c : kids) {
+                piece.emplace_back();
+                from.push_back(c);
+            }
+        }
+        return piece;
+    }
+
+    void terminal(int32_t k, uint32_t *slot) const {
+        const Split none{0, kCompactNeverRight};
+        slot[0] = slot[1] = slot[2] = none.record();
+        if (k < 0)
+            return; // value 0
+        auto values = [&](int32_t c, uint32_t *split, uint32_t *v) { // of a child of height at most 1
+            if (leaf(c)) {
+                v[0] = cut_[size_t(c)] ? 0u : value_[size_t(c)];
+                return;
+            }
+            *split = split_[size_t(c)].record();
+            for (int32_t j = 0; j < 2; j++) {
+                const size_t g = size_t(link_[size_t(c)] + j);
+                v[j] = cut_[g] ? 0u : value_[g];
+            }
+        };
+        if (leaf(k)) {
+            values(k, &slot[1], slot + 4);
+            return;
+        }
+        slot[0] = split_[size_t(k)].record();
+        values(link_[size_t(k)], &slot[1], slot + 4);
+        values(link_[size_t(k)] + 1, &slot[2], slot + 6);
+    }
+};
+
 // avg_tree_bytes: mean packed size of a tree, to pick how many trees a lane walks at once.
 // elem_bytes: 4 for float features, 2 for codes.
 LdsPlan plan_lds(int32_t n_cols, double avg_tree_bytes, int elem_bytes) {
@@ -856,6 +995,136 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             }
             for (int32_t m : most)
                 p.cp_total_rounds += m;
+        }
+    }
+
+    // ---- terminal packets (see TermPlan) -----------------------------------------------------------
+    {
+        constexpr int32_t W = kPacketWalkers, K = kTermTrees;
+        bool ok = !vec && plan.coded && n_small == n_trees && n_trees > 0 &&
+                  term_window_base(n_cols) + W * K * kTermWindowBytes <= kLdsPerCu;
+        for (size_t f = 0; ok && f < thr_of.size(); f++)
+            ok = thr_of[f].size() < kCompactNeverRight;
+        std::vector<TermTree::Piece> pieces;
+        const int shift_t = plan.narrow ? 16 : kWideChildShift;
+        const uint32_t cmask = plan.narrow ? kNarrowColMask : kWideColMask;
+        for (int32_t t = 0; ok && t < n_trees; t++) {
+            const size_t base = p.tree_node_off[size_t(t)];
+            const NodeRec *tree = p.nodes.data() + base;
+            const int64_t flat = tree_offsets[p.tree_orig[size_t(t)]];
+            TermTree tt(
+                int32_t(p.tree_node_off[size_t(t) + 1] - base),
+                [&](int32_t k) { return (tree[k].w & cmask) == 0 ? k : int32_t(tree[k].w >> shift_t); },
+                [&](int32_t k) {
+                    const size_t i = size_t(flat + p.orig_id[base + size_t(k)]);
+                    return TermTree::Split{uint32_t(feature[i]) + 1u,
+                                           std::isnan(canon(threshold[i])) ? kCompactNeverRight : thr_rank[i] + 1u};
+                },
+                [&](int32_t k) { return float_bits(value[flat + p.orig_id[base + size_t(k)]]); });
+            ok = tt.pieces(pieces);
+            // a model cut into many pieces keeps its other packets
+            ok = ok && int64_t(pieces.size()) <= int64_t(t + 1) + 8 * int64_t(n_trees);
+        }
+        const int32_t n_pieces = int32_t(pieces.size()), n_groups = (n_pieces + K - 1) / K;
+        const int32_t cap = kTermWindowBytes - 8;
+        const int32_t max_ng = (kCompactHeaderBytes / 4 - kCompactHeaderWords) / K;
+        // bytes of a piece's pairs (a lone terminal: one pair of itself)
+        auto body = [&](int32_t i) { return int32_t(4 * std::max<size_t>(2, pieces[size_t(i)].size() - 1)); };
+        std::vector<std::vector<std::pair<int32_t, int32_t>>> runs(static_cast<size_t>(W)); // first round, rounds
+        for (int32_t v = 0; v < W && ok; v++) {
+            std::vector<int32_t> used(static_cast<size_t>(K), 0);
+            for (int32_t r = 0; v + r * W < n_groups; r++) {
+                const int32_t g = v + r * W;
+                bool more = !runs[size_t(v)].empty() && runs[size_t(v)].back().second < max_ng;
+                for (int32_t i = 0; i < K && more; i++)
+                    more = g * K + i >= n_pieces || used[size_t(i)] + body(g * K + i) <= cap;
+                if (!more) {
+                    runs[size_t(v)].push_back({r, 0});
+                    std::fill(used.begin(), used.end(), 0);
+                }
+                runs[size_t(v)].back().second++;
+                for (int32_t i = 0; i < K; i++)
+                    if (g * K + i < n_pieces)
+                        used[size_t(i)] += body(g * K + i);
+            }
+        }
+        int32_t per = 0;
+        for (const auto &r : runs)
+            per = std::max(per, int32_t(r.size()));
+        // the kernel addresses packets and slots with 32-bit byte offsets
+        ok = ok && int64_t(W) * per * kTermSlotPacketWords * 4 < (int64_t(1) << 31);
+        if (ok) {
+            p.term.per_wave = per;
+            p.term.n_pieces = n_pieces;
+            p.term_packets.assign(size_t(W) * size_t(per) * size_t(kTermPacketWords), 0u);
+            p.term_slots.assign(size_t(W) * size_t(per) * size_t(kTermSlotPacketWords), 0u);
+            std::vector<int32_t> most(static_cast<size_t>(per), 0);
+            const uint32_t zero = (kCompactNeverRight << kCompactThrShift) | uint32_t(cap);
+            const uint32_t none = kCompactNeverRight << kCompactThrShift;
+            for (int32_t v = 0; v < W; v++) {
+                for (int32_t q = 0; q < per; q++) {
+                    const size_t at = size_t(v) * size_t(per) + size_t(q);
+                    uint32_t *img = p.term_packets.data() + at * size_t(kTermPacketWords);
+                    uint32_t *slots = p.term_slots.data() + at * size_t(kTermSlotPacketWords);
+                    uint32_t *hdr = img + kCompactWindowBytes / 4;
+                    // past a wave's last packet: a group of idle slots
+                    const bool idle = size_t(q) >= runs[size_t(v)].size();
+                    const int32_t r0 = idle ? 0 : runs[size_t(v)][size_t(q)].first;
+                    const int32_t ng = idle ? 1 : runs[size_t(v)][size_t(q)].second;
+                    if (!idle) {
+                        p.term.max_groups = std::max(p.term.max_groups, ng);
+                        most[size_t(q)] = std::max(most[size_t(q)], ng);
+                    }
+                    hdr[0] = uint32_t(ng);
+                    uint32_t off[K] = {};
+                    for (int32_t i = 0; i < K; i++) {
+                        // the zero pair at the end of each window: a left-side terminal of value 0
+                        const size_t zw = size_t(i * kTermWindowBytes + cap) / 4;
+                        img[zw] = img[zw + 1] = zero;
+                        for (size_t w = zw; w < zw + 2; w++)
+                            for (int s3 = 0; s3 < 3; s3++)
+                                slots[w * kTermSlotWords + size_t(s3)] = none;
+                    }
+                    for (int32_t j = 0; j < ng; j++) {
+                        for (int32_t i = 0; i < K; i++) {
+                            const int32_t t = (v + (r0 + j) * W) * K + i;
+                            uint32_t &root = hdr[kCompactHeaderWords + j * K + i];
+                            if (idle || t >= n_pieces) {
+                                root = zero;
+                                continue;
+                            }
+                            const TermTree::Piece &piece = pieces[size_t(t)];
+                            const uint32_t o = off[i];
+                            // node k's place among the pairs (a lone root: the first of its own pair)
+                            auto place = [&](size_t k) { return k == 0 ? o : o + uint32_t(k - 1) * 4u; };
+                            auto record = [&](size_t k) {
+                                const TermTree::Node &nd = piece[k];
+                                if (nd.left >= 0)
+                                    return nd.split.record() | place(size_t(nd.left));
+                                const uint32_t pos = place(k);
+                                return (((pos >> 2) & 1u) ? 0u : kCompactNeverRight << kCompactThrShift) | pos;
+                            };
+                            auto put = [&](size_t k) {
+                                const size_t w = size_t(uint32_t(i * kTermWindowBytes) + place(k)) / 4;
+                                img[w] = record(k);
+                                if (piece[k].left < 0)
+                                    std::memcpy(slots + w * kTermSlotWords, piece[k].slot, sizeof piece[k].slot);
+                            };
+                            root = record(0);
+                            if (piece.size() == 1) {
+                                put(0);
+                                img[size_t(uint32_t(i * kTermWindowBytes) + o) / 4 + 1] = root;
+                            } else {
+                                for (size_t k = 1; k < piece.size(); k++)
+                                    put(k);
+                            }
+                            off[i] += uint32_t(body(t));
+                        }
+                    }
+                }
+            }
+            for (int32_t m : most)
+                p.term.total_rounds += m;
         }
     }
 

@@ -128,6 +128,36 @@ constexpr uint32_t kCompactNeverRight = 2047u;
 constexpr int kCompactMaxColumns = 1023;  // column index field
 constexpr int kCompactMaxTreeNodes = 511; // root + 255 pairs: 2,040 bytes, one 2 KiB window
 constexpr int kCompactCodeShift = 5;
+// Terminal packets (scores only): coded models of one value per leaf, at most 2,046 distinct thresholds
+// per feature and at most 767 features, in 64-document blocks with one workgroup per CU. The records are the compact ones, but the walk ends above the lowest levels: a maximal
+// subtree of depth at most 2 is one terminal node (column 0, absorbing, like a compact leaf), whose
+// slot in device memory holds its up to three splits and four leaf values. A tree of 256 leaves
+// walked this way has about 240 records instead of 511, so a wave holds K = 4 trees in 1 KiB windows
+// where the compact packets hold two, and a walk is about two steps shorter.
+//   A tree whose records outgrow a window is cut into pieces: a subtree becomes a leaf of value 0 and,
+// below a copy of the path to it whose other branches end in leaves of value 0, a piece of its own
+// (the pieces' sums add up to the tree's).
+//   Packets are laid out as the compact ones (windows, then the header row; groups of K pieces, wave v
+// takes groups v, v + 16, ...; every packet has a group). Slot of the terminal at byte position o of
+// window i of packet q: words [8 * (q * 1024 + i * 256 + o / 4), ...):
+//   0, 1, 2  the subtree's root split, its left child's and its right child's, as records without a
+//            pair (code << 21 | column << 11; a leaf's: never right, column 0)
+//   4 .. 7   the values of its leaves, left to right: left-left, left-right, right-left, right-right
+struct TermPlan {
+    int32_t per_wave;     // packets per wave (0: the model has none)
+    int32_t max_groups;   // groups in the fullest packet
+    int64_t total_rounds; // the planner's rounds
+    int32_t n_pieces;
+};
+constexpr int kTermTrees = 4;         // K: trees per lane, one window each
+constexpr int kTermWindowBytes = 1024;
+constexpr int kTermMaxInner = 127;    // inner nodes of a piece (a pair each; the last pair of a window is the zero pair)
+constexpr int kTermSlotWords = 8;
+constexpr int kTermPacketWords = kCompactPacketBytes / 4; // four windows and the header row
+constexpr int kTermSlotPacketWords = kTermTrees * kTermWindowBytes / 4 * kTermSlotWords;
+// LDS byte address of the first window
+constexpr int32_t term_window_base(int32_t n_cols) { return ((n_cols + 1) * 128 + kTermWindowBytes - 1) & ~(kTermWindowBytes - 1); }
+
 // LDS byte address of the first window (windows are aligned to their size, at most 2 KiB)
 inline int32_t compact_window_base(int32_t xs_bytes) { return (xs_bytes + 2047) & ~2047; }
 
@@ -256,6 +286,10 @@ struct Packed {
     std::vector<uint32_t> cp_packets;
     std::vector<uint32_t> cp_leaf;
     std::vector<int32_t> cp_leaf_id;
+    // terminal packets (see TermPlan): wave v's packet q is packet v * per_wave + q
+    TermPlan term{};
+    std::vector<uint32_t> term_packets;
+    std::vector<uint32_t> term_slots;
     // uniform evaluation (see UniformPlan)
     UniformPlan uniform{};
     std::vector<uint32_t> uniform_nodes;

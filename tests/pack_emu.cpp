@@ -637,6 +637,95 @@ int emu_walk_compact(int32_t n_trees, const int64_t *tree_offsets, const int32_t
     return 0;
 }
 
+// All documents through the terminal packets (records as compact ones; the walk ends at subtrees of
+// depth 2, whose splits and leaf values are in the terminals' slots), the way the kernel addresses
+// them. Scores as emu_walk; returns 2 when the model has none, else 0 or 1 with a message, or a negative
+// packer status. plan_out: packets per wave, groups of the fullest packet, pieces.
+int emu_term(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feature, const float *threshold,
+             const int32_t *left, const int32_t *right, const float *value, uint32_t flags, const float *X,
+             int64_t n_docs, int32_t n_features, double *scores, int32_t *plan_out) {
+    treeens::Packed p;
+    std::string err;
+    const int rc = treeens::pack_model(n_trees, tree_offsets, feature, threshold, left, right, value, 1, flags, p, err);
+    if (rc != treeens::kOk) {
+        g_msg = err;
+        return rc;
+    }
+    const treeens::TermPlan &t = p.term;
+    if (t.per_wave == 0) {
+        g_msg = "no terminal packets";
+        return 2;
+    }
+    plan_out[0] = t.per_wave;
+    plan_out[1] = t.max_groups;
+    plan_out[2] = t.n_pieces;
+    constexpr int W = treeens::kPacketWalkers, K = treeens::kTermTrees, kWin = treeens::kTermWindowBytes;
+    const int64_t n_packets = int64_t(W) * t.per_wave;
+    if (p.term_packets.size() != size_t(n_packets) * treeens::kTermPacketWords ||
+        p.term_slots.size() != size_t(n_packets) * treeens::kTermSlotPacketWords || n_packets * treeens::kTermSlotPacketWords * 4 >= (int64_t(1) << 31))
+        return bad("term: wrong array sizes");
+    const uint32_t base = uint32_t(treeens::term_window_base(p.n_cols));
+    if (base % kWin || base < uint32_t(p.n_cols + 1) * 128u || base + W * K * kWin > uint32_t(treeens::kLdsPerCu))
+        return bad("term: windows outside the LDS");
+    int64_t groups = 0;
+    for (int64_t d = 0; d < n_docs; d++)
+        scores[d] = 0.0;
+    std::vector<uint16_t> x(static_cast<size_t>(p.n_cols) + 1);
+    for (int64_t d = 0; d < n_docs; d++) {
+        x[0] = 31;
+        for (int f = 0; f < p.n_cols; f++) {
+            const uint32_t code = code_of(p, f, X[d * n_features + f]);
+            if (code >= treeens::kCompactNeverRight)
+                return bad("term: a code reaches the never-right threshold");
+            x[size_t(f) + 1] = uint16_t(code << treeens::kCompactCodeShift | 31u);
+        }
+        auto right_of = [&](uint32_t r, bool *ok) {
+            const uint32_t col = (r >> treeens::kCompactColShift) & 0x3FFu;
+            *ok = col <= uint32_t(p.n_cols);
+            return *ok && uint32_t(x[col]) >= (r >> 16);
+        };
+        for (int64_t q = 0; q < n_packets; q++) {
+            const uint32_t *img = p.term_packets.data() + q * treeens::kTermPacketWords;
+            const uint32_t *hdr = img + treeens::kCompactWindowBytes / 4;
+            const int ng = int(hdr[0]);
+            if (ng < 1 || treeens::kCompactHeaderWords + ng * K > treeens::kCompactHeaderBytes / 4)
+                return bad("term: header out of range");
+            groups += d == 0 ? ng : 0;
+            for (int j = 0; j < ng; j++) {
+                for (int i = 0; i < K; i++) {
+                    uint32_t r = hdr[treeens::kCompactHeaderWords + j * K + i];
+                    bool ok = true;
+                    for (int steps = 0;; steps++) {
+                        const uint32_t pair = r & 0x3F8u; // the window base is OR-ed to it
+                        const bool inner = ((r >> 4) & 0x1FF80u) >= 128u;
+                        const uint32_t next = img[(uint32_t(i) * kWin + pair) / 4 + (right_of(r, &ok) ? 1 : 0)];
+                        if (!ok)
+                            return bad("term: a record reads outside the document tile");
+                        if (!inner) {
+                            if (next != r)
+                                return bad("term: a terminal does not absorb a further step");
+                            break;
+                        }
+                        if (steps > p.max_depth)
+                            return bad("term: walk longer than the deepest tree");
+                        r = next;
+                    }
+                    const uint32_t *slot = p.term_slots.data() + q * treeens::kTermSlotPacketWords +
+                                           ((r & 0x3FCu) + uint32_t(i) * kWin) / 4 * treeens::kTermSlotWords;
+                    const bool up = right_of(slot[0], &ok);
+                    const bool down = ok && right_of(slot[up ? 2 : 1], &ok);
+                    if (!ok)
+                        return bad("term: a slot reads outside the document tile");
+                    scores[d] += double(as_float(slot[4 + (up ? 2 : 0) + (down ? 1 : 0)]));
+                }
+            }
+        }
+    }
+    if (n_docs > 0 && groups * K < t.n_pieces)
+        return bad("term: fewer groups than the pieces need");
+    return 0;
+}
+
 // All documents through the tables of uniform evaluation (every node of a shallow tree, padded to a
 // complete one, evaluated in the kernel's arithmetic: 16-bit differences whose sign bits select and
 // then form the leaf's place). Scores as emu_walk; returns 2 when the model has no such tables, else
