@@ -520,6 +520,8 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         return depth_of[size_t(x)] > depth_of[size_t(y)];
     });
     p.n_small = n_small;
+    for (int32_t t = 0; t < n_trees; t++)
+        p.mean_steps += (lock_key[size_t(t)] + 1.0) / double(n_trees);
     p.nodes.reserve(size_t(n_nodes));
     p.orig_id.reserve(size_t(n_nodes));
     p.tree_node_off.resize(size_t(n_trees) + 1, 0);
@@ -653,8 +655,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             const Tile &tl = p.tiles[size_t(i)];
             const int32_t r = (tl.tree_end - tl.tree_begin + round - 1) / round;
             p.level_max_rounds[k] = std::max(p.level_max_rounds[k], r);
-            if (k == 0)
-                p.total_rounds += r;
         }
     }
     p.tile_recs.resize(p.tiles.size());
@@ -778,13 +778,11 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             p.pk_zero_rec = pk_zero;
             p.pk_per_walker = per;
             p.packets.assign(size_t(W) * size_t(per) * size_t(sub), NodeRec{0u, 0u});
-            std::vector<int32_t> most(static_cast<size_t>(per), 0);
             const NodeRec zero_leaf{zero_record_value(plan, vec), (uint32_t(pk_zero) / 8u) << shift};
             for (int32_t v = 0; v < W; v++) {
                 for (size_t q = 0; q < runs[size_t(v)].size(); q++) {
                     const int32_t r0 = runs[size_t(v)][q].first, ng = runs[size_t(v)][q].second;
                     p.pk_max_groups = std::max(p.pk_max_groups, ng);
-                    most[q] = std::max(most[q], ng);
                     // the common complete depth of every tree of the packet, else -1
                     int32_t complete = -2; // -2: no tree yet
                     bool idle = false;
@@ -838,8 +836,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                     }
                 }
             }
-            for (int32_t m : most)
-                p.pk_total_rounds += m;
         }
     }
 
@@ -910,7 +906,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             p.cp_packets.assign(total, 0u);
             p.cp_leaf.assign(total, 0u);
             p.cp_leaf_id.assign(total, -1);
-            std::vector<int32_t> most(static_cast<size_t>(per), 0);
             for (int32_t v = 0; v < W; v++) {
                 for (size_t q = 0; q < runs[size_t(v)].size(); q++) {
                     const int32_t r0 = runs[size_t(v)][q].first, ng = runs[size_t(v)][q].second;
@@ -920,7 +915,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                     int32_t *ids = p.cp_leaf_id.data() + at;
                     uint32_t *hdr = img + kCompactWindowBytes / 4;
                     p.cp_max_groups = std::max(p.cp_max_groups, ng);
-                    most[q] = std::max(most[q], ng);
                     // the zero pair at the end of each window: a left-side leaf of payload 0
                     const uint32_t zero = (kCompactNeverRight << kCompactThrShift) | uint32_t(cap);
                     for (int32_t i = 0; i < K; i++) {
@@ -993,8 +987,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                     }
                 }
             }
-            for (int32_t m : most)
-                p.cp_total_rounds += m;
         }
     }
 
@@ -1058,7 +1050,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             p.term.n_pieces = n_pieces;
             p.term_packets.assign(size_t(W) * size_t(per) * size_t(kTermPacketWords), 0u);
             p.term_slots.assign(size_t(W) * size_t(per) * size_t(kTermSlotPacketWords), 0u);
-            std::vector<int32_t> most(static_cast<size_t>(per), 0);
             const uint32_t zero = (kCompactNeverRight << kCompactThrShift) | uint32_t(cap);
             const uint32_t none = kCompactNeverRight << kCompactThrShift;
             for (int32_t v = 0; v < W; v++) {
@@ -1071,10 +1062,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                     const bool idle = size_t(q) >= runs[size_t(v)].size();
                     const int32_t r0 = idle ? 0 : runs[size_t(v)][size_t(q)].first;
                     const int32_t ng = idle ? 1 : runs[size_t(v)][size_t(q)].second;
-                    if (!idle) {
-                        p.term.max_groups = std::max(p.term.max_groups, ng);
-                        most[size_t(q)] = std::max(most[size_t(q)], ng);
-                    }
+                    p.term.max_groups = std::max(p.term.max_groups, ng);
                     hdr[0] = uint32_t(ng);
                     uint32_t off[K] = {};
                     for (int32_t i = 0; i < K; i++) {
@@ -1123,8 +1111,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
                     }
                 }
             }
-            for (int32_t m : most)
-                p.term.total_rounds += m;
         }
     }
 

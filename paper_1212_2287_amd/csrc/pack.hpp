@@ -129,11 +129,12 @@ constexpr int kCompactMaxColumns = 1023;  // column index field
 constexpr int kCompactMaxTreeNodes = 511; // root + 255 pairs: 2,040 bytes, one 2 KiB window
 constexpr int kCompactCodeShift = 5;
 // Terminal packets (scores only): coded models of one value per leaf, at most 2,046 distinct thresholds
-// per feature and at most 767 features, in 64-document blocks with one workgroup per CU. The records are the compact ones, but the walk ends above the lowest levels: a maximal
-// subtree of depth at most 2 is one terminal node (column 0, absorbing, like a compact leaf), whose
-// slot in device memory holds its up to three splits and four leaf values. A tree of 256 leaves
-// walked this way has about 240 records instead of 511, so a wave holds K = 4 trees in 1 KiB windows
-// where the compact packets hold two, and a walk is about two steps shorter.
+// per feature and at most 767 features, in 64-document blocks with one workgroup per CU. The records are
+// the compact ones, but the walk ends above the lowest levels: a maximal subtree of depth at most 2 is
+// one terminal node (column 0, absorbing, like a compact leaf), whose slot in device memory holds its up
+// to three splits and four leaf values. A tree of 256 leaves walked this way has about 240 records
+// instead of 511, so a wave holds K = 4 trees in 1 KiB windows where the compact packets hold two, and a
+// walk is about two steps shorter.
 //   A tree whose records outgrow a window is cut into pieces: a subtree becomes a leaf of value 0 and,
 // below a copy of the path to it whose other branches end in leaves of value 0, a piece of its own
 // (the pieces' sums add up to the tree's).
@@ -146,7 +147,6 @@ constexpr int kCompactCodeShift = 5;
 struct TermPlan {
     int32_t per_wave;     // packets per wave (0: the model has none)
     int32_t max_groups;   // groups in the fullest packet
-    int64_t total_rounds; // the planner's rounds
     int32_t n_pieces;
 };
 constexpr int kTermTrees = 4;         // K: trees per lane, one window each
@@ -245,6 +245,7 @@ struct Packed {
     int32_t n_small = 0;   // trees [0, n_small) are tiled; [n_small, n_trees) are big trees
     int32_t n_cols = 0;    // 1 + largest feature id read (0 if none)
     int32_t max_depth = 0; // over all trees
+    double mean_steps = 0.0; // expected steps of a tree's lockstep walk, on average
     LdsPlan plan{};
     std::vector<NodeRec> nodes;          // all trees, packed order
     std::vector<uint32_t> tree_node_off; // [n_trees + 1] packed node offset of each tree
@@ -258,10 +259,9 @@ struct Packed {
     int64_t level_image_off[kTileLevels] = {}; // first record of each tiling's images
     int32_t level_slot_recs[kTileLevels] = {}; // image stride of each tiling, in records
     std::vector<uint32_t> tile_recs;           // [tiles] records to copy for each tile
-    // walker rounds (groups of walkers x interleave trees) of the fullest tile of each tiling,
-    // and of all tiles of tiling 0: the launch planner's unit of time
+    // walker rounds (groups of walkers x interleave trees) of the fullest tile of each tiling: the
+    // launch planner's unit of time
     int32_t level_max_rounds[kTileLevels] = {};
-    int64_t total_rounds = 0;
     // feature trace of a two-workgroup plan: LDS byte address of the bitmasks in the tile slot
     // past the largest tiling-0 image (past the walkers' sub-slots with packets), or -1 when
     // they do not fit before the zero record
@@ -273,16 +273,13 @@ struct Packed {
     int32_t pk_zero_rec = 0; // LDS byte address of the zero record the packets' padding links to
     int32_t pk_per_walker = 0;
     int32_t pk_max_groups = 0;   // groups in the fullest packet
-    int64_t pk_total_rounds = 0; // sum over packet indices of the most groups any walker has there
     std::vector<NodeRec> packets;
     // Compact packets (see kCompactWindowBytes), used in place of the packets above when
-    // cp_k > 0: trees per lane, packets per wave, groups in the fullest packet, the planner's
-    // rounds, wave v's packet q at cp_packets[(v * cp_per_walker + q) * kCompactPacketBytes / 4],
+    // cp_k > 0: trees per lane, packets per wave, groups in the fullest packet, wave v's packet q at cp_packets[(v * cp_per_walker + q) * kCompactPacketBytes / 4],
     // and the leaf payloads and input node ids at the same positions.
     int32_t cp_k = 0;
     int32_t cp_per_walker = 0;
     int32_t cp_max_groups = 0;
-    int64_t cp_total_rounds = 0;
     std::vector<uint32_t> cp_packets;
     std::vector<uint32_t> cp_leaf;
     std::vector<int32_t> cp_leaf_id;

@@ -271,7 +271,7 @@ struct tree_ens {
     treeens::LdsPlan plan{};
     int32_t level_begin[treeens::kTileLevels + 1] = {};
     int32_t level_max_rounds[treeens::kTileLevels] = {}; // walker rounds of the fullest tile
-    int64_t total_rounds = 0;                            // walker rounds of all tiles, tiling 0
+    double mean_steps = 0.0;                             // expected steps of a group's walk
     int32_t usage_slot_off = -1; // feature-trace bitmasks in the tile slot (two-workgroup plans)
     int64_t level_image_off[treeens::kTileLevels] = {};
     int32_t level_slot_recs[treeens::kTileLevels] = {};
@@ -284,7 +284,6 @@ struct tree_ens {
     int32_t pk_zero_rec = 0;
     int32_t pk_per_walker = 0;
     int32_t pk_max_groups = 0;
-    int64_t pk_total_rounds = 0;
     uint2 *d_packets = nullptr;
     // compact packets (coded 64-document plans; in place of the packets above for scores, leaf
     // ids and vector-valued leaves): trees per lane (0: none), packets per wave, the planner's
@@ -292,7 +291,6 @@ struct tree_ens {
     int32_t cp_k = 0;
     int32_t cp_per_walker = 0;
     int32_t cp_max_groups = 0;
-    int64_t cp_total_rounds = 0;
     uint32_t *d_cpackets = nullptr;
     uint32_t *d_cleaf = nullptr;
     int32_t *d_cleaf_id = nullptr;
@@ -473,24 +471,9 @@ hipError_t upload(T **dst, const std::vector<T> &src) {
     return e;
 }
 
-// Launch shape for a batch of n_blocks document blocks: a tiling level, a number of head
-// blocks walked whole by one workgroup each, and the split count of the remaining (tail)
-// blocks, each split over that many workgroups that walk a contiguous share of the tiles. Time
-// is counted in walker rounds (every walker walking one group of K trees: a tile takes as long
-// as its fullest round, so tiles smaller than one round save nothing). With W resident
-// workgroups, the estimated makespan in units of one block walking all trees is
-//     head / W * (1 + c_wg)
-//     + ceil(tail blocks * splits / W) * (share + c_wg)
-//     + (splits > 1 ? c_reduce : 0) + tiny * workgroups,
-// where share = ceil(tiles / splits) * (rounds of the fullest tile + c_tile) / (rounds of all
-// tiles + tiles * c_tile) at tiling 0, c_tile is the cost of switching tiles (two barriers, the
-// copy into LDS, the part of the next tile's load the walk does not hide: about half a round on
-// 20,000 depth-3 trees, measured), c_wg is the per-workgroup cost (staging, prologue, epilogue)
-// and the last term prefers fewer
-// workgroups (fewer partial sums) among equal estimates. Candidates: everything split
-// uniformly (no head; small batches spread over the GPU), and whole rounds of workgroups as
-// head with the remainder split to fill the last round (a batch of 1,563 blocks on 512 resident
-// workgroups would otherwise run a fourth round at 5% occupancy).
+// Launch shape for a batch of n_blocks document blocks: a tiling level, a number of head blocks walked
+// whole by one workgroup each, and the split count of the remaining (tail) blocks, each split over that
+// many workgroups that walk a contiguous share of the tiles (or packets) each.
 struct LaunchShape {
     int level = 0;
     int64_t head = 0;
@@ -498,31 +481,42 @@ struct LaunchShape {
 };
 
 // What the planner knows of a model's tiles or packets: per tiling level their number and the rounds of
-// the fullest one; the rounds of all of level 0; the cost of switching to the next, in rounds.
+// the fullest one (a round: every walker walks one group of trees); the cost of switching to the next,
+// in rounds; where workgroups run one after another (kNumCus places, or twice as many), the time of a
+// round there, and what each further workgroup adds.
 struct PlanInput {
-    int64_t slots; // resident workgroups
     int n_levels;
     int tiles[treeens::kTileLevels];
     int rounds[treeens::kTileLevels];
-    int64_t total_rounds;
     double switch_rounds;
+    int64_t places;
+    double round_us;
+    double next_us;
 };
 
+// The estimate, in microseconds, is that of the fullest place: its workgroups' rounds, the first
+// workgroup's staging, prologue and reduction (kFirst), what each further one adds, and the second
+// kernel. 1,000 trees of 32 leaves (16 rounds of 1.15 us), times of a call against the estimate plus 6 us
+// of launch: 16,000 documents whole 31.8 (28.9), in halves 37.3 (34.4); 20,000 whole 49.1 (49.1);
+// 40,000 whole 70.1 (69.2); 100,000 whole 144.5 (149.8), with 27 blocks split 132.8 (134).
+// Candidates: all blocks split alike (small batches spread over the GPU), and whole rounds of one
+// block per place as head, the rest split to fill the places evenly (313 blocks on 256 CUs whole would
+// take as long as 512).
 LaunchShape choose_launch(const PlanInput &in, int64_t n_blocks) {
-    constexpr double kItemCost = 0.2;    // staging, prologue and restaging of one workgroup (measured)
-    constexpr double kReduceCost = 0.05; // the second kernel
-    constexpr double kPerWorkgroup = 1e-6;
-    const int64_t slots = in.slots;
-    const double total = double(std::max<int64_t>(in.total_rounds, 1)) + in.switch_rounds * double(in.tiles[0]);
+    constexpr double kFirst = 4.5, kReduce = 3.75;
+    constexpr double kAllocate = 8.0; // partial sums beyond the handle's scratch
+    constexpr double kPerWorkgroup = 1e-5;
+    auto rounds_of = [&](int level, int tiles) { return double(tiles) * (in.rounds[level] + in.switch_rounds); };
     double best = 1e300;
     LaunchShape pick;
     auto consider = [&](int level, int64_t head, int sp) {
         const int nt = in.tiles[level];
         const int64_t tail = n_blocks - head;
-        const double share = double((nt + sp - 1) / sp) * (in.rounds[level] + in.switch_rounds) / total;
-        const double cost = double(head / slots) * (1.0 + kItemCost) +
-                            double((tail * sp + slots - 1) / slots) * (share + kItemCost) +
-                            (sp > 1 ? kReduceCost : 0.0) + kPerWorkgroup * double(head + tail * sp);
+        const int64_t heads = (head + in.places - 1) / in.places, tails = (tail * sp + in.places - 1) / in.places;
+        const double rounds = double(heads) * rounds_of(level, nt) + double(tails) * rounds_of(level, (nt + sp - 1) / sp);
+        const double cost = kFirst + double(heads + tails - 1) * in.next_us + rounds * in.round_us +
+                            (sp > 1 ? kReduce + (tail * 64 * sp > int64_t(kScratchDoubles) ? kAllocate : 0.0) : 0.0) +
+                            kPerWorkgroup * double(head + tail * sp);
         if (cost < best - 1e-9) {
             best = cost;
             pick = LaunchShape{level, head, sp};
@@ -531,29 +525,39 @@ LaunchShape choose_launch(const PlanInput &in, int64_t n_blocks) {
     for (int k = 0; k < in.n_levels; ++k)
         for (int sp = 1; sp <= std::min(in.tiles[k], 1024); ++sp)
             consider(k, 0, sp);
-    const int64_t rem = n_blocks % slots;
-    if (n_blocks > slots && rem > 0)
-        for (int sp = 2; sp <= std::min<int64_t>(in.tiles[0], slots / rem); ++sp)
-            consider(0, n_blocks - rem, sp);
+    for (int64_t head = n_blocks / in.places * in.places; head > 0 && head + 2 * in.places > n_blocks; head -= in.places)
+        for (int sp = 2; head < n_blocks && sp <= std::min(in.tiles[0], 64); ++sp)
+            consider(0, head, sp);
     return pick;
 }
 
-constexpr double kTileRounds = 0.5;   // switching tiles, in walker rounds
+constexpr double kTileRounds = 0.5;   // switching tiles (barriers, the copy into LDS), in walker rounds
 constexpr double kPacketRounds = 0.1; // switching packets (no barrier), in walker rounds
 
+// Places and times of a plan, from the model's expected steps of a group. Two workgroups on a CU with
+// four trees per lane keep both its pipes busy, so they take twice as long as one would: the CU is one
+// place, 350 cycles a step, and the second one's staging is mostly hidden. With fewer trees per lane they
+// wait for latency and run side by side. One workgroup per CU: about 950 cycles a step (measured), its
+// staging in the open.
+void plan_times(const tree_ens *h, PlanInput &in) {
+    const bool pairs = h->plan.lds_bytes <= treeens::kLdsPerCu / 2, full = h->plan.interleave == 4;
+    in.places = pairs && !full ? 2 * kNumCus : kNumCus;
+    in.round_us = h->mean_steps * (pairs ? 0.147 : 0.4);
+    in.next_us = pairs && full ? 1.75 : 4.5;
+}
+
 LaunchShape choose_launch(const tree_ens *h, int64_t n_blocks) {
-    const int wg_per_cu = h->plan.lds_bytes <= treeens::kLdsPerCu / 2 ? 2 : 1;
-    PlanInput in{int64_t(kNumCus) * wg_per_cu, 1, {}, {}, 0, kPacketRounds};
+    PlanInput in{1, {}, {}, kPacketRounds, kNumCus, 0.0, 0.0};
+    plan_times(h, in);
     // walker packets (8-byte or compact records): one level, each walker's packets in place of
     // the tiles
     if (h->cp_k > 0) {
-        in.tiles[0] = h->cp_per_walker, in.rounds[0] = h->cp_max_groups, in.total_rounds = h->cp_total_rounds;
+        in.tiles[0] = h->cp_per_walker, in.rounds[0] = h->cp_max_groups;
     } else if (h->pk_recs > 0) {
-        in.tiles[0] = h->pk_per_walker, in.rounds[0] = h->pk_max_groups, in.total_rounds = h->pk_total_rounds;
+        in.tiles[0] = h->pk_per_walker, in.rounds[0] = h->pk_max_groups;
     } else {
         in.n_levels = treeens::kTileLevels;
         in.switch_rounds = kTileRounds;
-        in.total_rounds = h->total_rounds;
         for (int k = 0; k < in.n_levels; ++k) {
             in.tiles[k] = h->level_begin[k + 1] - h->level_begin[k];
             in.rounds[k] = h->level_max_rounds[k];
@@ -987,7 +991,8 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
         head = shape.head;
         splits = shape.splits;
     } else {
-        const PlanInput in{kNumCus, 1, {h->term.per_wave}, {h->term.max_groups}, h->term.total_rounds, kPacketRounds};
+        PlanInput in{1, {h->term.per_wave}, {h->term.max_groups}, kPacketRounds, kNumCus, 0.0, 0.0};
+        plan_times(h, in);
         const LaunchShape shape = choose_launch(in, n_blocks);
         head = shape.head;
         splits = shape.splits;
@@ -1216,13 +1221,12 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
     hipError_t e = hipGetDevice(&h->device);
     std::memcpy(h->level_image_off, p.level_image_off, sizeof h->level_image_off);
     std::memcpy(h->level_max_rounds, p.level_max_rounds, sizeof h->level_max_rounds);
-    h->total_rounds = p.total_rounds;
+    h->mean_steps = p.mean_steps;
     h->usage_slot_off = p.usage_slot_off;
     h->pk_recs = p.pk_recs;
     h->pk_zero_rec = p.pk_zero_rec;
     h->pk_per_walker = p.pk_per_walker;
     h->pk_max_groups = p.pk_max_groups;
-    h->pk_total_rounds = p.pk_total_rounds;
     std::memcpy(h->level_slot_recs, p.level_slot_recs, sizeof h->level_slot_recs);
     std::vector<uint2> images(p.images.size());
     if (!p.images.empty())
@@ -1234,7 +1238,6 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
     h->cp_k = p.cp_k;
     h->cp_per_walker = p.cp_per_walker;
     h->cp_max_groups = p.cp_max_groups;
-    h->cp_total_rounds = p.cp_total_rounds;
     if (e == hipSuccess && p.cp_k > 0) {
         // the compact packets replace the 8-byte ones (the feature trace walks the shared tiles)
         h->pk_recs = 0;
