@@ -275,6 +275,7 @@ struct tree_ens {
     int32_t usage_slot_off = -1; // feature-trace bitmasks in the tile slot (two-workgroup plans)
     int64_t level_image_off[treeens::kTileLevels] = {};
     int32_t level_slot_recs[treeens::kTileLevels] = {};
+    void *d_model = nullptr; // the one allocation that every array below lies in
     uint2 *d_images = nullptr;      // tile images of every tiling
     uint32_t *d_tile_recs = nullptr; // records of each tile image
     // walker packets (plans of 64- and 32-document blocks): records per sub-slot (0: the plan
@@ -389,26 +390,7 @@ int static_scratch(int device, unsigned char **out) {
 namespace {
 
 void free_device(tree_ens *h) {
-    (void)hipFree(h->d_images);
-    (void)hipFree(h->d_packets);
-    (void)hipFree(h->d_cpackets);
-    (void)hipFree(h->d_cleaf);
-    (void)hipFree(h->d_cleaf_id);
-    (void)hipFree(h->d_big);
-    (void)hipFree(h->d_tile_recs);
-    (void)hipFree(h->d_tree_node_off);
-    (void)hipFree(h->d_tree_orig);
-    (void)hipFree(h->d_tree_pos);
-    (void)hipFree(h->d_orig_id);
-    (void)hipFree(h->d_leaf_vec);
-    (void)hipFree(h->d_tree_row0);
-    (void)hipFree(h->d_term_packets);
-    (void)hipFree(h->d_term_slots);
-    (void)hipFree(h->d_uniform_nodes);
-    (void)hipFree(h->d_uniform_leaves);
-    (void)hipFree(h->d_code_search);
-    (void)hipFree(h->d_code_chunks);
-    (void)hipFree(h->d_scratch);
+    (void)hipFree(h->d_model);
     if (h->scratch_done)
         (void)hipEventDestroy(h->scratch_done);
     for (void *b : h->capture_bufs)
@@ -460,16 +442,55 @@ int compile_codegen(const std::string &src, std::vector<char> &code, std::string
     return TREE_ENS_OK;
 }
 
-template <typename T>
-hipError_t upload(T **dst, const std::vector<T> &src) {
-    const size_t bytes = std::max<size_t>(src.size() * sizeof(T), sizeof(T));
-    hipError_t e = hipMalloc(reinterpret_cast<void **>(dst), bytes);
-    if (e != hipSuccess)
+// The model's device arrays, in one allocation: the small ones (first, gathered) take one copy together,
+// the others one each.
+class DeviceArrays {
+public:
+    // src must outlive upload(); count elements from the first-th on
+    template <typename D, typename S>
+    void add(D **dst, const std::vector<S> &src, size_t first = 0) {
+        static_assert(sizeof(D) == sizeof(S), "same records");
+        reserve(reinterpret_cast<void **>(dst), src.data() + first, (src.size() - first) * sizeof(S));
+    }
+    void reserve(void **dst, const void *src, size_t bytes) { items_.push_back(Item{dst, src, bytes, 0}); }
+
+    hipError_t upload(void **base) {
+        std::stable_partition(items_.begin(), items_.end(), [](const Item &i) { return i.src && i.bytes <= kSmall; });
+        size_t total = 0, small = 0;
+        for (Item &i : items_) {
+            i.at = total;
+            total += (std::max<size_t>(i.bytes, 1) + 255) & ~size_t(255);
+            if (i.src && i.bytes <= kSmall)
+                small = total;
+        }
+        hipError_t e = hipMalloc(base, std::max<size_t>(total, 256));
+        if (e != hipSuccess)
+            return e;
+        unsigned char *at = static_cast<unsigned char *>(*base);
+        std::vector<unsigned char> gathered(small);
+        for (const Item &i : items_) {
+            *i.dst = at + i.at;
+            if (!i.src || i.bytes == 0)
+                continue;
+            if (i.bytes <= kSmall)
+                std::memcpy(gathered.data() + i.at, i.src, i.bytes);
+            else if (e == hipSuccess)
+                e = hipMemcpy(at + i.at, i.src, i.bytes, hipMemcpyHostToDevice);
+        }
+        if (e == hipSuccess && small > 0)
+            e = hipMemcpy(at, gathered.data(), small, hipMemcpyHostToDevice);
         return e;
-    if (!src.empty())
-        e = hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice);
-    return e;
-}
+    }
+
+private:
+    static constexpr size_t kSmall = size_t(256) << 10;
+    struct Item {
+        void **dst;
+        const void *src;
+        size_t bytes, at;
+    };
+    std::vector<Item> items_;
+};
 
 // Launch shape for a batch of n_blocks document blocks: a tiling level, a number of head blocks walked
 // whole by one workgroup each, and the split count of the remaining (tail) blocks, each split over that
@@ -1228,80 +1249,65 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
     h->pk_per_walker = p.pk_per_walker;
     h->pk_max_groups = p.pk_max_groups;
     std::memcpy(h->level_slot_recs, p.level_slot_recs, sizeof h->level_slot_recs);
-    std::vector<uint2> images(p.images.size());
-    if (!p.images.empty())
-        std::memcpy(images.data(), p.images.data(), p.images.size() * sizeof(NodeRec));
-    if (e == hipSuccess)
-        e = upload(&h->d_images, images);
-    if (e == hipSuccess)
-        e = upload(&h->d_tile_recs, p.tile_recs);
     h->cp_k = p.cp_k;
     h->cp_per_walker = p.cp_per_walker;
     h->cp_max_groups = p.cp_max_groups;
-    if (e == hipSuccess && p.cp_k > 0) {
-        // the compact packets replace the 8-byte ones (the feature trace walks the shared tiles)
-        h->pk_recs = 0;
-        e = upload(&h->d_cpackets, p.cp_packets);
-        if (e == hipSuccess)
-            e = upload(&h->d_cleaf, p.cp_leaf);
-        if (e == hipSuccess)
-            e = upload(&h->d_cleaf_id, p.cp_leaf_id);
-    } else if (e == hipSuccess && p.pk_recs > 0) {
-        std::vector<uint2> packets(p.packets.size());
-        std::memcpy(packets.data(), p.packets.data(), p.packets.size() * sizeof(NodeRec));
-        e = upload(&h->d_packets, packets);
-    }
     h->n_small = p.n_small;
     h->big_off0 = p.tree_node_off[size_t(p.n_small)];
-    if (e == hipSuccess && p.n_small < p.n_trees) {
-        std::vector<uint2> big(p.nodes.size() - h->big_off0);
-        std::memcpy(big.data(), p.nodes.data() + h->big_off0, big.size() * sizeof(NodeRec));
-        e = upload(&h->d_big, big);
+    h->term = p.term;
+    h->uniform = p.uniform;
+    try {
+        DeviceArrays arrays;
+        std::vector<int32_t> tree_pos(p.tree_orig.size());
+        for (size_t t = 0; t < tree_pos.size(); t++)
+            tree_pos[size_t(p.tree_orig[t])] = int32_t(t);
+        arrays.add(&h->d_images, p.images);
+        arrays.add(&h->d_tile_recs, p.tile_recs);
+        if (p.cp_k > 0) {
+            // the compact packets replace the 8-byte ones (the feature trace walks the shared tiles)
+            h->pk_recs = 0;
+            arrays.add(&h->d_cpackets, p.cp_packets);
+            arrays.add(&h->d_cleaf, p.cp_leaf);
+            arrays.add(&h->d_cleaf_id, p.cp_leaf_id);
+        } else if (p.pk_recs > 0) {
+            arrays.add(&h->d_packets, p.packets);
+        }
+        if (p.n_small < p.n_trees)
+            arrays.add(&h->d_big, p.nodes, h->big_off0);
+        arrays.add(&h->d_tree_node_off, p.tree_node_off);
+        arrays.add(&h->d_tree_orig, p.tree_orig);
+        arrays.add(&h->d_tree_pos, tree_pos);
+        arrays.add(&h->d_orig_id, p.orig_id);
+        arrays.reserve(reinterpret_cast<void **>(&h->d_scratch), nullptr, kScratchDoubles * sizeof(double));
+        if (p.n_outputs > 1) {
+            p.leaf_vec.resize(size_t(p.leaf_rows) * size_t(p.vec_stride));
+            arrays.add(&h->d_leaf_vec, p.leaf_vec);
+            arrays.add(&h->d_tree_row0, p.tree_row0);
+        }
+        if (p.term.per_wave > 0) {
+            arrays.add(&h->d_term_packets, p.term_packets);
+            arrays.add(&h->d_term_slots, p.term_slots);
+        }
+        if (p.uniform.depth > 0) {
+            arrays.add(&h->d_uniform_nodes, p.uniform_nodes);
+            arrays.add(&h->d_uniform_leaves, p.uniform_leaves);
+        }
+        if (p.plan.coded || p.uniform.depth > 0) {
+            arrays.add(&h->d_code_search, p.code_search);
+            arrays.add(&h->d_code_chunks, p.code_chunks);
+            h->n_code_chunks = int32_t(p.code_chunks.size());
+        }
+        if (e == hipSuccess)
+            e = arrays.upload(&h->d_model);
+    } catch (const std::bad_alloc &) {
+        e = hipErrorOutOfMemory;
     }
-    if (e == hipSuccess)
-        e = upload(&h->d_tree_node_off, p.tree_node_off);
-    if (e == hipSuccess)
-        e = upload(&h->d_tree_orig, p.tree_orig);
-    if (e == hipSuccess) {
-        std::vector<int32_t> pos(p.tree_orig.size());
-        for (size_t t = 0; t < pos.size(); t++)
-            pos[size_t(p.tree_orig[t])] = int32_t(t);
-        e = upload(&h->d_tree_pos, pos);
-    }
-    if (e == hipSuccess)
-        e = upload(&h->d_orig_id, p.orig_id);
-    if (e == hipSuccess)
-        e = hipMalloc(reinterpret_cast<void **>(&h->d_scratch), kScratchDoubles * sizeof(double));
     if (e == hipSuccess)
         e = hipEventCreateWithFlags(&h->scratch_done, hipEventDisableTiming);
-    if (e == hipSuccess && p.n_outputs > 1) {
-        p.leaf_vec.resize(size_t(p.leaf_rows) * size_t(p.vec_stride));
-        e = upload(&h->d_leaf_vec, p.leaf_vec);
-        if (e == hipSuccess)
-            e = upload(&h->d_tree_row0, p.tree_row0);
-    }
     if (e == hipSuccess && !cg_code.empty()) {
         e = hipModuleLoadData(&h->cg_module, cg_code.data());
         if (e == hipSuccess)
             e = hipModuleGetFunction(&h->cg_fn, h->cg_module, "tree_ens_cg");
-    }
-    h->term = p.term;
-    if (e == hipSuccess && p.term.per_wave > 0) {
-        e = upload(&h->d_term_packets, p.term_packets);
-        if (e == hipSuccess)
-            e = upload(&h->d_term_slots, p.term_slots);
-    }
-    h->uniform = p.uniform;
-    if (e == hipSuccess && p.uniform.depth > 0) {
-        e = upload(&h->d_uniform_nodes, p.uniform_nodes);
-        if (e == hipSuccess)
-            e = upload(&h->d_uniform_leaves, p.uniform_leaves);
-    }
-    if (e == hipSuccess && (p.plan.coded || p.uniform.depth > 0)) {
-        e = upload(&h->d_code_search, p.code_search);
-        if (e == hipSuccess)
-            e = upload(&h->d_code_chunks, p.code_chunks);
-        h->n_code_chunks = int32_t(p.code_chunks.size());
     }
     if (e != hipSuccess) {
         free_device(h);
