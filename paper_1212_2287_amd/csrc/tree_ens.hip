@@ -979,8 +979,8 @@ bool uniform_pays(const tree_ens *h, int64_t n_docs) {
 }
 
 // Scores by terminal packets, in calls of the same kind. The packer makes them for coded
-// models only: those code their documents anyway, where models of float documents would pay for it (1,000 trees of 64 leaves, 700 features,
-// 50,000 documents: 215 us on floats, 86 + 206 us on codes). Small batches of few trees keep the
+// models only: those code their documents anyway, where models of float documents would pay for it
+// (1,000 trees of 64 leaves, 700 features, 50,000 documents: 215 us on floats, 86 + 206 us on codes). Small batches of few trees keep the
 // compact packets, whose walk ends without the terminals' two loads (300 trees of 200 leaves, 1,000
 // documents: 60.7 against 62.1 us; 10,000 documents: 71.9 against 69.6; 5,000 trees of 256 leaves, 100
 // documents: 40.2 against 37.9). Trees beyond the compact packets (over 256 leaves) always take them
@@ -1145,7 +1145,8 @@ int launch_leaves(const tree_ens *h, hipStream_t stream, const float *X, int64_t
 // Smaller batches do not pay for the second launch and the scratch (8 outputs, 1,000 trees: 2,000
 // documents 33 us by two walks against 40, 5,000 documents 51 against 47; 100 trees: 1,024 documents
 // 24 against 25, 10,000 documents 32 against 25), nor do many trees of few documents (4,000 trees of 8
-// leaves, 5,000 documents: 83 against 110, 20,000 documents of 2,000 trees: 161 against 139). Up to four outputs one walk does it all.
+// leaves, 5,000 documents: 83 against 110, 20,000 documents of 2,000 trees: 161 against 139).
+// Up to four outputs one walk does it all.
 // Nor do models whose chunks hold fewer than kRowDocs documents (64 of them fill a workgroup):
 // 10,000 trees of 8 leaves, 6 outputs, 50,000 documents in chunks of 6,500: 1,474 against 2,194 us.
 constexpr int64_t kRowDocs = 32768;
