@@ -52,6 +52,7 @@ LDS_CLK_PER_INSTR = 2.2
 LDS_ISSUE_NODE_GBS = N_CU * CLOCK_HZ * 64 * 8 / (2 * LDS_CLK_PER_INSTR) / 1e9  # 71,494 GB/s
 CSRC = os.path.join(ROOT, "paper_1212_2287_amd", "csrc")
 KERNEL_SRC = [os.path.join(CSRC, n) for n in ("tree_ens.hip", "score.hip", "score.hpp", "uniform.hip", "term.hip", "pack.cpp", "pack.hpp")]
+SCORING_KERNELS = ("score_kernel", "uniform_kernel", "term_kernel")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 
@@ -452,7 +453,7 @@ def write_traffic(fetch_csv: str, write_csv: str, workload: str = HEADLINE,
                 v = float(r["Counter_Value"])
                 if "copyBuffer" in r["Kernel_Name"]:
                     copies.append(v)
-                elif "score_kernel" in r["Kernel_Name"]:
+                elif any(k in r["Kernel_Name"] for k in SCORING_KERNELS):
                     scores.append(v)
         if not copies or not scores:
             raise SystemExit(f"{path}: no copy or scoring dispatch with {counter}")
