@@ -9,8 +9,8 @@
 // with one bit-select (v_bfi). The signs of the three levels form the leaf's place in the tree's
 // table of 8 doubles in LDS, whose 16 words lie in different banks.
 //
-// Bound by VALU issue: 10 instructions per (64 documents, tree of depth 3), 85% of the issue slots
-// busy, LDS 48%; the walk takes 13.7 and 6.9 LDS instructions. 20,000 trees, 136 features,
+// Bound by VALU issue: 10 instructions per (64 documents, tree of depth 3), 83% of the issue slots
+// busy, LDS 47%; the walk takes 13.7 and 6.9 LDS instructions. 20,000 trees, 136 features,
 // 1,000,000 documents: 9.0 ms by the walk, 6.1 ms here and 0.35 ms of coding. Blocks of 512
 // documents (one 16-byte read per node and lane) halve the address arithmetic of 128.
 #include <hip/hip_runtime.h>
