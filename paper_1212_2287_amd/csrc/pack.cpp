@@ -185,7 +185,7 @@ private:
 };
 
 // avg_tree_bytes: mean packed size of a tree, to pick how many trees a lane walks at once.
-// elem_bytes: 4 for float features, 2 for codes.
+// elem_bytes: 4 for float features, 2 for codes. n_cols: at most the limit pack_model checks.
 LdsPlan plan_lds(int32_t n_cols, double avg_tree_bytes, int elem_bytes) {
     LdsPlan p{};
     p.elem_bytes = elem_bytes;
@@ -197,8 +197,6 @@ LdsPlan plan_lds(int32_t n_cols, double avg_tree_bytes, int elem_bytes) {
             break;
         }
     }
-    if (p.docs_per_block == 0)
-        return p;
     p.xs_bytes = int32_t(cols * p.docs_per_block * elem_bytes);
     const int reserve = 64; // the all-zero record, slack
     // 16 waves per workgroup; two workgroups per CU when the document tile is small
@@ -340,6 +338,13 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         depth_of[size_t(t)] = dmax;
     }
 
+    // checked before anything is sized by the feature ids
+    constexpr int32_t kMaxFeature = kXsMaxBytes / (8 * 4) - 2; // 8 float documents and the NaN column
+    if (max_fid > kMaxFeature) {
+        err = "feature id " + std::to_string(max_fid) + " is beyond the LDS document-tile limit (" +
+              std::to_string(kMaxFeature) + ")";
+        return kErrModel;
+    }
     const int32_t n_cols = max_fid + 1;
     auto canon = [&](float th) {
         float v = strict ? strict_to_inclusive(th) : th;
@@ -405,12 +410,9 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         plan = plan_lds(n_cols, avg_tree_bytes, 4);
         // Coding pays when float documents leave too few per block for the model's trees: when
         // a float tile cannot hold one tree for each walker, most walkers would idle.
-        coded = plan.docs_per_block > 0 && plan.docs_per_block < 64 &&
-                avg_tree_bytes * (1024 / plan.docs_per_block) > plan.tile_bytes && codes_fit;
+        coded = plan.docs_per_block < 64 && avg_tree_bytes * (1024 / plan.docs_per_block) > plan.tile_bytes && codes_fit;
         if (coded)
             plan = plan_lds(n_cols, avg_tree_bytes, 2);
-        if (plan.docs_per_block == 0)
-            break;
         // a one-tree tile holds the fixed header words and the root copies (padded to K records)
         max_nodes_per_tree = plan.tile_bytes / int64_t(sizeof(NodeRec)) - (kHeaderFixedWords / 2 + plan.interleave);
         bool changed = false;
@@ -421,11 +423,6 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         }
         if (!changed)
             break;
-    }
-    if (plan.docs_per_block == 0) {
-        err = "feature id " + std::to_string(max_fid) + " is beyond the LDS document-tile limit (" +
-              std::to_string(kXsMaxBytes / (8 * 4) - 2) + ")";
-        return kErrModel;
     }
     // the final plan's slot decides which trees are tiled
     int64_t largest_tree = 0;

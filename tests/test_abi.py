@@ -120,3 +120,18 @@ def test_c_client_reports_errors_without_a_device(tmp_path):
     exe = _build.build_c_client(out=str(tmp_path / "c_client"))
     r = subprocess.run([exe, "errors"], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout + r.stderr
+
+
+@pytest.mark.parametrize("feature", [3_071, 200_000_000, 1_000_000_000, 2**31 - 2, 2**31 - 1])
+def test_feature_beyond_the_limit_is_refused_without_memory_of_its_size(feature):
+    import resource
+    ens, _, _ = load_hand_ensemble()
+    f = ens.feature.copy(); f[0] = feature
+    T.load_library()
+    used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+    soft, hard = resource.getrlimit(resource.RLIMIT_AS)
+    resource.setrlimit(resource.RLIMIT_AS, (used + (256 << 20), hard))
+    try:
+        _expect(T.TREE_ENS_E_MODEL, ens, "document-tile limit (3070)", feature=f)
+    finally:
+        resource.setrlimit(resource.RLIMIT_AS, (soft, hard))
