@@ -100,8 +100,8 @@ int tree_ens_create(tree_ens_t **out, int32_t n_trees, const int64_t *tree_offse
  * n_outputs = n_bags = 1). With n_outputs > 1 the leaf rows live in a device table of
  * one row per leaf (and one of zeros) of ceil(n_outputs / 4) * 4 floats. A predict makes one pass
  * over the trees per four outputs. With more than four outputs, at most 4,096 trees and enough
- * documents (4,096, and 4 per tree) it makes one pass that stores each leaf's row in a
- * stream-ordered buffer (2 bytes per document and tree, at most 256 MiB:
+ * documents (4,096, and 4 per tree) it makes one pass that stores each leaf's row in
+ * borrowed memory (2 bytes per document and tree, at most 256 MiB:
  * larger batches go in chunks) and one reading of it per eight outputs.
  */
 int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree_offsets,
@@ -129,9 +129,12 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
  * splits document blocks over several workgroups (small batches, and the blocks of a last,
  * partial round of workgroups) their fp64 partial sums go to a 1 MiB scratch buffer owned by
  * the handle (calls on different streams are ordered by an event while they share it), or, if
- * larger, to a stream-ordered allocation (hipMallocAsync / hipFreeAsync on `stream`). Models
- * with threshold-coded features also take a stream-ordered buffer of n_docs x min_features
- * 16-bit codes for the duration of the call. A call made while `stream` is being captured into
+ * larger, to borrowed memory. Models with threshold-coded features also borrow n_docs x
+ * min_features 16-bit codes for the duration of the call. Borrowed memory comes from a pool that the
+ * library keeps on each device: at most 512 MiB, allocated when calls first need it (such a call may
+ * take longer), kept between calls, ordered between streams by events and given back when the
+ * device's last handle is destroyed. What the pool cannot lend (larger buffers, many streams at once) is a
+ * stream-ordered allocation (hipMallocAsync / hipFreeAsync on `stream`). A call made while `stream` is being captured into
  * a HIP graph takes neither: it gets a device buffer of its own for its partial sums and codes,
  * allocated when it is captured and kept by the handle until tree_ens_destroy, so the graph's
  * replays never share scratch with other calls of the handle, eager or captured.
@@ -163,7 +166,7 @@ int tree_ens_predict_noalloc(const tree_ens_t *h, void *stream, const float *X, 
  *
  *   leaf_ids  device, int32 [n_docs][n_trees] row-major: the tree-local id, in the caller's
  *             input numbering, of the leaf that document d reaches in tree t.
- * Other arguments and behaviour as tree_ens_predict. Large outputs take a stream-ordered buffer of
+ * Other arguments and behaviour as tree_ens_predict. Large outputs borrow
  * 2 bytes per document and tree (at most 256 MiB: larger batches go in chunks) for the duration of the
  * call, in calls that are not captured into a graph.
  */

@@ -15,6 +15,7 @@
 
 #include "pack.hpp"
 #include "score.hpp"
+#include "scratch.hpp"
 #include "status.hpp"
 #include "term.hpp"
 #include "tree_ens.h"
@@ -587,6 +588,77 @@ LaunchShape choose_launch(const tree_ens *h, int64_t n_blocks) {
     return choose_launch(in, n_blocks);
 }
 
+// The pool's memory (scratch.hpp) on the current device. The capture mode is relaxed where another
+// stream may be capturing: none of this is part of a capture.
+struct HipScratch {
+    using Stream = hipStream_t;
+    using Event = hipEvent_t;
+    struct Relaxed {
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+        ~Relaxed() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    };
+    static bool ok(hipError_t e) {
+        if (e != hipSuccess)
+            (void)hipGetLastError(); // the caller falls back
+        return e == hipSuccess;
+    }
+    void *allocate(size_t bytes) {
+        const Relaxed relaxed;
+        void *p = nullptr;
+        return ok(hipMalloc(&p, bytes)) ? p : nullptr;
+    }
+    void release(void *p, Event done) {
+        const Relaxed relaxed;
+        ok(hipEventSynchronize(done));
+        ok(hipFree(p));
+        ok(hipEventDestroy(done));
+    }
+    bool make_event(Event *ev) { return ok(hipEventCreateWithFlags(ev, hipEventDisableTiming)); }
+    bool record(Event ev, Stream s) { return ok(hipEventRecord(ev, s)); }
+    bool wait(Stream s, Event ev) { return ok(hipStreamWaitEvent(s, ev, 0)); }
+    void finish(Stream s) { ok(hipStreamSynchronize(s)); }
+};
+using Pool = treeens::ScratchPool<HipScratch>;
+
+// The device's pool; never destroyed (handles may outlive static objects), empty without handles.
+Pool *pool_of(int device) {
+    static Pool *const pools = new (std::nothrow) Pool[kMaxDevices];
+    return pools && device >= 0 && device < kMaxDevices ? pools + device : nullptr;
+}
+
+// Device memory of one eager call on `stream`: from the pool, or a stream-ordered allocation where
+// the pool has none to lend. Goes back when the object ends, after the work enqueued until then.
+class CallScratch {
+public:
+    CallScratch(int device, hipStream_t stream) : pool_(pool_of(device)), stream_(stream) {}
+    CallScratch(const CallScratch &) = delete;
+    ~CallScratch() {
+        if (block_)
+            pool_->give(block_);
+        else if (async_)
+            (void)hipFreeAsync(async_, stream_);
+    }
+    // nullptr: no memory, `error` says why
+    unsigned char *take(size_t bytes) {
+        if (pool_ && (block_ = pool_->lend(bytes, stream_)))
+            return static_cast<unsigned char *>(block_->p);
+        error = hipMallocAsync(&async_, bytes, stream_);
+        if (error != hipSuccess) {
+            async_ = nullptr;
+            (void)hipGetLastError();
+        }
+        return static_cast<unsigned char *>(async_);
+    }
+    hipError_t error = hipSuccess;
+
+private:
+    Pool *pool_;
+    hipStream_t stream_;
+    Pool::Block *block_ = nullptr;
+    void *async_ = nullptr;
+};
+
 struct DeviceGuard {
     int prev = -1;
     hipError_t err = hipSuccess;
@@ -756,7 +828,7 @@ hipError_t launch_reduce(hipStream_t stream, const double *partials, int splits,
 // words).
 // Where a call's scratch (split partial sums, threshold codes) comes from.
 enum class ScratchSource {
-    kHandle, // the handle's shared buffer or stream-ordered allocations (eager calls), a buffer
+    kHandle, // the handle's shared buffer or the device's pool (eager calls), a buffer
              // of the call's own kept by the handle (calls captured into a graph)
     kStatic, // the library's static device array only (tree_ens_predict_noalloc)
 };
@@ -832,8 +904,7 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
     double *partials = nullptr;
     uint16_t *codes = nullptr;
     bool shared_scratch = false; // partials in the handle's event-ordered buffer
-    bool async_alloc = false;    // partials and codes from hipMallocAsync, freed on the stream
-    void *async_buf = nullptr;
+    CallScratch lent(h->device, stream); // else partials and codes
     std::unique_lock<std::mutex> scratch_lock;
     if (source == ScratchSource::kStatic) {
         // the static array only: a shape whose partials do not fit takes no splits (every
@@ -888,13 +959,11 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
                 partials = h->d_scratch;
                 shared_scratch = true;
             } else if (need > 0) {
-                e = hipMallocAsync(&async_buf, need, stream);
-                if (e != hipSuccess)
-                    return hip_fail(e, "hipMallocAsync(scratch)");
-                async_alloc = true;
-                codes = h->plan.coded ? static_cast<uint16_t *>(async_buf) : nullptr;
-                partials = pb ? reinterpret_cast<double *>(static_cast<unsigned char *>(async_buf) + codes_bytes)
-                              : nullptr;
+                unsigned char *buf = lent.take(need);
+                if (!buf)
+                    return hip_fail(lent.error, "hipMallocAsync(scratch)");
+                codes = h->plan.coded ? reinterpret_cast<uint16_t *>(buf) : nullptr;
+                partials = pb ? reinterpret_cast<double *>(buf + codes_bytes) : nullptr;
             }
         }
     }
@@ -956,10 +1025,6 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
             e = hipEventRecord(h->scratch_done, stream);
         h->scratch_stream = stream;
         h->scratch_used = true;
-    } else if (async_alloc) {
-        hipError_t e2 = hipFreeAsync(async_buf, stream);
-        if (e == hipSuccess)
-            e = e2;
     }
     if (e != hipSuccess)
         return hip_fail(e, "kernel launch");
@@ -1023,14 +1088,13 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
     const int64_t head_docs = head * docs, tail_docs = std::max<int64_t>(0, n_docs - head_docs);
     const size_t codes_bytes = (size_t(n_docs) * size_t(h->n_cols) * sizeof(uint16_t) + 255) & ~size_t(255);
     const size_t partial_bytes = splits > 1 ? size_t(splits) * size_t(tail_docs) * sizeof(double) : 0;
-    void *buf = nullptr;
-    if (hipMallocAsync(&buf, codes_bytes + partial_bytes, stream) != hipSuccess) {
-        (void)hipGetLastError();
+    CallScratch lent(h->device, stream);
+    unsigned char *buf = lent.take(codes_bytes + partial_bytes);
+    if (!buf)
         return TREE_ENS_OK;
-    }
     *taken = true;
-    uint16_t *codes = static_cast<uint16_t *>(buf);
-    double *partials = partial_bytes ? reinterpret_cast<double *>(static_cast<unsigned char *>(buf) + codes_bytes) : nullptr;
+    uint16_t *codes = reinterpret_cast<uint16_t *>(buf);
+    double *partials = partial_bytes ? reinterpret_cast<double *>(buf + codes_bytes) : nullptr;
     const double scale = 1.0 / double(h->n_bags);
     launch_coding(h, stream, X, n_docs, n_features, uniform ? 0 : treeens::kCompactCodeShift, codes);
     const TimedLaunch timed(h, stream);
@@ -1048,9 +1112,6 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
         e = hipEventRecord(timed.stop, stream);
     if (e == hipSuccess && partials)
         e = launch_reduce(stream, partials, splits, tail_docs, ReduceOut{scores + head_docs, 1, 1, 0, scale});
-    const hipError_t e2 = hipFreeAsync(buf, stream);
-    if (e == hipSuccess)
-        e = e2;
     return e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "kernel launch");
 }
 
@@ -1090,26 +1151,25 @@ int walk_positions(const tree_ens *h, hipStream_t stream, const float *X, int64_
     if (hipStreamIsCapturing(stream, &cap) != hipSuccess)
         cap = hipStreamCaptureStatusNone;
     (void)hipGetLastError();
-    void *pos = nullptr;
-    if (cap != hipStreamCaptureStatusNone || hipMallocAsync(&pos, size_t(per * block_bytes), stream) != hipSuccess) {
-        (void)hipGetLastError();
+    CallScratch lent(h->device, stream);
+    unsigned char *buf = cap == hipStreamCaptureStatusNone ? lent.take(size_t(per * block_bytes)) : nullptr;
+    if (!buf)
         return TREE_ENS_OK;
-    }
     *taken = true;
+    uint16_t *pos = reinterpret_cast<uint16_t *>(buf);
     int rc = TREE_ENS_OK;
     for (int64_t b = 0; b < n_blocks && rc == TREE_ENS_OK; b += per) {
         const int64_t doc0 = b * dl, nd = std::min(std::min(per, n_blocks - b) * dl, n_docs - doc0);
         rc = launch_predict<MODE>(h, stream, X + doc0 * n_features, nd, n_features, nullptr, nullptr, nullptr, 0,
-                                  ScratchSource::kHandle, static_cast<uint16_t *>(pos));
+                                  ScratchSource::kHandle, pos);
         if (rc != TREE_ENS_OK)
             break;
-        then(static_cast<const uint16_t *>(pos), doc0, nd);
+        then(pos, doc0, nd);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess)
             rc = hip_fail(e, "kernel launch");
     }
-    const hipError_t e = hipFreeAsync(pos, stream);
-    return rc != TREE_ENS_OK ? rc : e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "hipFreeAsync");
+    return rc;
 }
 
 // The kernel for a plan's document blocks.
@@ -1316,6 +1376,8 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
         return fail(e == hipErrorOutOfMemory ? TREE_ENS_E_NOMEM : TREE_ENS_E_DEVICE,
                     std::string("device upload failed: ") + hipGetErrorString(e));
     }
+    if (Pool *pool = pool_of(h->device))
+        pool->add_user();
     *out = h;
     return TREE_ENS_OK;
 }
@@ -1557,6 +1619,8 @@ void tree_ens_destroy(tree_ens_t *h) {
     if (!h)
         return;
     DeviceGuard g(h->device);
+    if (Pool *pool = pool_of(h->device))
+        pool->drop_user();
     free_device(h);
     delete h;
 }

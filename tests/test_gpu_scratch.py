@@ -1,0 +1,111 @@
+"""Device memory that calls borrow (positions of leaf ids, rows of leaf vectors, threshold codes, split
+sums): the calls return while earlier work of the stream still runs, keep their memory over a
+synchronisation, give it back with the last handle, and don't share it between streams."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from _gpu import assert_leaves_equal, assert_scores_close, dev
+
+pytestmark = pytest.mark.gpu
+
+# what the call is, trees, features, leaves, depth, documents, outputs
+CALLS = [
+    ("leaf positions", 300, 20, 8, None, 20_000, 1),
+    ("leaf rows", 200, 20, 8, None, 30_000, 6),
+    ("shallow codes", 2_000, 30, 8, 3, 60_000, 1),
+    ("terminal codes", 64, 500, 250, None, 40_000, 1),
+]
+
+
+@pytest.fixture(scope="module")
+def T():
+    import paper_1212_2287_amd as T
+    T.load_library()
+    return T
+
+
+def _model(T, trees, features, leaves, depth, n_out):
+    ens = W.random_ensemble(trees + n_out, trees, features, leaves, leaves, depth)
+    vals = W.make_leaf_vectors(ens, n_out, "dense", seed=1) if n_out > 1 else None
+    return ens, vals, (T.TreeEnsemble.from_ensemble(ens, leaf_values=vals) if n_out > 1 else T.TreeEnsemble.from_ensemble(ens))
+
+
+def _call(m, what):
+    return m.predict_leaves if what == "leaf positions" else m.predict
+
+
+@pytest.mark.parametrize("what,trees,features,leaves,depth,docs,n_out", CALLS, ids=[c[0] for c in CALLS])
+def test_calls_return_without_waiting(T, what, trees, features, leaves, depth, docs, n_out):
+    import torch
+    _, _, m = _model(T, trees, features, leaves, depth, n_out)
+    a = torch.randn(8192, 8192, device="cuda")
+    c = torch.empty_like(a)
+    with m:
+        x = torch.rand((docs, features), device="cuda")
+        out = _call(m, what)(x)  # the first call may allocate
+        torch.mm(a, a, out=c)
+        torch.cuda.synchronize()
+        for _ in range(20):  # over 100 ms
+            torch.mm(a, a, out=c)
+        before = torch.cuda.Event()
+        before.record()
+        _call(m, what)(x, out)
+        _call(m, what)(x, out)
+        assert not before.query(), "the call waited for the stream"
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("what,trees,features,leaves,depth,docs,n_out", CALLS, ids=[c[0] for c in CALLS])
+def test_memory_is_kept_between_calls_and_given_back(T, what, trees, features, leaves, depth, docs, n_out):
+    import torch
+    _, _, m = _model(T, trees, features, leaves, depth, n_out)
+    with m:
+        x = torch.rand((docs, features), device="cuda")
+        out = _call(m, what)(x)
+        torch.cuda.synchronize()
+        idle = torch.cuda.mem_get_info()[0]
+        small = _call(m, what)(x[:docs // 2].contiguous())
+        kept = []
+        for _ in range(4):
+            _call(m, what)(x, out)
+            torch.cuda.synchronize()
+            kept.append(torch.cuda.mem_get_info()[0])
+        del small
+        assert len(set(kept)) == 1
+    del m
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] >= idle + (2 << 20), "the handle's memory and the calls'"
+
+
+@pytest.mark.parametrize("what,trees,features,leaves,depth,docs,n_out", CALLS, ids=[c[0] for c in CALLS])
+def test_streams_do_not_share_memory(T, what, trees, features, leaves, depth, docs, n_out):
+    """Three streams with batches of their own, the handle's calls in turn without a synchronisation."""
+    import torch
+    ens, vals, m = _model(T, trees, features, leaves, depth, n_out)
+    sizes = [docs, docs - 77, docs // 2 + 5]
+    X = [W.random_docs(n, n, features) for n in sizes]
+    with m:
+        x = [dev(v) for v in X]
+        streams = [torch.cuda.Stream() for _ in sizes]
+        outs = [[] for _ in sizes]
+        torch.cuda.synchronize()
+        for _ in range(6):
+            for s, v, o in zip(streams, x, outs):
+                with torch.cuda.stream(s):
+                    o.append(_call(m, what)(v))
+        torch.cuda.synchronize()
+        for v, o in zip(X, outs):
+            assert all(torch.equal(r, o[0]) for r in o)
+            got = o[0].cpu().numpy()
+            if what == "leaf positions":
+                assert_leaves_equal(got, oracle.score(ens, v)[1], what)
+            elif n_out > 1:
+                ref = oracle.score_multi(ens, vals, v)
+                for c in range(n_out):
+                    assert_scores_close(got[:, c], ref[:, c], what)
+            else:
+                assert_scores_close(got, oracle.score(ens, v)[0], what)
