@@ -167,8 +167,9 @@ int tree_ens_predict_noalloc(const tree_ens_t *h, void *stream, const float *X, 
  *   leaf_ids  device, int32 [n_docs][n_trees] row-major: the tree-local id, in the caller's
  *             input numbering, of the leaf that document d reaches in tree t.
  * Other arguments and behaviour as tree_ens_predict. Large outputs borrow
- * 2 bytes per document and tree (at most 256 MiB: larger batches go in chunks) for the duration of the
- * call, in calls that are not captured into a graph.
+ * 2 bytes per document and tree, and the codes of models with threshold-coded features (at most
+ * 256 MiB together: larger batches go in chunks) for the duration of the call, in calls that are not
+ * captured into a graph; if they cannot be had, the call goes on without the positions.
  */
 int tree_ens_predict_leaves(const tree_ens_t *h, void *stream, const float *X, int64_t n_docs,
                             int32_t n_features, int32_t *leaf_ids);

@@ -833,11 +833,17 @@ enum class ScratchSource {
     kStatic, // the library's static device array only (tree_ens_predict_noalloc)
 };
 
+// Memory of a call that launches the walk as its first step.
+struct WalkBuffers {
+    uint16_t *leaf_pos = nullptr; // leaf positions or rows go here (kModeLeaves, kModeRows)
+    uint16_t *codes = nullptr;    // room for the threshold codes (coded models)
+};
+
 template <int MODE>
 int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs,
                    int32_t n_features, float *scores, int32_t *leaf_ids, uint32_t *masks = nullptr,
                    int32_t mask_words = 0, ScratchSource source = ScratchSource::kHandle,
-                   uint16_t *leaf_pos = nullptr) {
+                   const WalkBuffers &given = {}) {
     constexpr bool kScores = MODE == kModeScore || MODE == kModeVector; // split partial sums
     // entries per document in the partial sums, and launches (four outputs each)
     const int comps = MODE == kModeVector ? kVecPerLaunch : 1;
@@ -895,7 +901,7 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
     // scratch of this call: split partial sums (score modes with splits) and threshold codes
     // (coded models), each 256-byte aligned
     auto align256 = [](size_t b) { return (b + 255) & ~size_t(255); };
-    const size_t codes_bytes = h->plan.coded ? align256(size_t(n_docs) * size_t(h->n_cols) * sizeof(uint16_t)) : 0;
+    const size_t codes_bytes = h->plan.coded && !given.codes ? align256(size_t(n_docs) * size_t(h->n_cols) * sizeof(uint16_t)) : 0;
     auto partial_bytes = [&](const LaunchShape &sh) {
         return kScores && sh.splits > 1
                    ? align256(size_t(sh.splits) * size_t(n_docs - sh.head * dl) * size_t(comps) * sizeof(double))
@@ -967,6 +973,8 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
             }
         }
     }
+    if (given.codes)
+        codes = given.codes;
     const int level = shape.level, splits = shape.splits;
     const int64_t tail_docs = n_docs - shape.head * dl;
     // tail blocks after a head are laid out in whole XCD columns (see the kernel)
@@ -1008,7 +1016,7 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
                            h->d_tree_orig, h->n_trees, masks, mask_words, usage_off,
                            reinterpret_cast<const float4 *>(h->d_leaf_vec), h->vec_stride / 4, n_out,
                            chunk, scale, cp ? treeens::kCompactPacketBytes / 8 : pk ? h->pk_recs : 0,
-                           h->d_big, h->n_small, h->big_off0, h->d_cleaf, h->d_cleaf_id, leaf_pos);
+                           h->d_big, h->n_small, h->big_off0, h->d_cleaf, h->d_cleaf_id, given.leaf_pos);
         e = hipGetLastError();
         if (e == hipSuccess && timed.stop)
             e = hipEventRecord(timed.stop, stream);
@@ -1117,7 +1125,7 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
 
 // Leaf ids. Large outputs: the walk stores 16-bit leaf positions in its own (block, packed tree)
 // order and leaf_ids_kernel turns them into the output's rows, in chunks of documents whose
-// positions take at most kPositionBytes (they stay in the last-level cache). 1,000 trees of 32
+// positions (and codes) take at most kPositionBytes (they stay in the last-level cache). 1,000 trees of 32
 // leaves, 30,011 documents: 383 us with ids stored by the walk, 103 us this way (62 us the walk,
 // 37 us the second kernel at 4.8 TB/s).
 // The walk stores ids directly where that is as fast: outputs of at most kLeafDirectBytes (the
@@ -1144,7 +1152,9 @@ int walk_positions(const tree_ens *h, hipStream_t stream, const float *X, int64_
                    bool *taken, Then &&then) {
     const int dl = h->plan.docs_per_block;
     const int64_t n_blocks = (n_docs + dl - 1) / dl;
-    const int64_t block_bytes = int64_t(h->n_trees) * dl * int64_t(sizeof(uint16_t));
+    // positions and, for coded models, threshold codes
+    const int64_t pos_bytes = int64_t(h->n_trees) * dl * int64_t(sizeof(uint16_t));
+    const int64_t block_bytes = pos_bytes + (h->plan.coded ? int64_t(h->n_cols) * dl * int64_t(sizeof(uint16_t)) : 0);
     const int64_t per = std::min(n_blocks, std::max<int64_t>(1, kPositionBytes / block_bytes / (64 / dl) * (64 / dl)));
     *taken = false;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -1156,12 +1166,14 @@ int walk_positions(const tree_ens *h, hipStream_t stream, const float *X, int64_
     if (!buf)
         return TREE_ENS_OK;
     *taken = true;
+    // block_bytes are a multiple of 16 (8 documents at least): so is the codes' place
     uint16_t *pos = reinterpret_cast<uint16_t *>(buf);
+    const WalkBuffers given{pos, h->plan.coded ? reinterpret_cast<uint16_t *>(buf + per * pos_bytes) : nullptr};
     int rc = TREE_ENS_OK;
     for (int64_t b = 0; b < n_blocks && rc == TREE_ENS_OK; b += per) {
         const int64_t doc0 = b * dl, nd = std::min(std::min(per, n_blocks - b) * dl, n_docs - doc0);
         rc = launch_predict<MODE>(h, stream, X + doc0 * n_features, nd, n_features, nullptr, nullptr, nullptr, 0,
-                                  ScratchSource::kHandle, pos);
+                                  ScratchSource::kHandle, given);
         if (rc != TREE_ENS_OK)
             break;
         then(pos, doc0, nd);

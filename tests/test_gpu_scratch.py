@@ -109,3 +109,46 @@ def test_streams_do_not_share_memory(T, what, trees, features, leaves, depth, do
                     assert_scores_close(got[:, c], ref[:, c], what)
             else:
                 assert_scores_close(got, oracle.score(ens, v)[0], what)
+
+
+@pytest.mark.parametrize("n_out", [1, 6])
+def test_room_for_the_codes_alone_is_enough(T, n_out):
+    """A coded model on a device with room for its codes, but not for positions and codes: the walk
+    stores its results directly, as it does for small batches."""
+    import torch
+    ens = W.random_ensemble(11, 200, 500, 250, 250)
+    docs, mib = 100_000, 1 << 20  # 38 MiB of positions, 95 MiB of codes
+    vals = W.make_leaf_vectors(ens, n_out, "dense", seed=1) if n_out > 1 else None
+
+    def handle():
+        return T.TreeEnsemble.from_ensemble(ens, leaf_values=vals) if n_out > 1 else T.TreeEnsemble.from_ensemble(ens)
+    x = torch.rand((docs, 500), device="cuda")
+    small = x[:21_000].contiguous()
+    with handle() as m:
+        ref = (m.predict if n_out > 1 else m.predict_leaves)(x)
+        torch.cuda.synchronize()
+    with handle() as m:
+        call = m.predict if n_out > 1 else m.predict_leaves
+        out = torch.zeros_like(ref)
+        few = call(small)  # kernels loaded, 29 MiB in the pool
+        call(small[:500].contiguous())
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        fill = []
+        for _ in range(4):  # the first figure can lag behind memory given back
+            free = torch.cuda.mem_get_info()[0]
+            if free > 88 * mib:
+                fill.append(torch.empty(free - 80 * mib, dtype=torch.uint8, device="cuda"))
+        print(f"[scratch] {n_out} outputs, {free / mib:.0f} MiB free", flush=True)
+        assert 72 * mib <= free <= 88 * mib
+        call(x, out)
+        torch.cuda.synchronize()
+        del fill, few
+        torch.cuda.empty_cache()
+        if n_out == 1:
+            assert torch.equal(out, ref)
+        else:
+            assert torch.allclose(out, ref, rtol=1e-5, atol=1e-6)
+        call(x, out)  # and with room again
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
