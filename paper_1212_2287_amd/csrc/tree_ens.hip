@@ -1063,6 +1063,27 @@ bool term_pays(const tree_ens *h, int64_t n_docs) {
     return h->cp_k == 0 || h->n_trees >= 1024 || double(n_docs) * h->n_trees >= 2.0e6;
 }
 
+// Launch shape of `n_docs` coded documents: uniform blocks or terminal packets.
+LaunchShape coded_shape(const tree_ens *h, bool uniform, int64_t n_docs) {
+    LaunchShape shape;
+    int64_t n_blocks = (n_docs + 63) / 64;
+    if (uniform) {
+        const treeens::UniformShape us = treeens::uniform_shape(h->uniform, n_docs);
+        n_blocks = (n_docs + h->uniform.docs_per_block - 1) / h->uniform.docs_per_block;
+        shape = LaunchShape{0, us.head, us.splits};
+    } else {
+        PlanInput in{1, {h->term.per_wave}, {h->term.max_groups}, kPacketRounds, kNumCus, 0.0, 0.0};
+        plan_times(h, in);
+        shape = choose_launch(in, n_blocks);
+    }
+    if (shape.splits == 1)
+        shape.head = n_blocks;
+    return shape;
+}
+
+// Bytes of a chunk's codes.
+constexpr int64_t kCodeChunkBytes = int64_t(256) << 20;
+
 int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features,
                          float *scores, bool *taken) {
     *taken = false;
@@ -1076,50 +1097,55 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
     (void)hipGetLastError();
     if (cap != hipStreamCaptureStatusNone || n_docs > int64_t(64) * 0x7ffffff)
         return TREE_ENS_OK;
+    // Shallow models of any batch borrow a bounded amount: their documents go in chunks of whole rounds
+    // (a block for every CU) whose codes take at most kCodeChunkBytes; a chunk but the last has no
+    // tail to split (20,000 trees, 1,000,000 documents: 6.47 ms in two chunks, 6.48 in one). Coded models
+    // take the codes of the whole batch, as every call of theirs does (5,000 trees of 256 leaves, 700
+    // features, 1,000,000 documents: 15.46 ms whole, 15.69 in seven chunks).
     const int docs = uniform ? h->uniform.docs_per_block : 64;
-    const int64_t n_blocks = (n_docs + docs - 1) / docs;
-    int64_t head = n_blocks;
-    int splits = 1;
-    if (uniform) {
-        const treeens::UniformShape shape = treeens::uniform_shape(h->uniform, n_docs);
-        head = shape.head;
-        splits = shape.splits;
-    } else {
-        PlanInput in{1, {h->term.per_wave}, {h->term.max_groups}, kPacketRounds, kNumCus, 0.0, 0.0};
-        plan_times(h, in);
-        const LaunchShape shape = choose_launch(in, n_blocks);
-        head = shape.head;
-        splits = shape.splits;
-        if (splits == 1)
-            head = n_blocks;
-    }
-    const int64_t head_docs = head * docs, tail_docs = std::max<int64_t>(0, n_docs - head_docs);
-    const size_t codes_bytes = (size_t(n_docs) * size_t(h->n_cols) * sizeof(uint16_t) + 255) & ~size_t(255);
-    const size_t partial_bytes = splits > 1 ? size_t(splits) * size_t(tail_docs) * sizeof(double) : 0;
+    const int64_t round = int64_t(docs) * kNumCus, row_bytes = int64_t(h->n_cols) * int64_t(sizeof(uint16_t));
+    const int64_t per =
+        uniform ? std::min(n_docs, std::max<int64_t>(1, kCodeChunkBytes / (round * row_bytes)) * round) : n_docs;
+    auto align256 = [](size_t b) { return (b + 255) & ~size_t(255); };
+    const size_t codes_bytes = align256(size_t(per * row_bytes));
+    const int64_t last_docs = n_docs - (n_docs - 1) / per * per; // 1 .. per
+    const LaunchShape whole = coded_shape(h, uniform, per);
+    const LaunchShape last = last_docs == per ? whole : coded_shape(h, uniform, last_docs);
+    // documents past the head blocks (a split launch has some)
+    auto tail_docs = [&](const LaunchShape &sh, int64_t nd) { return std::max<int64_t>(0, nd - sh.head * docs); };
+    auto partial_bytes = [&](const LaunchShape &sh, int64_t nd) {
+        return sh.splits > 1 ? size_t(sh.splits) * size_t(tail_docs(sh, nd)) * sizeof(double) : size_t(0);
+    };
     CallScratch lent(h->device, stream);
-    unsigned char *buf = lent.take(codes_bytes + partial_bytes);
+    unsigned char *buf = lent.take(codes_bytes + std::max(partial_bytes(whole, per), partial_bytes(last, last_docs)));
     if (!buf)
         return TREE_ENS_OK;
     *taken = true;
     uint16_t *codes = reinterpret_cast<uint16_t *>(buf);
-    double *partials = partial_bytes ? reinterpret_cast<double *>(buf + codes_bytes) : nullptr;
+    double *partials = reinterpret_cast<double *>(buf + codes_bytes);
     const double scale = 1.0 / double(h->n_bags);
-    launch_coding(h, stream, X, n_docs, n_features, uniform ? 0 : treeens::kCompactCodeShift, codes);
-    const TimedLaunch timed(h, stream);
-    hipError_t e = timed.start ? hipEventRecord(timed.start, stream) : hipSuccess;
-    if (e == hipSuccess) {
+    hipError_t e = hipSuccess;
+    for (int64_t doc0 = 0; doc0 < n_docs && e == hipSuccess; doc0 += per) {
+        const int64_t nd = std::min(per, n_docs - doc0);
+        const LaunchShape &sh = nd == per ? whole : last;
+        float *out = scores + doc0;
+        launch_coding(h, stream, X + doc0 * n_features, nd, n_features, uniform ? 0 : treeens::kCompactCodeShift, codes);
+        const TimedLaunch timed(h, stream);
+        if (timed.start && (e = hipEventRecord(timed.start, stream)) != hipSuccess)
+            break;
         if (uniform)
-            treeens::launch_uniform(h->uniform, stream, codes, n_docs, h->n_cols, h->d_uniform_nodes, h->d_uniform_leaves,
-                                    treeens::UniformShape{head, splits}, partials, scores, scale);
+            treeens::launch_uniform(h->uniform, stream, codes, nd, h->n_cols, h->d_uniform_nodes, h->d_uniform_leaves,
+                                    treeens::UniformShape{sh.head, sh.splits}, partials, out, scale);
         else
-            treeens::launch_term(h->term, stream, codes, n_docs, h->n_cols, h->d_term_packets, h->d_term_slots, head, splits,
-                                 partials, scores, scale);
+            treeens::launch_term(h->term, stream, codes, nd, h->n_cols, h->d_term_packets, h->d_term_slots, sh.head,
+                                 sh.splits, partials, out, scale);
         e = hipGetLastError();
+        if (e == hipSuccess && timed.stop)
+            e = hipEventRecord(timed.stop, stream);
+        if (e == hipSuccess && sh.splits > 1)
+            e = launch_reduce(stream, partials, sh.splits, tail_docs(sh, nd),
+                              ReduceOut{out + sh.head * docs, 1, 1, 0, scale});
     }
-    if (e == hipSuccess && timed.stop)
-        e = hipEventRecord(timed.stop, stream);
-    if (e == hipSuccess && partials)
-        e = launch_reduce(stream, partials, splits, tail_docs, ReduceOut{scores + head_docs, 1, 1, 0, scale});
     return e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "kernel launch");
 }
 
