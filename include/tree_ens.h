@@ -137,9 +137,10 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
  * take longer), kept between calls, ordered between streams by events and given back when the
  * device's last handle is destroyed. What the pool cannot lend (larger buffers, many streams at once) is a
  * stream-ordered allocation (hipMallocAsync / hipFreeAsync on `stream`). A call made while `stream` is being captured into
- * a HIP graph takes neither: it gets a device buffer of its own for its partial sums and codes,
- * allocated when it is captured and kept by the handle until tree_ens_destroy, so the graph's
- * replays never share scratch with other calls of the handle, eager or captured.
+ * a HIP graph takes neither: it gets a device buffer of its own for its partial sums, codes and leaf
+ * rows, allocated when it is captured and kept by the handle until tree_ens_destroy, so the graph's
+ * replays never share scratch with other calls of the handle, eager or captured. The same kernels
+ * run, and give the same bits.
  */
 int tree_ens_predict(const tree_ens_t *h, void *stream, const float *X, int64_t n_docs,
                      int32_t n_features, float *scores);
@@ -147,15 +148,20 @@ int tree_ens_predict(const tree_ens_t *h, void *stream, const float *X, int64_t 
 /*
  * tree_ens_predict_noalloc -- tree_ens_predict for callers that cannot allocate device memory
  * during the call (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc). Arguments, results and errors as tree_ens_predict; the same kernels run.
+ * hipMalloc). Arguments, results and errors as tree_ens_predict; the same kernels run, and give
+ * the same bits, while their scratch fits (see below).
  *
  * The call allocates nothing: no hipMalloc, hipMallocAsync or hipFree, no allocating library
  * routine. Its scratch (the fp64 partial sums of document blocks split over several workgroups,
  * and the 16-bit threshold codes of coded models) lives in one static device array of 16 MiB
- * that the library holds on each device it runs on until the process ends. A batch whose split
+ * that the library holds on each device it runs on until the process ends. A batch whose codes or leaf
+ * rows do not fit next to its partial sums is walked as one that is too small for those kernels
+ * (shallow models: codes of n_docs x min_features x 2 bytes; more than four outputs: n_docs x n_trees x 2
+ * bytes; the scores are the same within the documented tolerance). A batch whose split
  * partial sums would not fit is launched without splits (every workgroup walks all trees of its
  * block; the scores are the same within the documented tolerance); a batch whose threshold
- * codes (n_docs x min_features x 2 bytes) exceed 16 MiB is refused with TREE_ENS_E_ARG.
+ * codes (models with threshold-coded features; n_docs x min_features x 2 bytes) exceed 16 MiB is
+ * refused with TREE_ENS_E_ARG.
  * Every call on a device shares that device's array and leaves its contents behind: calls of
  * this function that overlap in time on one device (different streams, or graph replays next to
  * eager calls) race on it and must be ordered by the caller.

@@ -627,11 +627,29 @@ Pool *pool_of(int device) {
     return pools && device >= 0 && device < kMaxDevices ? pools + device : nullptr;
 }
 
-// Device memory of one eager call on `stream`: from the pool, or a stream-ordered allocation where
-// the pool has none to lend. Goes back when the object ends, after the work enqueued until then.
+// Where a call's scratch (split partial sums, threshold codes, leaf positions) comes from.
+enum class ScratchSource {
+    kHandle, // the handle's shared buffer or the device's pool (eager calls), a buffer
+             // of the call's own kept by the handle (calls captured into a graph)
+    kStatic, // the library's static device array only (tree_ens_predict_noalloc)
+};
+
+bool capturing(hipStream_t stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess)
+        cap = hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return cap != hipStreamCaptureStatusNone;
+}
+
+// Device memory of one call on `stream`. Eager calls: from the pool, or a stream-ordered allocation
+// where the pool has none to lend; it goes back when the object ends, after the work enqueued until then.
+// Captured calls: a buffer of the call's own, kept by the handle, so that replays of the graph never
+// share it with eager calls or other graphs. Allocation-free calls: the static array.
 class CallScratch {
 public:
-    CallScratch(int device, hipStream_t stream) : pool_(pool_of(device)), stream_(stream) {}
+    CallScratch(const tree_ens *h, hipStream_t stream, ScratchSource source)
+        : h_(h), pool_(pool_of(h->device)), stream_(stream), source_(source) {}
     CallScratch(const CallScratch &) = delete;
     ~CallScratch() {
         if (block_)
@@ -641,6 +659,13 @@ public:
     }
     // nullptr: no memory, `error` says why
     unsigned char *take(size_t bytes) {
+        if (source_ == ScratchSource::kStatic) {
+            unsigned char *base = nullptr;
+            error = hipErrorOutOfMemory;
+            return bytes <= kStaticScratchBytes && static_scratch(h_->device, &base) == TREE_ENS_OK ? base : nullptr;
+        }
+        if (capturing(stream_))
+            return take_captured(bytes);
         if (pool_ && (block_ = pool_->lend(bytes, stream_)))
             return static_cast<unsigned char *>(block_->p);
         error = hipMallocAsync(&async_, bytes, stream_);
@@ -653,8 +678,27 @@ public:
     hipError_t error = hipSuccess;
 
 private:
+    unsigned char *take_captured(size_t bytes) {
+        std::lock_guard<std::mutex> lock(h_->capture_mu);
+        try {
+            h_->capture_bufs.reserve(h_->capture_bufs.size() + 1);
+        } catch (const std::bad_alloc &) {
+            error = hipErrorOutOfMemory;
+            return nullptr;
+        }
+        void *buf = HipScratch().allocate(bytes);
+        if (!buf) {
+            error = hipErrorOutOfMemory;
+            return nullptr;
+        }
+        h_->capture_bufs.push_back(buf);
+        return static_cast<unsigned char *>(buf);
+    }
+
+    const tree_ens *h_;
     Pool *pool_;
     hipStream_t stream_;
+    ScratchSource source_;
     Pool::Block *block_ = nullptr;
     void *async_ = nullptr;
 };
@@ -826,13 +870,6 @@ hipError_t launch_reduce(hipStream_t stream, const double *partials, int splits,
 // four outputs); kModeLeaves writes leaf_ids [n_docs][n_trees]; kModeUsage writes per-document
 // feature counts into leaf_ids and, if masks is not NULL, the bitmasks (rows of mask_words
 // words).
-// Where a call's scratch (split partial sums, threshold codes) comes from.
-enum class ScratchSource {
-    kHandle, // the handle's shared buffer or the device's pool (eager calls), a buffer
-             // of the call's own kept by the handle (calls captured into a graph)
-    kStatic, // the library's static device array only (tree_ens_predict_noalloc)
-};
-
 // Memory of a call that launches the walk as its first step.
 struct WalkBuffers {
     uint16_t *leaf_pos = nullptr; // leaf positions or rows go here (kModeLeaves, kModeRows)
@@ -907,14 +944,12 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
                    ? align256(size_t(sh.splits) * size_t(n_docs - sh.head * dl) * size_t(comps) * sizeof(double))
                    : size_t(0);
     };
-    double *partials = nullptr;
-    uint16_t *codes = nullptr;
     bool shared_scratch = false; // partials in the handle's event-ordered buffer
-    CallScratch lent(h->device, stream); // else partials and codes
+    CallScratch lent(h, stream, source);
     std::unique_lock<std::mutex> scratch_lock;
     if (source == ScratchSource::kStatic) {
-        // the static array only: a shape whose partials do not fit takes no splits (every
-        // workgroup walks all tiles of its block); codes that do not fit are an error
+        // a shape whose partials do not fit takes no splits (every workgroup walks all tiles of its
+        // block); codes that do not fit are an error
         if (codes_bytes > kStaticScratchBytes)
             return fail(TREE_ENS_E_ARG,
                         "the batch's threshold codes (" + std::to_string(codes_bytes) +
@@ -922,59 +957,26 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
                             std::to_string(kStaticScratchBytes) + " bytes");
         if (codes_bytes + partial_bytes(shape) > kStaticScratchBytes)
             shape = LaunchShape{0, n_blocks, 1};
-        unsigned char *base = nullptr;
-        const int rc = static_scratch(h->device, &base);
-        if (rc != TREE_ENS_OK)
-            return rc;
-        codes = h->plan.coded ? reinterpret_cast<uint16_t *>(base) : nullptr;
-        partials = partial_bytes(shape) ? reinterpret_cast<double *>(base + codes_bytes) : nullptr;
-    } else {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(stream, &cap) != hipSuccess)
-            cap = hipStreamCaptureStatusNone;
-        (void)hipGetLastError();
-        const size_t need = codes_bytes + partial_bytes(shape);
-        if (cap == hipStreamCaptureStatusActive) {
-            // a buffer of this call's own, kept by the handle: replays of the graph never share
-            // it with eager calls or other graphs (allocated outside the stream's order, so the
-            // capture mode is relaxed for the allocation)
-            if (need > 0) {
-                void *buf = nullptr;
-                hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-                (void)hipThreadExchangeStreamCaptureMode(&mode);
-                e = hipMalloc(&buf, need);
-                (void)hipThreadExchangeStreamCaptureMode(&mode);
-                if (e != hipSuccess)
-                    return hip_fail(e, "hipMalloc(scratch of a captured call)");
-                std::lock_guard<std::mutex> lock(h->capture_mu);
-                h->capture_bufs.push_back(buf);
-                codes = h->plan.coded ? static_cast<uint16_t *>(buf) : nullptr;
-                partials = partial_bytes(shape)
-                               ? reinterpret_cast<double *>(static_cast<unsigned char *>(buf) + codes_bytes)
-                               : nullptr;
-            }
-        } else {
-            const size_t pb = partial_bytes(shape);
-            if (pb > 0 && pb <= kScratchDoubles * sizeof(double) && codes_bytes == 0) {
-                scratch_lock = std::unique_lock<std::mutex>(h->scratch_mu);
-                if (h->scratch_used && h->scratch_stream != stream) {
-                    e = hipStreamWaitEvent(stream, h->scratch_done, 0);
-                    if (e != hipSuccess)
-                        return hip_fail(e, "hipStreamWaitEvent");
-                }
-                partials = h->d_scratch;
-                shared_scratch = true;
-            } else if (need > 0) {
-                unsigned char *buf = lent.take(need);
-                if (!buf)
-                    return hip_fail(lent.error, "hipMallocAsync(scratch)");
-                codes = h->plan.coded ? reinterpret_cast<uint16_t *>(buf) : nullptr;
-                partials = pb ? reinterpret_cast<double *>(buf + codes_bytes) : nullptr;
-            }
-        }
     }
-    if (given.codes)
-        codes = given.codes;
+    const size_t pb = partial_bytes(shape);
+    unsigned char *buf = nullptr;
+    if (source == ScratchSource::kHandle && pb > 0 && pb <= kScratchDoubles * sizeof(double) && codes_bytes == 0 &&
+        !capturing(stream)) {
+        scratch_lock = std::unique_lock<std::mutex>(h->scratch_mu);
+        if (h->scratch_used && h->scratch_stream != stream) {
+            e = hipStreamWaitEvent(stream, h->scratch_done, 0);
+            if (e != hipSuccess)
+                return hip_fail(e, "hipStreamWaitEvent");
+        }
+        buf = reinterpret_cast<unsigned char *>(h->d_scratch);
+        shared_scratch = true;
+    } else if (codes_bytes + pb > 0) {
+        buf = lent.take(codes_bytes + pb);
+        if (!buf)
+            return hip_fail(lent.error, "scratch of the call");
+    }
+    uint16_t *codes = given.codes ? given.codes : reinterpret_cast<uint16_t *>(buf);
+    double *partials = pb > 0 ? reinterpret_cast<double *>(buf + codes_bytes) : nullptr;
     const int level = shape.level, splits = shape.splits;
     const int64_t tail_docs = n_docs - shape.head * dl;
     // tail blocks after a head are laid out in whole XCD columns (see the kernel)
@@ -1040,9 +1042,8 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
 }
 
 // Scores of a shallow model by uniform evaluation. `taken` is false (and nothing was launched) for
-// calls that keep the walk: those that do not pay for the coding pass and a workgroup's staging,
-// calls captured into a graph (which then hold no buffer), and when the scratch cannot be
-// allocated.
+// calls that keep the walk: those that do not pay for the coding pass and a workgroup's staging, and
+// when the scratch cannot be had (allocation-free calls: batches beyond the static array).
 // Coding and staging cost a document as much as 32 trees per feature save (4,000 trees, 136
 // features, 100,000 documents: 202 us by the walk, 207 this way; 1,000 trees, 30 features: 64, 64;
 // 20,000 trees, 136 features: 937, 724), and the second launch and the scratch as much as 1e8 walks
@@ -1085,17 +1086,11 @@ LaunchShape coded_shape(const tree_ens *h, bool uniform, int64_t n_docs) {
 constexpr int64_t kCodeChunkBytes = int64_t(256) << 20;
 
 int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features,
-                         float *scores, bool *taken) {
+                         float *scores, ScratchSource source, bool *taken) {
     *taken = false;
     const bool uniform = h->uniform.depth > 0 && uniform_pays(h, n_docs);
     const bool term = !uniform && h->term.per_wave > 0 && term_pays(h, n_docs);
-    if (!uniform && !term)
-        return TREE_ENS_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess)
-        cap = hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    if (cap != hipStreamCaptureStatusNone || n_docs > int64_t(64) * 0x7ffffff)
+    if ((!uniform && !term) || n_docs > int64_t(64) * 0x7ffffff)
         return TREE_ENS_OK;
     // Shallow models of any batch borrow a bounded amount: their documents go in chunks of whole rounds
     // (a block for every CU) whose codes take at most kCodeChunkBytes; a chunk but the last has no
@@ -1116,10 +1111,11 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
     auto partial_bytes = [&](const LaunchShape &sh, int64_t nd) {
         return sh.splits > 1 ? size_t(sh.splits) * size_t(tail_docs(sh, nd)) * sizeof(double) : size_t(0);
     };
-    CallScratch lent(h->device, stream);
+    CallScratch lent(h, stream, source);
     unsigned char *buf = lent.take(codes_bytes + std::max(partial_bytes(whole, per), partial_bytes(last, last_docs)));
     if (!buf)
         return TREE_ENS_OK;
+    (void)hipGetLastError();
     *taken = true;
     uint16_t *codes = reinterpret_cast<uint16_t *>(buf);
     double *partials = reinterpret_cast<double *>(buf + codes_bytes);
@@ -1171,11 +1167,11 @@ bool leaves_direct(int32_t n_trees, int64_t n_docs) {
 }
 
 // The walk's leaf positions in chunks of documents (MODE: kModeLeaves or kModeRows), each chunk
-// followed by `then(pos, first document, documents)`. `taken` is false (and nothing was launched) in
-// calls captured into a graph and when the scratch cannot be allocated.
+// followed by `then(pos, first document, documents)`. `taken` is false (and nothing was launched)
+// when the scratch cannot be had.
 template <int MODE, typename Then>
 int walk_positions(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features,
-                   bool *taken, Then &&then) {
+                   ScratchSource source, bool *taken, Then &&then) {
     const int dl = h->plan.docs_per_block;
     const int64_t n_blocks = (n_docs + dl - 1) / dl;
     // positions and, for coded models, threshold codes
@@ -1183,12 +1179,8 @@ int walk_positions(const tree_ens *h, hipStream_t stream, const float *X, int64_
     const int64_t block_bytes = pos_bytes + (h->plan.coded ? int64_t(h->n_cols) * dl * int64_t(sizeof(uint16_t)) : 0);
     const int64_t per = std::min(n_blocks, std::max<int64_t>(1, kPositionBytes / block_bytes / (64 / dl) * (64 / dl)));
     *taken = false;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess)
-        cap = hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    CallScratch lent(h->device, stream);
-    unsigned char *buf = cap == hipStreamCaptureStatusNone ? lent.take(size_t(per * block_bytes)) : nullptr;
+    CallScratch lent(h, stream, source);
+    unsigned char *buf = lent.take(size_t(per * block_bytes));
     if (!buf)
         return TREE_ENS_OK;
     *taken = true;
@@ -1199,7 +1191,7 @@ int walk_positions(const tree_ens *h, hipStream_t stream, const float *X, int64_
     for (int64_t b = 0; b < n_blocks && rc == TREE_ENS_OK; b += per) {
         const int64_t doc0 = b * dl, nd = std::min(std::min(per, n_blocks - b) * dl, n_docs - doc0);
         rc = launch_predict<MODE>(h, stream, X + doc0 * n_features, nd, n_features, nullptr, nullptr, nullptr, 0,
-                                  ScratchSource::kHandle, given);
+                                  source, given);
         if (rc != TREE_ENS_OK)
             break;
         then(pos, doc0, nd);
@@ -1219,14 +1211,14 @@ Fn pick_block(int dl, Fn f64, Fn f32, Fn f16, Fn f8) {
 int launch_leaves(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs,
                   int32_t n_features, int32_t *leaf_ids) {
     bool taken = false;
-    if (!leaves_direct(h->n_trees, n_docs)) {
+    if (!leaves_direct(h->n_trees, n_docs) && !capturing(stream)) {
         const int dl = h->plan.docs_per_block;
         // compact packets store input node ids, the other records positions in the packed tree
         const int32_t *map = h->cp_k > 0 ? nullptr : h->d_orig_id;
         auto *fn = pick_block(dl, leaf_ids_kernel<64>, leaf_ids_kernel<32>, leaf_ids_kernel<16>, leaf_ids_kernel<8>);
         const int64_t tiles = (h->n_trees + kIdTrees - 1) / kIdTrees;
         const int rc = walk_positions<kModeLeaves>(
-            h, stream, X, n_docs, n_features, &taken, [&](const uint16_t *pos, int64_t doc0, int64_t nd) {
+            h, stream, X, n_docs, n_features, ScratchSource::kHandle, &taken, [&](const uint16_t *pos, int64_t doc0, int64_t nd) {
                 const int64_t nb = (nd + dl - 1) / dl;
                 hipLaunchKernelGGL(fn, dim3(unsigned((nb + kXcds - 1) / kXcds * kXcds * tiles)), dim3(kIdThreads), 0,
                                    stream, pos, nd, h->n_trees, h->d_tree_pos, h->d_tree_node_off, map,
@@ -1253,7 +1245,8 @@ bool rows_pay(const tree_ens *h, int64_t n_docs) {
            h->n_trees * kRowDocs * int64_t(sizeof(uint16_t)) <= kPositionBytes;
 }
 
-int launch_vector(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features, float *scores) {
+int launch_vector(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features, float *scores,
+                  ScratchSource source) {
     bool taken = false;
     if (rows_pay(h, n_docs)) {
         const int dl = h->plan.docs_per_block, n_out = h->n_outputs;
@@ -1261,7 +1254,7 @@ int launch_vector(const tree_ens *h, hipStream_t stream, const float *X, int64_t
         auto *one = pick_block(dl, sum_rows_kernel<64, 1>, sum_rows_kernel<32, 1>, sum_rows_kernel<16, 1>, sum_rows_kernel<8, 1>);
         const double scale = 1.0 / double(h->n_bags);
         const int rc = walk_positions<kModeRows>(
-            h, stream, X, n_docs, n_features, &taken, [&](const uint16_t *pos, int64_t doc0, int64_t nd) {
+            h, stream, X, n_docs, n_features, source, &taken, [&](const uint16_t *pos, int64_t doc0, int64_t nd) {
                 const int chunks = (n_out + kVecPerLaunch - 1) / kVecPerLaunch;
                 for (int c = 0; c < chunks; c += 2)
                     hipLaunchKernelGGL(c + 1 < chunks ? two : one, dim3(unsigned((nd + 63) / 64)), dim3(kRowThreads), 0,
@@ -1272,7 +1265,18 @@ int launch_vector(const tree_ens *h, hipStream_t stream, const float *X, int64_t
         if (taken)
             return rc;
     }
-    return launch_predict<kModeVector>(h, stream, X, n_docs, n_features, scores, nullptr);
+    return launch_predict<kModeVector>(h, stream, X, n_docs, n_features, scores, nullptr, nullptr, 0, source);
+}
+
+int launch_scores(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features, float *scores,
+                  ScratchSource source) {
+    if (h->n_outputs > 1)
+        return launch_vector(h, stream, X, n_docs, n_features, scores, source);
+    bool taken = false;
+    const int rc = launch_coded_predict(h, stream, X, n_docs, n_features, scores, source, &taken);
+    if (taken)
+        return rc;
+    return launch_predict<kModeScore>(h, stream, X, n_docs, n_features, scores, nullptr, nullptr, 0, source);
 }
 
 } // namespace
@@ -1438,8 +1442,6 @@ int tree_ens_predict(const tree_ens_t *h, void *stream, const float *X, int64_t 
         hipError_t e = hipGetLastError();
         return e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "kernel launch");
     }
-    if (h->n_outputs > 1)
-        return launch_vector(h, s, X, n_docs, n_features, scores);
     if (h->cg_fn) {
         // the model's own kernel: one document per thread
         const float *x = X;
@@ -1456,11 +1458,7 @@ int tree_ens_predict(const tree_ens_t *h, void *stream, const float *X, int64_t 
                                              1, 1, 0, s, args, nullptr);
         return e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "specialised kernel launch");
     }
-    bool taken = false;
-    const int urc = launch_coded_predict(h, s, X, n_docs, n_features, scores, &taken);
-    if (taken)
-        return urc;
-    return launch_predict<kModeScore>(h, s, X, n_docs, n_features, scores, nullptr);
+    return launch_scores(h, s, X, n_docs, n_features, scores, ScratchSource::kHandle);
 }
 
 int tree_ens_predict_noalloc(const tree_ens_t *h, void *stream, const float *X, int64_t n_docs,
@@ -1475,11 +1473,7 @@ int tree_ens_predict_noalloc(const tree_ens_t *h, void *stream, const float *X, 
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     if (h->n_trees == 0 || h->cg_fn)
         return tree_ens_predict(h, stream, X, n_docs, n_features, scores); // no scratch used
-    if (h->n_outputs > 1)
-        return launch_predict<kModeVector>(h, s, X, n_docs, n_features, scores, nullptr, nullptr, 0,
-                                           ScratchSource::kStatic);
-    return launch_predict<kModeScore>(h, s, X, n_docs, n_features, scores, nullptr, nullptr, 0,
-                                      ScratchSource::kStatic);
+    return launch_scores(h, s, X, n_docs, n_features, scores, ScratchSource::kStatic);
 }
 
 int tree_ens_predict_leaves(const tree_ens_t *h, void *stream, const float *X, int64_t n_docs,

@@ -1,0 +1,132 @@
+"""Serving calls run the kernels of eager ones: captured predicts replayed between eager calls, and
+allocation-free predicts, give tree_ens_predict's scores bit for bit on both sides of every choice
+of kernels (shallow models, terminal packets, leaf vectors, the walk); allocation-free batches whose
+scratch exceeds the static array are walked and agree with the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from _gpu import assert_leaves_equal, assert_scores_close, dev
+
+pytestmark = pytest.mark.gpu
+
+# trees, features, smallest and largest tree, depth, outputs, documents
+SCORES = [
+    (1_000, 25, 8, 8, 3, 1, 99_999), (1_000, 25, 8, 8, 3, 1, 100_000), (1_000, 25, 8, 8, 3, 1, 300_001),  # uniform from 1e8 walks
+    (1_640, 41, 1, 4, 2, 1, 61_001),
+    (304, 450, 100, 255, None, 1, 6_570), (304, 450, 100, 255, None, 1, 6_600),  # terminal packets from 2e6 walks
+    (304, 450, 100, 255, None, 1, 17_001),
+    (160, 500, 400, 512, None, 1, 65), (160, 500, 400, 512, None, 1, 16_449),      # no compact packets: always
+    (200, 20, 8, 8, None, 6, 4_095), (200, 20, 8, 8, None, 6, 4_096), (200, 20, 8, 8, None, 5, 30_001),  # one walk
+    (104, 500, 150, 250, None, 7, 5_000), (160, 1_200, 10, 10, None, 13, 5_003),
+    (104, 136, 32, 32, None, 3, 20_000), (1_000, 136, 32, 32, None, 1, 20_000),
+]
+
+
+@pytest.fixture(scope="module")
+def T():
+    import paper_1212_2287_amd as T
+    T.load_library()
+    return T
+
+
+def _model(T, trees, features, least, most, depth, n_out, seed, noise=False):
+    """noise: every tree eight times, four of them with negated leaf values, which span 40 binary orders:
+    the scores are what rounding leaves of sums that cancel, and in another order other ones."""
+    ens = W.random_ensemble(seed, trees // 8 if noise else trees, features, least, most, depth)
+    vals = W.make_leaf_vectors(ens, n_out, "dense", seed=seed) if n_out > 1 else None
+    if noise:
+        rng = np.random.default_rng(seed)
+        v = vals if n_out > 1 else ens.value
+        v *= np.exp2(rng.integers(0, 41, v.shape)).astype(np.float32)
+        # each copy's sign, by tree, then by node
+        sign = rng.permuted(np.tile(np.repeat(np.float32([1, -1]), 4), (ens.n_trees, 1)), axis=1).T
+        v = np.concatenate([(v.T * np.repeat(s, np.diff(ens.tree_offsets))).T for s in sign])
+        same = [np.tile(a, 8) for a in (ens.feature, ens.threshold, ens.left, ens.right)]
+        offsets = np.concatenate([[0]] + [ens.tree_offsets[1:] + i * ens.n_nodes for i in range(8)])
+        ens = W.Ensemble(offsets, *same, np.tile(ens.value, 8) if n_out > 1 else v, features)
+        vals = v if n_out > 1 else None
+    if n_out > 1:
+        return ens, vals, T.TreeEnsemble.from_ensemble(ens, leaf_values=vals, n_bags=2)
+    return ens, vals, T.TreeEnsemble.from_ensemble(ens)
+
+
+@pytest.mark.parametrize("trees,features,least,most,depth,n_out,docs", SCORES)
+def test_captured_scores_are_the_eager_ones(T, trees, features, least, most, depth, n_out, docs):
+    import torch
+    _, _, m = _model(T, trees, features, least, most, depth, n_out, docs, noise=True)
+    with m:
+        x = dev(W.random_docs(docs, docs, features))
+        other = dev(W.random_docs(docs + 1, docs, features))
+        eager, eager_other = m.predict(x), m.predict(other)
+        torch.cuda.synchronize()
+        assert (eager != 0).any()  # there is noise
+        xin, out = x.clone(), torch.zeros_like(eager)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            m.predict(xin, out)
+        for i in range(4):
+            src, ref = ((x, eager), (other, eager_other))[i % 2]
+            xin.copy_(src)
+            out.zero_()
+            g.replay()
+            between = m.predict(other)
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref), f"replay {i}"
+            assert torch.equal(between, eager_other), f"eager call {i}"
+
+
+@pytest.mark.parametrize("trees,features,least,most,depth,n_out,docs", SCORES)
+def test_allocation_free_scores(T, trees, features, least, most, depth, n_out, docs):
+    import torch
+    _, _, m = _model(T, trees, features, least, most, depth, n_out, docs, noise=True)
+    with m:
+        x = dev(W.random_docs(docs, docs, features))
+        ref = m.predict(x)
+        got = m.predict_noalloc(x, torch.full_like(ref, float("nan")))
+        torch.cuda.synchronize()
+        assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("trees,features,depth,n_out,docs", [
+    (1_000, 25, 3, 1, 400_000),   # 20 MB of codes
+    (300, 20, None, 6, 30_000),   # 18 MB of leaf rows
+])
+def test_allocation_free_batches_beyond_the_static_array(T, trees, features, depth, n_out, docs):
+    import torch
+    ens, vals, m = _model(T, trees, features, 8, 8, depth, n_out, docs)
+    X = W.random_docs(docs, docs, features)
+    with m:
+        got = m.predict_noalloc(dev(X), torch.full((docs, n_out) if n_out > 1 else (docs,), float("nan"), device="cuda"))
+        got = got.cpu().numpy().reshape(docs, n_out)
+    ref = oracle.score(ens, X)[0][:, None] if n_out == 1 else oracle.score_multi(ens, vals, X, n_bags=2)
+    for c in range(n_out):
+        assert_scores_close(got[:, c], ref[:, c], f"output {c}")
+
+
+@pytest.mark.parametrize("trees,features,leaves,docs", [(300, 20, 8, 20_000), (300, 500, 250, 9_001)])
+def test_captured_leaf_ids(T, trees, features, leaves, docs):
+    """Outputs of the two-kernel size: the captured walk stores the ids directly."""
+    import torch
+    ens = W.random_ensemble(docs, trees, features, 1, leaves)
+    X = W.random_docs(docs, docs, features)
+    ref = oracle.score(ens, X)[1]
+    with T.TreeEnsemble.from_ensemble(ens) as m:
+        x = dev(X)
+        eager = m.predict_leaves(x)
+        out = torch.zeros_like(eager)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            m.predict_leaves(x, out)
+        for _ in range(3):
+            out.fill_(-1)
+            g.replay()
+            again = m.predict_leaves(x)
+            torch.cuda.synchronize()
+            assert_leaves_equal(out.cpu().numpy(), ref, "replay")
+            assert torch.equal(again, eager)
+    assert_leaves_equal(eager.cpu().numpy(), ref, "eager")
