@@ -518,7 +518,8 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
     });
     p.n_small = n_small;
     for (int32_t t = 0; t < n_trees; t++)
-        p.mean_steps += (lock_key[size_t(t)] + 1.0) / double(n_trees);
+        if (!is_big[size_t(t)])
+            p.mean_steps += (lock_key[size_t(t)] + 1.0) / double(n_small);
     p.nodes.reserve(size_t(n_nodes));
     p.orig_id.reserve(size_t(n_nodes));
     p.tree_node_off.resize(size_t(n_trees) + 1, 0);
@@ -652,6 +653,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             const Tile &tl = p.tiles[size_t(i)];
             const int32_t r = (tl.tree_end - tl.tree_begin + round - 1) / round;
             p.level_max_rounds[k] = std::max(p.level_max_rounds[k], r);
+            p.level_mean_rounds[k] += double(r) / double(p.level_begin[k + 1] - p.level_begin[k]);
         }
     }
     p.tile_recs.resize(p.tiles.size());
@@ -774,6 +776,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             p.pk_recs = sub;
             p.pk_zero_rec = pk_zero;
             p.pk_per_walker = per;
+            p.pk_mean_groups = double(n_groups) / double(W * P * per);
             p.packets.assign(size_t(W) * size_t(per) * size_t(sub), NodeRec{0u, 0u});
             const NodeRec zero_leaf{zero_record_value(plan, vec), (uint32_t(pk_zero) / 8u) << shift};
             for (int32_t v = 0; v < W; v++) {
@@ -899,6 +902,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
             const uint32_t col_bytes = uint32_t(plan.docs_per_block * plan.elem_bytes);
             p.cp_k = K;
             p.cp_per_walker = per;
+            p.cp_mean_groups = double(n_groups) / double(W * per);
             const size_t total = size_t(W) * size_t(per) * size_t(kWords);
             p.cp_packets.assign(total, 0u);
             p.cp_leaf.assign(total, 0u);
@@ -1045,6 +1049,7 @@ int pack_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
         if (ok) {
             p.term.per_wave = per;
             p.term.n_pieces = n_pieces;
+            p.term.mean_groups = double(n_groups) / double(W * per);
             p.term_packets.assign(size_t(W) * size_t(per) * size_t(kTermPacketWords), 0u);
             p.term_slots.assign(size_t(W) * size_t(per) * size_t(kTermSlotPacketWords), 0u);
             const uint32_t zero = (kCompactNeverRight << kCompactThrShift) | uint32_t(cap);

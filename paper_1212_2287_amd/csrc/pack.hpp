@@ -147,6 +147,7 @@ constexpr int kCompactCodeShift = 5;
 struct TermPlan {
     int32_t per_wave;     // packets per wave (0: the model has none)
     int32_t max_groups;   // groups in the fullest packet
+    double mean_groups;   // groups of a wave's packets, on average
     int32_t n_pieces;
 };
 constexpr int kTermTrees = 4;         // K: trees per lane, one window each
@@ -245,7 +246,7 @@ struct Packed {
     int32_t n_small = 0;   // trees [0, n_small) are tiled; [n_small, n_trees) are big trees
     int32_t n_cols = 0;    // 1 + largest feature id read (0 if none)
     int32_t max_depth = 0; // over all trees
-    double mean_steps = 0.0; // expected steps of a tree's lockstep walk, on average
+    double mean_steps = 0.0; // expected steps of a tiled tree's lockstep walk, on average
     LdsPlan plan{};
     std::vector<NodeRec> nodes;          // all trees, packed order
     std::vector<uint32_t> tree_node_off; // [n_trees + 1] packed node offset of each tree
@@ -262,6 +263,7 @@ struct Packed {
     // walker rounds (groups of walkers x interleave trees) of the fullest tile of each tiling: the
     // launch planner's unit of time
     int32_t level_max_rounds[kTileLevels] = {};
+    double level_mean_rounds[kTileLevels] = {}; // of its tiles, on average
     // feature trace of a two-workgroup plan: LDS byte address of the bitmasks in the tile slot
     // past the largest tiling-0 image (past the walkers' sub-slots with packets), or -1 when
     // they do not fit before the zero record
@@ -273,6 +275,7 @@ struct Packed {
     int32_t pk_zero_rec = 0; // LDS byte address of the zero record the packets' padding links to
     int32_t pk_per_walker = 0;
     int32_t pk_max_groups = 0;   // groups in the fullest packet
+    double pk_mean_groups = 0.0; // groups of a walker's packets, on average
     std::vector<NodeRec> packets;
     // Compact packets (see kCompactWindowBytes), used in place of the packets above when
     // cp_k > 0: trees per lane, packets per wave, groups in the fullest packet, wave v's packet q at cp_packets[(v * cp_per_walker + q) * kCompactPacketBytes / 4],
@@ -280,6 +283,7 @@ struct Packed {
     int32_t cp_k = 0;
     int32_t cp_per_walker = 0;
     int32_t cp_max_groups = 0;
+    double cp_mean_groups = 0.0;
     std::vector<uint32_t> cp_packets;
     std::vector<uint32_t> cp_leaf;
     std::vector<int32_t> cp_leaf_id;

@@ -6,10 +6,10 @@
 #include <hip/hip_runtime.h>
 
 #include "pack.hpp"
+#include "planner.hpp"
 
 namespace treeens {
 
-constexpr int kNumCus = 256;
 constexpr int kXcds = 8; // accelerator complex dies, each with its own L2
 // s_waitcnt immediate for gfx9: vmcnt(0), expcnt and lgkmcnt left at their maxima (no wait)
 constexpr int kWaitVmcnt0 = 0x0F70;

@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "pack.hpp"
+#include "planner.hpp"
 #include "score.hpp"
 #include "scratch.hpp"
 #include "status.hpp"
@@ -271,8 +272,7 @@ struct tree_ens {
     int64_t n_nodes = 0;
     treeens::LdsPlan plan{};
     int32_t level_begin[treeens::kTileLevels + 1] = {};
-    int32_t level_max_rounds[treeens::kTileLevels] = {}; // walker rounds of the fullest tile
-    double mean_steps = 0.0;                             // expected steps of a group's walk
+    treeens::PlanFacts facts{};  // what the launch planner goes by
     int32_t usage_slot_off = -1; // feature-trace bitmasks in the tile slot (two-workgroup plans)
     int64_t level_image_off[treeens::kTileLevels] = {};
     int32_t level_slot_recs[treeens::kTileLevels] = {};
@@ -280,19 +280,17 @@ struct tree_ens {
     uint2 *d_images = nullptr;      // tile images of every tiling
     uint32_t *d_tile_recs = nullptr; // records of each tile image
     // walker packets (plans of 64- and 32-document blocks): records per sub-slot (0: the plan
-    // walks shared tiles), the packets' zero record, packets per wave, the planner's rounds,
-    // and the images
+    // walks shared tiles), the packets' zero record, packets per wave, and the
+    // images
     int32_t pk_recs = 0;
     int32_t pk_zero_rec = 0;
     int32_t pk_per_walker = 0;
-    int32_t pk_max_groups = 0;
     uint2 *d_packets = nullptr;
     // compact packets (coded 64-document plans; in place of the packets above for scores, leaf
-    // ids and vector-valued leaves): trees per lane (0: none), packets per wave, the planner's
-    // figures, the packets, and the leaf payloads and input node ids at the leaves' positions
+    // ids and vector-valued leaves): trees per lane (0: none), packets per wave, the
+    // packets, and the leaf payloads and input node ids at the leaves' positions
     int32_t cp_k = 0;
     int32_t cp_per_walker = 0;
-    int32_t cp_max_groups = 0;
     uint32_t *d_cpackets = nullptr;
     uint32_t *d_cleaf = nullptr;
     int32_t *d_cleaf_id = nullptr;
@@ -347,12 +345,16 @@ struct tree_ens {
     mutable bool timing = false;
     mutable std::vector<hipEvent_t> t_start, t_stop;
     mutable int32_t t_used = 0;
-    // launch shape of the last batch size seen (callers usually repeat one batch size)
+    // launch shapes of the last batch sizes seen (callers usually repeat a few), by the kind of
+    // work (a treeens::Work, or kUniformWork) and the batch's blocks, replaced in turn
+    struct Shape {
+        int work = -1;
+        int64_t blocks = 0;
+        treeens::LaunchShape shape;
+    };
     mutable std::mutex shape_mu;
-    mutable int64_t shape_blocks = -1;
-    mutable int shape_level = 0;
-    mutable int64_t shape_head = 0;
-    mutable int shape_splits = 1;
+    mutable Shape shapes[8];
+    mutable unsigned next_shape = 0;
 };
 
 namespace {
@@ -493,101 +495,6 @@ private:
     std::vector<Item> items_;
 };
 
-// Launch shape for a batch of n_blocks document blocks: a tiling level, a number of head blocks walked
-// whole by one workgroup each, and the split count of the remaining (tail) blocks, each split over that
-// many workgroups that walk a contiguous share of the tiles (or packets) each.
-struct LaunchShape {
-    int level = 0;
-    int64_t head = 0;
-    int splits = 1;
-};
-
-// What the planner knows of a model's tiles or packets: per tiling level their number and the rounds of
-// the fullest one (a round: every walker walks one group of trees); the cost of switching to the next,
-// in rounds; where workgroups run one after another (kNumCus places, or twice as many), the time of a
-// round there, and what each further workgroup adds.
-struct PlanInput {
-    int n_levels;
-    int tiles[treeens::kTileLevels];
-    int rounds[treeens::kTileLevels];
-    double switch_rounds;
-    int64_t places;
-    double round_us;
-    double next_us;
-};
-
-// The estimate, in microseconds, is that of the fullest place: its workgroups' rounds, the first
-// workgroup's staging, prologue and reduction (kFirst), what each further one adds, and the second
-// kernel. 1,000 trees of 32 leaves (16 rounds of 1.15 us), times of a call against the estimate plus 6 us
-// of launch: 16,000 documents whole 31.8 (28.9), in halves 37.3 (34.4); 20,000 whole 49.1 (49.1);
-// 40,000 whole 70.1 (69.2); 100,000 whole 144.5 (149.8), with 27 blocks split 132.8 (134).
-// Candidates: all blocks split alike (small batches spread over the GPU), and whole rounds of one
-// block per place as head, the rest split to fill the places evenly (313 blocks on 256 CUs whole would
-// take as long as 512).
-LaunchShape choose_launch(const PlanInput &in, int64_t n_blocks) {
-    constexpr double kFirst = 4.5, kReduce = 3.75;
-    constexpr double kAllocate = 8.0; // partial sums beyond the handle's scratch
-    constexpr double kPerWorkgroup = 1e-5;
-    auto rounds_of = [&](int level, int tiles) { return double(tiles) * (in.rounds[level] + in.switch_rounds); };
-    double best = 1e300;
-    LaunchShape pick;
-    auto consider = [&](int level, int64_t head, int sp) {
-        const int nt = in.tiles[level];
-        const int64_t tail = n_blocks - head;
-        const int64_t heads = (head + in.places - 1) / in.places, tails = (tail * sp + in.places - 1) / in.places;
-        const double rounds = double(heads) * rounds_of(level, nt) + double(tails) * rounds_of(level, (nt + sp - 1) / sp);
-        const double cost = kFirst + double(heads + tails - 1) * in.next_us + rounds * in.round_us +
-                            (sp > 1 ? kReduce + (tail * 64 * sp > int64_t(kScratchDoubles) ? kAllocate : 0.0) : 0.0) +
-                            kPerWorkgroup * double(head + tail * sp);
-        if (cost < best - 1e-9) {
-            best = cost;
-            pick = LaunchShape{level, head, sp};
-        }
-    };
-    for (int k = 0; k < in.n_levels; ++k)
-        for (int sp = 1; sp <= std::min(in.tiles[k], 1024); ++sp)
-            consider(k, 0, sp);
-    for (int64_t head = n_blocks / in.places * in.places; head > 0 && head + 2 * in.places > n_blocks; head -= in.places)
-        for (int sp = 2; head < n_blocks && sp <= std::min(in.tiles[0], 64); ++sp)
-            consider(0, head, sp);
-    return pick;
-}
-
-constexpr double kTileRounds = 0.5;   // switching tiles (barriers, the copy into LDS), in walker rounds
-constexpr double kPacketRounds = 0.1; // switching packets (no barrier), in walker rounds
-
-// Places and times of a plan, from the model's expected steps of a group. Two workgroups on a CU with
-// four trees per lane keep both its pipes busy, so they take twice as long as one would: the CU is one
-// place, 350 cycles a step, and the second one's staging is mostly hidden. With fewer trees per lane they
-// wait for latency and run side by side. One workgroup per CU: about 950 cycles a step (measured), its
-// staging in the open.
-void plan_times(const tree_ens *h, PlanInput &in) {
-    const bool pairs = h->plan.lds_bytes <= treeens::kLdsPerCu / 2, full = h->plan.interleave == 4;
-    in.places = pairs && !full ? 2 * kNumCus : kNumCus;
-    in.round_us = h->mean_steps * (pairs ? 0.147 : 0.4);
-    in.next_us = pairs && full ? 1.75 : 4.5;
-}
-
-LaunchShape choose_launch(const tree_ens *h, int64_t n_blocks) {
-    PlanInput in{1, {}, {}, kPacketRounds, kNumCus, 0.0, 0.0};
-    plan_times(h, in);
-    // walker packets (8-byte or compact records): one level, each walker's packets in place of
-    // the tiles
-    if (h->cp_k > 0) {
-        in.tiles[0] = h->cp_per_walker, in.rounds[0] = h->cp_max_groups;
-    } else if (h->pk_recs > 0) {
-        in.tiles[0] = h->pk_per_walker, in.rounds[0] = h->pk_max_groups;
-    } else {
-        in.n_levels = treeens::kTileLevels;
-        in.switch_rounds = kTileRounds;
-        for (int k = 0; k < in.n_levels; ++k) {
-            in.tiles[k] = h->level_begin[k + 1] - h->level_begin[k];
-            in.rounds[k] = h->level_max_rounds[k];
-        }
-    }
-    return choose_launch(in, n_blocks);
-}
-
 // The pool's memory (scratch.hpp) on the current device. The capture mode is relaxed where another
 // stream may be capturing: none of this is part of a capture.
 struct HipScratch {
@@ -625,6 +532,19 @@ using Pool = treeens::ScratchPool<HipScratch>;
 Pool *pool_of(int device) {
     static Pool *const pools = new (std::nothrow) Pool[kMaxDevices];
     return pools && device >= 0 && device < kMaxDevices ? pools + device : nullptr;
+}
+
+// The handle's kept shape for this work and number of blocks, or that of `choose`.
+constexpr int kUniformWork = 100;
+template <typename Choose>
+LaunchShape kept_shape(const tree_ens *h, int work, int64_t n_blocks, Choose &&choose) {
+    std::lock_guard<std::mutex> lock(h->shape_mu);
+    for (const tree_ens::Shape &s : h->shapes)
+        if (s.work == work && s.blocks == n_blocks)
+            return s.shape;
+    const LaunchShape shape = choose();
+    h->shapes[h->next_shape++ % (sizeof h->shapes / sizeof h->shapes[0])] = tree_ens::Shape{work, n_blocks, shape};
+    return shape;
 }
 
 // Where a call's scratch (split partial sums, threshold codes, leaf positions) comes from.
@@ -909,16 +829,8 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
                 return fail(TREE_ENS_E_ARG, "feature bitmasks do not fit the LDS plan");
         }
     } else {
-        std::lock_guard<std::mutex> lock(h->shape_mu);
-        if (h->shape_blocks == n_blocks) {
-            shape = LaunchShape{h->shape_level, h->shape_head, h->shape_splits};
-        } else {
-            shape = choose_launch(h, n_blocks);
-            h->shape_blocks = n_blocks;
-            h->shape_level = shape.level;
-            h->shape_head = shape.head;
-            h->shape_splits = shape.splits;
-        }
+        const Work work = MODE == kModeScore ? Work::kScores : MODE == kModeVector ? Work::kVector : Work::kPositions;
+        shape = kept_shape(h, int(work), n_blocks, [&] { return choose_launch(h->facts, work, n_blocks); });
     }
     {
         // grid of the chosen shape (the no-split shape the allocation-free path may fall back
@@ -1066,20 +978,20 @@ bool term_pays(const tree_ens *h, int64_t n_docs) {
 
 // Launch shape of `n_docs` coded documents: uniform blocks or terminal packets.
 LaunchShape coded_shape(const tree_ens *h, bool uniform, int64_t n_docs) {
-    LaunchShape shape;
-    int64_t n_blocks = (n_docs + 63) / 64;
-    if (uniform) {
-        const treeens::UniformShape us = treeens::uniform_shape(h->uniform, n_docs);
-        n_blocks = (n_docs + h->uniform.docs_per_block - 1) / h->uniform.docs_per_block;
-        shape = LaunchShape{0, us.head, us.splits};
-    } else {
-        PlanInput in{1, {h->term.per_wave}, {h->term.max_groups}, kPacketRounds, kNumCus, 0.0, 0.0};
-        plan_times(h, in);
-        shape = choose_launch(in, n_blocks);
-    }
-    if (shape.splits == 1)
-        shape.head = n_blocks;
-    return shape;
+    const int docs = uniform ? h->uniform.docs_per_block : 64;
+    const int64_t n_blocks = (n_docs + docs - 1) / docs;
+    return kept_shape(h, uniform ? kUniformWork : int(Work::kTerminal), n_blocks, [&] {
+        LaunchShape shape;
+        if (uniform) {
+            const treeens::UniformShape us = treeens::uniform_shape(h->uniform, n_docs);
+            shape = LaunchShape{0, us.head, us.splits};
+        } else {
+            shape = choose_launch(h->facts, Work::kTerminal, n_blocks);
+        }
+        if (shape.splits == 1)
+            shape.head = n_blocks;
+        return shape;
+    });
 }
 
 // Bytes of a chunk's codes.
@@ -1344,17 +1256,14 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
     std::memcpy(h->level_begin, p.level_begin, sizeof h->level_begin);
     hipError_t e = hipGetDevice(&h->device);
     std::memcpy(h->level_image_off, p.level_image_off, sizeof h->level_image_off);
-    std::memcpy(h->level_max_rounds, p.level_max_rounds, sizeof h->level_max_rounds);
-    h->mean_steps = p.mean_steps;
+    h->facts = treeens::plan_facts(p);
     h->usage_slot_off = p.usage_slot_off;
     h->pk_recs = p.pk_recs;
     h->pk_zero_rec = p.pk_zero_rec;
     h->pk_per_walker = p.pk_per_walker;
-    h->pk_max_groups = p.pk_max_groups;
     std::memcpy(h->level_slot_recs, p.level_slot_recs, sizeof h->level_slot_recs);
     h->cp_k = p.cp_k;
     h->cp_per_walker = p.cp_per_walker;
-    h->cp_max_groups = p.cp_max_groups;
     h->n_small = p.n_small;
     h->big_off0 = p.tree_node_off[size_t(p.n_small)];
     h->term = p.term;
