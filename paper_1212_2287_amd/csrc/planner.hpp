@@ -17,6 +17,7 @@ struct LaunchShape {
     int level = 0;
     int64_t head = 0;
     int splits = 1;
+    double us = 0.0; // the estimate it was chosen by
 };
 
 // What a launch does with the leaves it reaches.
@@ -38,9 +39,12 @@ struct Tiling {
     double switch_rounds = 0.0;
 };
 struct PlanFacts {
-    Tiling walk, term;
+    Tiling walk, term; // term.tiles[0] == 0: no terminal packets
+    UniformPlan uniform{};
     bool pairs = false, full = false; // two workgroups on a CU; four trees per lane
+    bool compact = false;             // the walk takes compact packets
     double mean_steps = 0.0;
+    int32_t n_trees = 0, n_cols = 0, n_outputs = 1, docs_per_block = 0;
 };
 
 constexpr double kTileRounds = 0.5;   // switching tiles (barriers, the copy into LDS), in walker rounds
@@ -50,7 +54,13 @@ inline PlanFacts plan_facts(const Packed &p) {
     PlanFacts f;
     f.pairs = p.plan.lds_bytes <= kLdsPerCu / 2;
     f.full = p.plan.interleave == 4;
+    f.compact = p.cp_k > 0;
     f.mean_steps = p.mean_steps;
+    f.n_trees = p.n_trees;
+    f.n_cols = p.n_cols;
+    f.n_outputs = p.n_outputs;
+    f.docs_per_block = p.plan.docs_per_block;
+    f.uniform = p.uniform;
     auto packets = [](int per_wave, int max_groups, double mean_groups) {
         Tiling t;
         t.tiles[0] = per_wave, t.max_rounds[0] = max_groups, t.mean_rounds[0] = mean_groups;
@@ -95,9 +105,12 @@ inline PlanFacts plan_facts(const Packed &p) {
 // models, each measured in all its shapes, the shapes picked take 1 to 3% longer than the fastest on
 // average (two workgroups of fewer than four trees per lane: 13%, most of it in batches below 1,000
 // documents).
+// Terminal packets are bound by latency and the L2s: workgroups whose shares are a packet short leave the
+// others more of both, so a fifth of the average share counts (5,000 trees, 500 documents, 80
+// packets: 27 shares of 2 or 3 58.9 us, 32 such shares 51.3).
 struct PlanTimes {
     int64_t places;
-    double round_us, next_us, lone, reduce_us;
+    double round_us, next_us, lone, reduce_us, average;
 };
 inline PlanTimes plan_times(const PlanFacts &f, Work work) {
     const bool full_pairs = f.pairs && f.full && work != Work::kTerminal;
@@ -108,6 +121,7 @@ inline PlanTimes plan_times(const PlanFacts &f, Work work) {
     t.next_us = full_pairs ? 1.75 : 4.5;
     t.lone = vector ? 1.1 : 1.0;
     t.reduce_us = work == Work::kPositions ? 0.0 : 3.75;
+    t.average = work == Work::kTerminal ? 0.2 : 0.0;
     return t;
 }
 
@@ -117,8 +131,8 @@ inline LaunchShape choose_launch(const PlanFacts &f, Work work, int64_t n_blocks
     constexpr double kPerSplit = 0.015; // of the second kernel
     const Tiling &tl = work == Work::kTerminal ? f.term : f.walk;
     const PlanTimes pt = plan_times(f, work);
-    auto rounds_of = [&](int level, int tiles) {
-        return double(tiles) * (tl.mean_rounds[level] + tl.switch_rounds) + (tl.max_rounds[level] - tl.mean_rounds[level]);
+    auto rounds_of = [&](int level, double tiles) {
+        return tiles * (tl.mean_rounds[level] + tl.switch_rounds) + (tl.max_rounds[level] - tl.mean_rounds[level]);
     };
     double best = 1e300;
     LaunchShape pick;
@@ -126,13 +140,14 @@ inline LaunchShape choose_launch(const PlanFacts &f, Work work, int64_t n_blocks
         const int nt = tl.tiles[level];
         const int64_t tail = n_blocks - head;
         const int64_t heads = (head + pt.places - 1) / pt.places, tails = (tail * sp + pt.places - 1) / pt.places;
-        const double rounds = double(heads) * rounds_of(level, nt) + double(tails) * rounds_of(level, (nt + sp - 1) / sp);
+        const double share = (1.0 - pt.average) * double((nt + sp - 1) / sp) + pt.average * double(nt) / double(sp);
+        const double rounds = double(heads) * rounds_of(level, nt) + double(tails) * rounds_of(level, share);
         const double cost = kFirst + double(heads + tails - 1) * pt.next_us +
                             rounds * pt.round_us * (heads + tails == 1 ? pt.lone : 1.0) + (sp > 1 && pt.reduce_us > 0.0 ? pt.reduce_us + kPerSplit * sp : 0.0) +
                             kPerWorkgroup * double(head + tail * sp);
         if (cost < best - 1e-9) {
             best = cost;
-            pick = LaunchShape{level, head, sp};
+            pick = LaunchShape{level, head, sp, cost};
         }
     };
     for (int k = 0; k < tl.n_levels; ++k)
@@ -142,6 +157,93 @@ inline LaunchShape choose_launch(const PlanFacts &f, Work work, int64_t n_blocks
         for (int sp = 2; head < n_blocks && sp <= std::min(tl.tiles[0], 64); ++sp)
             consider(0, head, sp);
     return pick;
+}
+
+// Uniform launches: `head` document blocks walk all chunks of trees, the others are split over
+// `splits` workgroups that leave partial sums.
+inline LaunchShape uniform_shape(const UniformPlan &u, int64_t n_docs) {
+    // one workgroup per CU; time in units of 16 chunks (one per wave)
+    constexpr double kItem = 3.0; // staging and reduction of one workgroup (measured)
+    constexpr double kReduce = 1.0;
+    const int64_t n_blocks = (n_docs + u.docs_per_block - 1) / u.docs_per_block;
+    const double all = double(u.n_chunks) / 16.0;
+    LaunchShape best{0, n_blocks, 1};
+    double least = 1e300;
+    auto consider = [&](int64_t head, int splits) {
+        const double share = double((u.n_chunks + splits - 1) / splits + 15) / 16.0; // fullest wave
+        const double cost = double((head + kNumCus - 1) / kNumCus) * (all + kItem) +
+                            double(((n_blocks - head) * splits + kNumCus - 1) / kNumCus) * (share + kItem) +
+                            (splits > 1 ? kReduce : 0.0);
+        if (cost < least - 1e-9) {
+            least = cost;
+            best = LaunchShape{0, head, splits, cost};
+        }
+    };
+    consider(n_blocks, 1);
+    const int most = int(std::max<int64_t>(1, std::min<int64_t>(u.n_chunks / 16, 256)));
+    for (int s = 2; s <= most; ++s) {
+        consider(0, s);
+        if (n_blocks > kNumCus && n_blocks % kNumCus != 0)
+            consider(n_blocks / kNumCus * kNumCus, s);
+    }
+    return best;
+}
+
+// Which kernels a call takes.
+
+// Shallow models by uniform evaluation, or by the walk.
+// Coding and staging cost a document as much as 32 trees per feature save (4,000 trees, 136
+// features, 100,000 documents: 202 us by the walk, 207 this way; 1,000 trees, 30 features: 64, 64;
+// 20,000 trees, 136 features: 937, 724), and the second launch and the scratch as much as 1e8 walks
+// (20,000 trees, 1,000 documents: 27 against 36 us, 10,000 documents: 126 against 99).
+inline bool uniform_pays(const PlanFacts &f, int64_t n_docs) {
+    return f.uniform.depth > 0 && f.n_trees >= 40 * int64_t(f.n_cols) && double(n_docs) * f.n_trees >= 1.0e8;
+}
+
+// Coded models by terminal packets, or by the walk. The packer makes them for coded models only: those
+// code their documents anyway, where models of float documents would pay for it (1,000 trees of 64
+// leaves, 700 features, 50,000 documents: 215 us on floats, 86 + 206 us on codes). Small batches of
+// fewer than kTermTreesAlways trees keep the compact packets, whose walk ends without the terminals' two
+// loads (us by compact packets against terminal ones: 1,024 trees of 256 leaves, 1,000 documents 42.3,
+// 48.9, 2,000 49.6, 52.8, 6,700 76.9, 74.8; 300 trees of 200 leaves, 6,700 documents 51.0, 54.0, 10,000
+// 56.4, 54.6; 2,000 trees of 150 leaves, 64 documents 24.7, 21.3, 1,000 35.5, 33.5). Trees beyond the
+// compact packets (over 256 leaves) always take the terminal ones (1,000 trees of 512 leaves, 50,000
+// documents: 912 us by 8-byte records, 524; 300 trees, 100 documents: 34.4, 32.2).
+constexpr int32_t kTermTreesAlways = 1536;
+inline bool term_pays(const PlanFacts &f, int64_t n_docs) {
+    return f.term.tiles[0] > 0 &&
+           (!f.compact || f.n_trees >= kTermTreesAlways || double(n_docs) * f.n_trees >= 2.5e6);
+}
+
+// Leaf ids: whether the walk stores them directly.
+// The walk stores ids directly where that is as fast: outputs of at most kLeafDirectBytes (the
+// L2s hold them until their lines are full; 1,000 trees x 1,000 documents 16.5 us against 28 us,
+// x 2,500 39 against 28), twice that below 256 trees (128 x 30,000: 26.8 against 28.7 us), and
+// rows of fewer than kLeafDirectTrees ids at any size (the L2s then hold the rows of all resident
+// blocks; 100 x 30,000: 22.6 against 26.8 us; 128 x 100,000: 79.8 against 59.3). Calls captured
+// into a graph store ids directly too (they then hold no buffer), as does a call whose scratch
+// cannot be allocated.
+constexpr int32_t kLeafDirectTrees = 128;
+constexpr int64_t kLeafDirectBytes = int64_t(8) << 20;
+constexpr int64_t kPositionBytes = int64_t(256) << 20;
+inline bool leaves_direct(const PlanFacts &f, int64_t n_docs) {
+    const int64_t most = f.n_trees < 2 * kLeafDirectTrees ? 2 * kLeafDirectBytes : kLeafDirectBytes;
+    return f.n_trees < kLeafDirectTrees || n_docs <= most / 4 / f.n_trees;
+}
+
+// Vector-valued scores. More than four outputs of enough documents: the walk stores each
+// leaf's row once, and sum_rows_kernel adds up to eight outputs per pass; else one walk per four.
+// Smaller batches do not pay for the second launch and the scratch (8 outputs, 1,000 trees: 2,000
+// documents 33 us by two walks against 40, 5,000 documents 51 against 47; 100 trees: 1,024 documents
+// 24 against 25, 10,000 documents 32 against 25), nor do many trees of few documents (4,000 trees of 8
+// leaves, 5,000 documents: 83 against 110, 20,000 documents of 2,000 trees: 161 against 139).
+// Up to four outputs one walk does it all.
+// Nor do models whose chunks hold fewer than kRowDocs documents (64 of them fill a workgroup):
+// 10,000 trees of 8 leaves, 6 outputs, 50,000 documents in chunks of 6,500: 1,474 against 2,194 us.
+constexpr int64_t kRowDocs = 32768;
+inline bool rows_pay(const PlanFacts &f, int64_t n_docs) {
+    return f.n_outputs > 4 && n_docs >= std::max<int64_t>(4096, 4 * int64_t(f.n_trees)) &&
+           f.n_trees * kRowDocs * int64_t(sizeof(uint16_t)) <= kPositionBytes;
 }
 
 } // namespace treeens

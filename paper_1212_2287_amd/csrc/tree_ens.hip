@@ -953,41 +953,16 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
     return TREE_ENS_OK;
 }
 
-// Scores of a shallow model by uniform evaluation. `taken` is false (and nothing was launched) for
-// calls that keep the walk: those that do not pay for the coding pass and a workgroup's staging, and
-// when the scratch cannot be had (allocation-free calls: batches beyond the static array).
-// Coding and staging cost a document as much as 32 trees per feature save (4,000 trees, 136
-// features, 100,000 documents: 202 us by the walk, 207 this way; 1,000 trees, 30 features: 64, 64;
-// 20,000 trees, 136 features: 937, 724), and the second launch and the scratch as much as 1e8 walks
-// (20,000 trees, 1,000 documents: 27 against 36 us, 10,000 documents: 126 against 99).
-bool uniform_pays(const tree_ens *h, int64_t n_docs) {
-    return h->n_trees >= 40 * int64_t(h->n_cols) && double(n_docs) * h->n_trees >= 1.0e8;
-}
-
-// Scores by terminal packets, in calls of the same kind. The packer makes them for coded
-// models only: those code their documents anyway, where models of float documents would pay for it
-// (1,000 trees of 64 leaves, 700 features, 50,000 documents: 215 us on floats, 86 + 206 us on codes). Small batches of few trees keep the
-// compact packets, whose walk ends without the terminals' two loads (300 trees of 200 leaves, 1,000
-// documents: 60.7 against 62.1 us; 10,000 documents: 71.9 against 69.6; 5,000 trees of 256 leaves, 100
-// documents: 40.2 against 37.9). Trees beyond the compact packets (over 256 leaves) always take them
-// (1,000 trees of 512 leaves, 50,000 documents: 912 us by 8-byte records, 524; 300 trees, 100
-// documents: 34.4, 32.2).
-bool term_pays(const tree_ens *h, int64_t n_docs) {
-    return h->cp_k == 0 || h->n_trees >= 1024 || double(n_docs) * h->n_trees >= 2.0e6;
-}
-
+// Scores of a shallow model by uniform evaluation, or of a coded one by terminal packets. `taken` is
+// false (and nothing was launched) for calls that keep the walk (uniform_pays, term_pays), and when the
+// scratch cannot be had (allocation-free calls: batches beyond the static array).
 // Launch shape of `n_docs` coded documents: uniform blocks or terminal packets.
 LaunchShape coded_shape(const tree_ens *h, bool uniform, int64_t n_docs) {
     const int docs = uniform ? h->uniform.docs_per_block : 64;
     const int64_t n_blocks = (n_docs + docs - 1) / docs;
     return kept_shape(h, uniform ? kUniformWork : int(Work::kTerminal), n_blocks, [&] {
-        LaunchShape shape;
-        if (uniform) {
-            const treeens::UniformShape us = treeens::uniform_shape(h->uniform, n_docs);
-            shape = LaunchShape{0, us.head, us.splits};
-        } else {
-            shape = choose_launch(h->facts, Work::kTerminal, n_blocks);
-        }
+        LaunchShape shape = uniform ? treeens::uniform_shape(h->uniform, n_docs)
+                                    : choose_launch(h->facts, Work::kTerminal, n_blocks);
         if (shape.splits == 1)
             shape.head = n_blocks;
         return shape;
@@ -1000,8 +975,8 @@ constexpr int64_t kCodeChunkBytes = int64_t(256) << 20;
 int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features,
                          float *scores, ScratchSource source, bool *taken) {
     *taken = false;
-    const bool uniform = h->uniform.depth > 0 && uniform_pays(h, n_docs);
-    const bool term = !uniform && h->term.per_wave > 0 && term_pays(h, n_docs);
+    const bool uniform = uniform_pays(h->facts, n_docs);
+    const bool term = !uniform && term_pays(h->facts, n_docs);
     if ((!uniform && !term) || n_docs > int64_t(64) * 0x7ffffff)
         return TREE_ENS_OK;
     // Shallow models of any batch borrow a bounded amount: their documents go in chunks of whole rounds
@@ -1043,7 +1018,7 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
             break;
         if (uniform)
             treeens::launch_uniform(h->uniform, stream, codes, nd, h->n_cols, h->d_uniform_nodes, h->d_uniform_leaves,
-                                    treeens::UniformShape{sh.head, sh.splits}, partials, out, scale);
+                                    sh, partials, out, scale);
         else
             treeens::launch_term(h->term, stream, codes, nd, h->n_cols, h->d_term_packets, h->d_term_slots, sh.head,
                                  sh.splits, partials, out, scale);
@@ -1062,22 +1037,8 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
 // positions (and codes) take at most kPositionBytes (they stay in the last-level cache). 1,000 trees of 32
 // leaves, 30,011 documents: 383 us with ids stored by the walk, 103 us this way (62 us the walk,
 // 37 us the second kernel at 4.8 TB/s).
-// The walk stores ids directly where that is as fast: outputs of at most kLeafDirectBytes (the
-// L2s hold them until their lines are full; 1,000 trees x 1,000 documents 16.5 us against 28 us,
-// x 2,500 39 against 28), twice that below 256 trees (128 x 30,000: 26.8 against 28.7 us), and
-// rows of fewer than kLeafDirectTrees ids at any size (the L2s then hold the rows of all resident
-// blocks; 100 x 30,000: 22.6 against 26.8 us; 128 x 100,000: 79.8 against 59.3). Calls captured
-// into a graph store ids directly too (they then hold no buffer), as does a call whose scratch
-// cannot be allocated.
-constexpr int32_t kLeafDirectTrees = 128;
-constexpr int64_t kLeafDirectBytes = int64_t(8) << 20;
-constexpr int64_t kPositionBytes = int64_t(256) << 20;
-
-bool leaves_direct(int32_t n_trees, int64_t n_docs) {
-    const int64_t most = n_trees < 2 * kLeafDirectTrees ? 2 * kLeafDirectBytes : kLeafDirectBytes;
-    return n_trees < kLeafDirectTrees || n_docs <= most / 4 / n_trees;
-}
-
+// Where that does not pay (leaves_direct), in calls captured into a graph and where the scratch cannot
+// be had, the walk stores the ids directly.
 // The walk's leaf positions in chunks of documents (MODE: kModeLeaves or kModeRows), each chunk
 // followed by `then(pos, first document, documents)`. `taken` is false (and nothing was launched)
 // when the scratch cannot be had.
@@ -1123,7 +1084,7 @@ Fn pick_block(int dl, Fn f64, Fn f32, Fn f16, Fn f8) {
 int launch_leaves(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs,
                   int32_t n_features, int32_t *leaf_ids) {
     bool taken = false;
-    if (!leaves_direct(h->n_trees, n_docs) && !capturing(stream)) {
+    if (!leaves_direct(h->facts, n_docs) && !capturing(stream)) {
         const int dl = h->plan.docs_per_block;
         // compact packets store input node ids, the other records positions in the packed tree
         const int32_t *map = h->cp_k > 0 ? nullptr : h->d_orig_id;
@@ -1142,25 +1103,12 @@ int launch_leaves(const tree_ens *h, hipStream_t stream, const float *X, int64_t
     return launch_predict<kModeLeaves>(h, stream, X, n_docs, n_features, nullptr, leaf_ids);
 }
 
-// Vector-valued scores. More than kVecPerLaunch outputs of enough documents: the walk stores each
-// leaf's row once, and sum_rows_kernel adds up to eight outputs per pass; else one walk per four.
-// Smaller batches do not pay for the second launch and the scratch (8 outputs, 1,000 trees: 2,000
-// documents 33 us by two walks against 40, 5,000 documents 51 against 47; 100 trees: 1,024 documents
-// 24 against 25, 10,000 documents 32 against 25), nor do many trees of few documents (4,000 trees of 8
-// leaves, 5,000 documents: 83 against 110, 20,000 documents of 2,000 trees: 161 against 139).
-// Up to four outputs one walk does it all.
-// Nor do models whose chunks hold fewer than kRowDocs documents (64 of them fill a workgroup):
-// 10,000 trees of 8 leaves, 6 outputs, 50,000 documents in chunks of 6,500: 1,474 against 2,194 us.
-constexpr int64_t kRowDocs = 32768;
-bool rows_pay(const tree_ens *h, int64_t n_docs) {
-    return h->n_outputs > kVecPerLaunch && n_docs >= std::max<int64_t>(4096, 4 * int64_t(h->n_trees)) &&
-           h->n_trees * kRowDocs * int64_t(sizeof(uint16_t)) <= kPositionBytes;
-}
-
+// Vector-valued scores: the walk stores each leaf's row once and sum_rows_kernel adds up to eight outputs
+// per pass, or (rows_pay) one walk per four outputs.
 int launch_vector(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features, float *scores,
                   ScratchSource source) {
     bool taken = false;
-    if (rows_pay(h, n_docs)) {
+    if (rows_pay(h->facts, n_docs)) {
         const int dl = h->plan.docs_per_block, n_out = h->n_outputs;
         auto *two = pick_block(dl, sum_rows_kernel<64, 2>, sum_rows_kernel<32, 2>, sum_rows_kernel<16, 2>, sum_rows_kernel<8, 2>);
         auto *one = pick_block(dl, sum_rows_kernel<64, 1>, sum_rows_kernel<32, 1>, sum_rows_kernel<16, 1>, sum_rows_kernel<8, 1>);

@@ -292,36 +292,8 @@ uniform_kernel(const uint16_t *__restrict__ codes, int64_t n_docs, int32_t n_col
 
 } // namespace
 
-UniformShape uniform_shape(const UniformPlan &u, int64_t n_docs) {
-    // one workgroup per CU; time in units of 16 chunks (one per wave)
-    constexpr double kItem = 3.0; // staging and reduction of one workgroup (measured)
-    constexpr double kReduce = 1.0;
-    const int64_t n_blocks = (n_docs + u.docs_per_block - 1) / u.docs_per_block;
-    const double all = double(u.n_chunks) / 16.0;
-    UniformShape best{n_blocks, 1};
-    double least = 1e300;
-    auto consider = [&](int64_t head, int splits) {
-        const double share = double((u.n_chunks + splits - 1) / splits + 15) / 16.0; // fullest wave
-        const double cost = double((head + kNumCus - 1) / kNumCus) * (all + kItem) +
-                            double(((n_blocks - head) * splits + kNumCus - 1) / kNumCus) * (share + kItem) +
-                            (splits > 1 ? kReduce : 0.0);
-        if (cost < least - 1e-9) {
-            least = cost;
-            best = UniformShape{head, splits};
-        }
-    };
-    consider(n_blocks, 1);
-    const int most = int(std::max<int64_t>(1, std::min<int64_t>(u.n_chunks / 16, 256)));
-    for (int s = 2; s <= most; ++s) {
-        consider(0, s);
-        if (n_blocks > kNumCus && n_blocks % kNumCus != 0)
-            consider(n_blocks / kNumCus * kNumCus, s);
-    }
-    return best;
-}
-
 void launch_uniform(const UniformPlan &u, hipStream_t stream, const uint16_t *codes, int64_t n_docs, int32_t n_cols,
-                    const uint32_t *nodes, const double *leaves, const UniformShape &shape, double *partials,
+                    const uint32_t *nodes, const double *leaves, const LaunchShape &shape, double *partials,
                     float *scores, double scale) {
     const int words = u.docs_per_block / 128;
     auto *fn = u.depth == 3 ? (words == 4 ? uniform_kernel<3, 4> : words == 2 ? uniform_kernel<3, 2> : uniform_kernel<3, 1>)

@@ -7,21 +7,14 @@
 #include <hip/hip_runtime.h>
 
 #include "pack.hpp"
+#include "planner.hpp"
 
 namespace treeens {
-
-// Workgroups of a uniform launch: `head` document blocks walk all chunks of trees, the others are
-// split over `splits` workgroups that leave partial sums.
-struct UniformShape {
-    int64_t head;
-    int splits;
-};
-UniformShape uniform_shape(const UniformPlan &u, int64_t n_docs);
 
 // codes: rows of n_cols 16-bit threshold codes. Blocks past the head leave partial sums
 // [split][doc - head * docs_per_block] in `partials` (splits > 1).
 void launch_uniform(const UniformPlan &u, hipStream_t stream, const uint16_t *codes, int64_t n_docs, int32_t n_cols,
-                    const uint32_t *nodes, const double *leaves, const UniformShape &shape, double *partials,
+                    const uint32_t *nodes, const double *leaves, const LaunchShape &shape, double *partials,
                     float *scores, double scale);
 
 } // namespace treeens

@@ -25,3 +25,24 @@ int plan_model(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feat
     return 0;
 }
 }
+
+extern "C" {
+
+// pays[i]: whether documents docs[i] take rule `rule` (0 uniform, 1 terminal, 2 ids stored directly, 3 leaf rows).
+int plan_rules(int32_t n_trees, const int64_t *tree_offsets, const int32_t *feature, const float *threshold,
+               const int32_t *left, const int32_t *right, const float *value, int32_t n_outputs, int32_t n,
+               const int32_t *rule, const int64_t *docs, int32_t *pays) {
+    treeens::Packed p;
+    std::string err;
+    const int rc = treeens::pack_model(n_trees, tree_offsets, feature, threshold, left, right, value, n_outputs, 0, p, err);
+    if (rc != treeens::kOk)
+        return rc;
+    const treeens::PlanFacts f = treeens::plan_facts(p);
+    for (int32_t i = 0; i < n; i++)
+        pays[i] = rule[i] == 0   ? treeens::uniform_pays(f, docs[i])
+                  : rule[i] == 1 ? treeens::term_pays(f, docs[i])
+                  : rule[i] == 2 ? treeens::leaves_direct(f, docs[i])
+                                 : treeens::rows_pay(f, docs[i]);
+    return 0;
+}
+}

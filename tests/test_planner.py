@@ -1,6 +1,6 @@
 """The launch planner on packed models: shapes a launch can run, for batches and models of all kinds; no
-split without something to gain; and shapes that were measured: the ones picked are the fastest of
-their batch, or within a few percent."""
+split without something to gain; shapes that were measured: the ones picked are the fastest of
+their batch, or within a few percent; and the choice of kernels on both sides of each rule."""
 from __future__ import annotations
 
 import ctypes
@@ -24,17 +24,22 @@ def lib(tmp_path_factory):
                     os.path.join(CSRC, "pack.cpp"), "-o", out], check=True)
     lib = ctypes.CDLL(out)
     P = ctypes.c_void_p
-    lib.plan_model.argtypes = [ctypes.c_int32, P, P, P, P, P, P, ctypes.c_int32, ctypes.c_int32, P, P, P]
+    for fn in (lib.plan_model, lib.plan_rules):
+        fn.argtypes = [ctypes.c_int32, P, P, P, P, P, P, ctypes.c_int32, ctypes.c_int32, P, P, P]
     return lib
 
 
-def _plan(lib, ens, asks, n_out=1):
-    """(level, head, splits, tiles) of each (work, documents)."""
+def _model(ens, n_out):
     arrs = [np.ascontiguousarray(a, t) for a, t in ((ens.tree_offsets, np.int64), (ens.feature, np.int32),
             (ens.threshold, np.float32), (ens.left, np.int32), (ens.right, np.int32), (ens.value, np.float32))]
     if n_out > 1:
         arrs[5] = np.zeros((ens.n_nodes, n_out), np.float32)
-    args = (ens.n_trees, *[a.ctypes.data for a in arrs], n_out)
+    return arrs, (ens.n_trees, *[a.ctypes.data for a in arrs], n_out)
+
+
+def _plan(lib, ens, asks, n_out=1):
+    """(level, head, splits, tiles, blocks) of each (work, documents)."""
+    _keep, args = _model(ens, n_out)
     out = np.zeros((len(asks), 5), np.int64)
     work = np.array([w for w, _ in asks], np.int32)
     one = np.ones(len(asks), np.int64)
@@ -63,6 +68,15 @@ def test_shapes_can_be_launched(lib, trees, features, least, most):
             assert head <= blocks
 
 
+def _forest(trees, features, least, most, depth=None):
+    """`trees` trees, at most 64 different ones; the widest feature is read."""
+    base = W.random_ensemble(features + trees + least, min(trees, 64), features, least, most, depth, thr_values=VALUES)
+    base.feature[np.argmax(base.feature >= 0)] = features - 1
+    each = [base.tree(t % base.n_trees) for t in range(trees)]
+    offsets = np.concatenate([[0], np.cumsum([len(t[0]) for t in each])]).astype(np.int64)
+    return W.Ensemble(offsets, *[np.concatenate([t[k] for t in each]) for k in range(5)], features)
+
+
 @pytest.mark.parametrize("trees,features,least,most,work,docs,shapes", [
     # leaf ids reduce nothing: 8.5 us in two shares, 11.6 whole
     (128, 136, 32, 32, POSITIONS, 100, [(0, 2)]), (128, 136, 32, 32, POSITIONS, 3_000, [(0, 2)]),
@@ -72,13 +86,36 @@ def test_shapes_can_be_launched(lib, trees, features, least, most):
     (600, 136, 5, 300, SCORES, 3_000, [(0, s) for s in range(5, 13)]),
     # terminal packets, 105 blocks: 187 us in halves, 234 in seven shares
     (5_000, 700, 256, 256, TERMINAL, 6_700, [(0, 2)]), (1_000, 700, 512, 512, TERMINAL, 6_700, [(0, 2)]),
+    # 80 packets, 8 blocks: 51.3 us in 32 shares of 2 or 3, 58.9 in 27
+    (5_000, 700, 256, 256, TERMINAL, 500, [(0, 32)]),
     # 300 trees, 63 blocks of 8 documents: 13.5 us whole, 15.7 in three shares
     (300, 2_000, 30, 30, SCORES, 500, [(0, 1)]),
 ])
 def test_measured_shapes(lib, trees, features, least, most, work, docs, shapes):
-    base = W.random_ensemble(features + trees + least, min(trees, 64), features, least, most, thr_values=VALUES)
-    each = [base.tree(t % base.n_trees) for t in range(trees)]
-    offsets = np.concatenate([[0], np.cumsum([len(t[0]) for t in each])]).astype(np.int64)
-    ens = W.Ensemble(offsets, *[np.concatenate([t[k] for t in each]) for k in range(5)], features)
+    ens = _forest(trees, features, least, most)
     _, head, splits, _, _ = _plan(lib, ens, [(work, docs)])[0]
     assert (head, splits) in shapes or (splits == 1 and (0, 1) in shapes)
+
+
+def _pays(lib, ens, rule, docs, n_out=1):
+    _keep, args = _model(ens, n_out)
+    n = len(docs)
+    pays = np.zeros(n, np.int32)
+    assert lib.plan_rules(*args, n, np.full(n, rule, np.int32).ctypes.data, np.array(docs, np.int64).ctypes.data,
+                          pays.ctypes.data) == 0
+    return pays.tolist()
+
+
+@pytest.mark.parametrize("trees,features,least,most,walked,terminal", [
+    # documents at which the walk by compact packets was the faster, and the terminal packets
+    (1_024, 700, 256, 256, [500, 1_000, 2_000], [3_500, 6_700, 20_000]),
+    (300, 450, 200, 200, [100, 2_000, 6_700], [10_000, 20_000]),
+    (1_100, 450, 100, 255, [1_000, 2_000], [6_700, 50_000]),
+    (2_000, 600, 150, 150, [], [1, 64, 1_000, 50_000]),
+    (60, 600, 400, 600, [], [1, 1_000]),           # trees beyond the compact packets
+    (1_000, 136, 32, 32, [100, 100_000], []),      # float documents
+])
+def test_terminal_packets_where_they_pay(lib, trees, features, least, most, walked, terminal):
+    ens = _forest(trees, features, least, most)
+    assert _pays(lib, ens, 1, walked) == [0] * len(walked)
+    assert _pays(lib, ens, 1, terminal) == [1] * len(terminal)
