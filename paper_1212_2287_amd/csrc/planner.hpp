@@ -231,19 +231,26 @@ inline bool leaves_direct(const PlanFacts &f, int64_t n_docs) {
     return f.n_trees < kLeafDirectTrees || n_docs <= most / 4 / f.n_trees;
 }
 
-// Vector-valued scores. More than four outputs of enough documents: the walk stores each
-// leaf's row once, and sum_rows_kernel adds up to eight outputs per pass; else one walk per four.
-// Smaller batches do not pay for the second launch and the scratch (8 outputs, 1,000 trees: 2,000
-// documents 33 us by two walks against 40, 5,000 documents 51 against 47; 100 trees: 1,024 documents
-// 24 against 25, 10,000 documents 32 against 25), nor do many trees of few documents (4,000 trees of 8
-// leaves, 5,000 documents: 83 against 110, 20,000 documents of 2,000 trees: 161 against 139).
-// Up to four outputs one walk does it all.
-// Nor do models whose chunks hold fewer than kRowDocs documents (64 of them fill a workgroup):
-// 10,000 trees of 8 leaves, 6 outputs, 50,000 documents in chunks of 6,500: 1,474 against 2,194 us.
+// Vector-valued scores: whether the walk stores each leaf's row once and sum_rows_kernel adds up to eight
+// outputs per pass; else one walk per four (up to four outputs one walk does it all).
+// Smaller batches do not pay for the second launch (us by walks against rows; 8 outputs, 1,000 trees of 32
+// leaves: 2,000 documents 31.6, 38.7, 4,096 43.7, 44.0, 8,192 63.0, 53.2), nor do many trees of few
+// documents (6 outputs, 4,000 trees of 8 leaves: 8,192 documents 118, 127, 12,000 151, 137; 64 outputs,
+// 1,000 trees: 4,096 documents 342, 368, 6,000 488, 378).
+// Nor do models whose chunks hold fewer than kRowDocs documents (64 of them fill a workgroup; 10,000
+// trees of 8 leaves, 6 outputs, 50,000 documents in chunks of 6,500: 1,474, 2,194), and many trees of few
+// steps, whose walks cost less than the gathers of the rows (8 leaves, 50,000 documents: 4,000 trees,
+// 6 outputs 483, 601, 16 outputs 1,011, 1,188; 3,000 trees, 6 outputs 362, 395, 12 outputs 544, 522;
+// 2,000 trees 256, 248; 4,000 trees, 16,384 documents, two full rounds of workgroups: 205, 162).
 constexpr int64_t kRowDocs = 32768;
+constexpr double kCheapSteps = 6.0; // 8 leaves: 5.3, 16: 6.8
 inline bool rows_pay(const PlanFacts &f, int64_t n_docs) {
-    return f.n_outputs > 4 && n_docs >= std::max<int64_t>(4096, 4 * int64_t(f.n_trees)) &&
-           f.n_trees * kRowDocs * int64_t(sizeof(uint16_t)) <= kPositionBytes;
+    if (f.n_outputs <= 4 || f.n_trees * kRowDocs * int64_t(sizeof(uint16_t)) > kPositionBytes)
+        return false;
+    const bool cheap_walks = f.pairs && f.full && f.mean_steps < kCheapSteps;
+    if (cheap_walks && f.n_trees > (f.n_outputs <= 8 ? 2048 : 3072) && n_docs > kRowDocs / 2 + 2048)
+        return false;
+    return n_docs >= std::max<int64_t>(4096, (f.n_outputs <= 32 ? 4 : 5) * int64_t(f.n_trees));
 }
 
 } // namespace treeens

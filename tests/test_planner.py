@@ -119,3 +119,18 @@ def test_terminal_packets_where_they_pay(lib, trees, features, least, most, walk
     ens = _forest(trees, features, least, most)
     assert _pays(lib, ens, 1, walked) == [0] * len(walked)
     assert _pays(lib, ens, 1, terminal) == [1] * len(terminal)
+
+
+@pytest.mark.parametrize("trees,features,leaves,outputs,walked,rows", [
+    (1_000, 136, 32, 8, [500, 2_000], [6_000, 16_384, 200_000]), (1_000, 136, 32, 64, [2_000, 4_096], [6_000, 50_000]),
+    (4_000, 30, 8, 6, [4_096, 8_192, 24_000, 50_000, 200_000], [16_384]),  # walks cheaper than gathers
+    (4_000, 30, 8, 16, [8_192, 50_000], [16_384]), (3_000, 30, 8, 6, [50_000], [16_384]),
+    (3_000, 30, 8, 12, [6_000], [16_384, 50_000]), (2_000, 30, 8, 6, [6_000], [12_000, 16_384, 50_000]),
+    (10, 20, 8, 5, [], [4_096, 200_000]), (4_096, 136, 16, 24, [8_192], [16_384, 100_000]),
+    (6_000, 30, 8, 8, [4_096, 50_000], []),     # chunks too small
+    (300, 1_200, 10, 10, [], [4_096, 200_000]), (300, 136, 32, 4, [4_096, 50_000], []),
+])
+def test_leaf_rows_where_they_pay(lib, trees, features, leaves, outputs, walked, rows):
+    ens = _forest(trees, features, leaves, leaves)
+    assert _pays(lib, ens, 3, walked, outputs) == [0] * len(walked)
+    assert _pays(lib, ens, 3, rows, outputs) == [1] * len(rows)
