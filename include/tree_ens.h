@@ -132,8 +132,8 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
  * the handle (calls on different streams are ordered by an event while they share it), or, if
  * larger, to borrowed memory. Models with threshold-coded features also borrow n_docs x
  * min_features 16-bit codes for the duration of the call, and so do models of trees of depth 2 and 3 in
- * calls of at least 40 trees per feature and 1e8 walks (at most 256 MiB of codes: larger batches go in
- * chunks; without them the call walks the trees instead). Borrowed memory comes from a pool that the
+ * calls of at least 40 trees per feature and 1e8 walks, where an estimate finds that faster (at most 256
+ * MiB of codes: larger batches go in chunks; without them the call walks the trees instead). Borrowed memory comes from a pool that the
  * library keeps on each device: at most 512 MiB, allocated when calls first need it (such a call may
  * take longer), kept between calls, ordered between streams by events and given back when the
  * device's last handle is destroyed. What the pool cannot lend (larger buffers, many streams at once) is a

@@ -191,13 +191,35 @@ inline LaunchShape uniform_shape(const UniformPlan &u, int64_t n_docs) {
 
 // Which kernels a call takes.
 
-// Shallow models by uniform evaluation, or by the walk.
-// Coding and staging cost a document as much as 32 trees per feature save (4,000 trees, 136
-// features, 100,000 documents: 202 us by the walk, 207 this way; 1,000 trees, 30 features: 64, 64;
-// 20,000 trees, 136 features: 937, 724), and the second launch and the scratch as much as 1e8 walks
-// (20,000 trees, 1,000 documents: 27 against 36 us, 10,000 documents: 126 against 99).
+// Shallow models by uniform evaluation, or by the walk: models of at least 40 trees per column in calls
+// of at least 1e8 walks (us by the walk against this; 136 columns, 3,000 trees, 400,000 documents 576,
+// 624; 5,440 trees, 9,191 documents 42.7, 49.3), where the estimates of both agree with it. Both
+// go in whole rounds of blocks, of 512 to 128 documents here and 64 or 32 there, and a batch
+// that just fills rounds of one may leave the other's nearly empty (25 columns, 1,000 trees of depth 2:
+// 100,000 documents 47.8, 42.7, 140,000 59.6, 73.8, 200,000 83.2, 76.9; 300 columns, 12,000 trees: 16,666
+// documents 145, 184, 37,500 305, 294).
+// The estimates: microseconds of uniform evaluation by depth and block, within 6% at the median
+// of 305 measured batches; the walk's by the planner, scaled to complete trees.
+inline double uniform_us(const PlanFacts &f, int64_t n_docs) {
+    const int width = f.uniform.docs_per_block;
+    const double unit = f.uniform.depth == 3 ? (width == 512 ? 9.6 : width == 256 ? 6.1 : 4.1)   // 16 chunks of trees
+                                             : (width == 512 ? 10.4 : width == 256 ? 5.5 : 4.0);
+    const double item = width == 128 ? 8.0 : 4.0;                     // a further workgroup's staging
+    const double call = 9.5, coding = 3.5e-6 * double(n_docs) * f.n_cols, reduce = 4.0;
+    const LaunchShape s = uniform_shape(f.uniform, n_docs);
+    const int64_t n_blocks = (n_docs + width - 1) / width;
+    const double heads = double((s.head + kNumCus - 1) / kNumCus);
+    const double tails = double(((n_blocks - s.head) * s.splits + kNumCus - 1) / kNumCus);
+    const double share = double((f.uniform.n_chunks + s.splits - 1) / s.splits + 15) / 16.0;
+    return call + coding + unit * (heads * f.uniform.n_chunks / 16.0 + tails * share) + item * (heads + tails) +
+           (s.splits > 1 ? reduce : 0.0);
+}
 inline bool uniform_pays(const PlanFacts &f, int64_t n_docs) {
-    return f.uniform.depth > 0 && f.n_trees >= 40 * int64_t(f.n_cols) && double(n_docs) * f.n_trees >= 1.0e8;
+    if (f.uniform.depth == 0 || f.n_trees < 40 * int64_t(f.n_cols) || double(n_docs) * f.n_trees < 1.0e8)
+        return false;
+    const int64_t n_blocks = (n_docs + f.docs_per_block - 1) / f.docs_per_block;
+    const double scale = f.pairs ? (f.uniform.depth == 3 ? 0.8 : 0.65) : (f.uniform.depth == 3 ? 1.05 : 0.95);
+    return uniform_us(f, n_docs) < 1.03 * (8.0 + scale * choose_launch(f, Work::kScores, n_blocks).us);
 }
 
 // Coded models by terminal packets, or by the walk. The packer makes them for coded models only: those

@@ -536,6 +536,7 @@ Pool *pool_of(int device) {
 
 // The handle's kept shape for this work and number of blocks, or that of `choose`.
 constexpr int kUniformWork = 100;
+constexpr int kUniformRule = 101; // (level: whether it pays; by documents)
 template <typename Choose>
 LaunchShape kept_shape(const tree_ens *h, int work, int64_t n_blocks, Choose &&choose) {
     std::lock_guard<std::mutex> lock(h->shape_mu);
@@ -975,7 +976,9 @@ constexpr int64_t kCodeChunkBytes = int64_t(256) << 20;
 int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_t n_docs, int32_t n_features,
                          float *scores, ScratchSource source, bool *taken) {
     *taken = false;
-    const bool uniform = uniform_pays(h->facts, n_docs);
+    const bool uniform =
+        h->uniform.depth > 0 &&
+        kept_shape(h, kUniformRule, n_docs, [&] { return LaunchShape{uniform_pays(h->facts, n_docs)}; }).level != 0;
     const bool term = !uniform && term_pays(h->facts, n_docs);
     if ((!uniform && !term) || n_docs > int64_t(64) * 0x7ffffff)
         return TREE_ENS_OK;

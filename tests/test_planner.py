@@ -134,3 +134,18 @@ def test_leaf_rows_where_they_pay(lib, trees, features, leaves, outputs, walked,
     ens = _forest(trees, features, leaves, leaves)
     assert _pays(lib, ens, 3, walked, outputs) == [0] * len(walked)
     assert _pays(lib, ens, 3, rows, outputs) == [1] * len(rows)
+
+
+@pytest.mark.parametrize("trees,features,depth,walked,uniform", [
+    # documents; 512-, 256- and 128-document blocks
+    (1_000, 25, 2, [50_000, 140_000], [100_000, 450_000, 2_500_000]), (1_000, 25, 3, [50_000], [100_000, 300_000, 1_200_000]),
+    (5_440, 136, 2, [18_382, 36_764, 82_720], [128_676, 459_558]), (5_440, 136, 3, [9_191, 18_382], [128_676, 459_558]),
+    (20_000, 136, 3, [2_500], [10_000, 60_000, 1_000_000]), (8_000, 200, 3, [2_500], [12_500, 87_500, 312_500]),
+    (12_000, 300, 3, [16_666, 25_000], [100_000, 208_333]), (16_800, 420, 3, [8_333, 11_904, 17_857], [71_428]),
+    (3_000, 136, 3, [33_333, 400_000], []),  # too few trees for their columns
+    (2_000, 30, 4, [100_000], []),           # deeper trees
+])
+def test_uniform_evaluation_where_it_pays(lib, trees, features, depth, walked, uniform):
+    ens = _forest(trees, features, 1 << depth, 1 << depth, depth)
+    assert _pays(lib, ens, 0, walked) == [0] * len(walked)
+    assert _pays(lib, ens, 0, uniform) == [1] * len(uniform)
