@@ -238,19 +238,19 @@ inline bool term_pays(const PlanFacts &f, int64_t n_docs) {
 }
 
 // Leaf ids: whether the walk stores them directly.
-// The walk stores ids directly where that is as fast: outputs of at most kLeafDirectBytes (the
-// L2s hold them until their lines are full; 1,000 trees x 1,000 documents 16.5 us against 28 us,
-// x 2,500 39 against 28), twice that below 256 trees (128 x 30,000: 26.8 against 28.7 us), and
-// rows of fewer than kLeafDirectTrees ids at any size (the L2s then hold the rows of all resident
-// blocks; 100 x 30,000: 22.6 against 26.8 us; 128 x 100,000: 79.8 against 59.3). Calls captured
-// into a graph store ids directly too (they then hold no buffer), as does a call whose scratch
-// cannot be allocated.
+// It does where that is as fast (us stored directly against two kernels): outputs of at most
+// kLeafDirectBytes (the L2s hold them until their lines are full; 1,000 trees of 32 leaves x 1,048
+// documents 18.2, 18.5, x 2,621 38.5, 24.8; 256 x 8,192 18.3, 20.8, x 16,384 57.8, 27.5), twice that below
+// 256 trees (128 x 24,576 21.3, 21.5), and rows of fewer than kLeafDirectTrees ids at any size (the
+// L2s then hold the rows of all resident blocks; 100 x 31,457 22.1, 24.4), or four times as many in blocks
+// of 8 documents, of which fewer are resident (300 trees x 41,943 312, 337; 400 x 31,457 201, 196; 1,000 x
+// 12,582 135, 124).
 constexpr int32_t kLeafDirectTrees = 128;
 constexpr int64_t kLeafDirectBytes = int64_t(8) << 20;
 constexpr int64_t kPositionBytes = int64_t(256) << 20;
 inline bool leaves_direct(const PlanFacts &f, int64_t n_docs) {
     const int64_t most = f.n_trees < 2 * kLeafDirectTrees ? 2 * kLeafDirectBytes : kLeafDirectBytes;
-    return f.n_trees < kLeafDirectTrees || n_docs <= most / 4 / f.n_trees;
+    return f.n_trees < (f.docs_per_block == 8 ? 4 : 1) * kLeafDirectTrees || n_docs <= most / 4 / f.n_trees;
 }
 
 // Vector-valued scores: whether the walk stores each leaf's row once and sum_rows_kernel adds up to eight

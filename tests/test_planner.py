@@ -149,3 +149,15 @@ def test_uniform_evaluation_where_it_pays(lib, trees, features, depth, walked, u
     ens = _forest(trees, features, 1 << depth, 1 << depth, depth)
     assert _pays(lib, ens, 0, walked) == [0] * len(walked)
     assert _pays(lib, ens, 0, uniform) == [1] * len(uniform)
+
+
+@pytest.mark.parametrize("trees,features,leaves,direct,rows", [
+    (127, 20, 8, [1_000_000], []), (128, 136, 32, [24_576, 32_768], [32_769, 327_680]),
+    (256, 136, 32, [8_192], [8_193, 163_840]), (1_000, 136, 32, [1_048, 2_097], [2_098, 41_943]),
+    (300, 500, 10, [6_990], [6_991]), (300, 1_200, 10, [6_990], [6_991]),          # 32 and 16 documents a block
+    (300, 2_600, 30, [6_990, 139_810], []), (511, 2_000, 10, [100_000], []), (512, 2_000, 10, [4_096], [4_097]),  # 8
+])
+def test_ids_stored_directly(lib, trees, features, leaves, direct, rows):
+    ens = _forest(trees, features, leaves, leaves)
+    assert _pays(lib, ens, 2, direct) == [1] * len(direct)
+    assert _pays(lib, ens, 2, rows) == [0] * len(rows)
