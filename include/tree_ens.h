@@ -288,6 +288,19 @@ int tree_ens_outputs(const tree_ens_t *h, int32_t *n_outputs, int32_t *n_bags);
 int tree_ens_kernel_timing(const tree_ens_t *h, int32_t enable);
 int tree_ens_kernel_time(const tree_ens_t *h, double *total_ms, int32_t *launches);
 
+/*
+ * tree_ens_last_path -- measurement aid: which kernels the handle's last predict, predict_noalloc,
+ * predict_leaves or feature_usage call enqueued (one of TREE_ENS_PATH_*; with calls on several threads,
+ * that of any of them). Returns TREE_ENS_E_ARG for a NULL handle or path.
+ */
+#define TREE_ENS_PATH_NONE 0     /* no launch yet */
+#define TREE_ENS_PATH_WALK 1     /* the walk, once or per four outputs */
+#define TREE_ENS_PATH_UNIFORM 2  /* shallow models: every node evaluated for every document */
+#define TREE_ENS_PATH_TERMINAL 3 /* walks that end at subtrees of depth 2 */
+#define TREE_ENS_PATH_ROWS 4     /* one walk that stores leaf positions or rows, then a second kernel */
+#define TREE_ENS_PATH_CODEGEN 5  /* the model's own kernel */
+int tree_ens_last_path(const tree_ens_t *h, int32_t *path);
+
 /* tree_ens_destroy -- free the handle and its device memory. NULL is accepted. The caller must
  * ensure no enqueued predict that uses h is still pending. */
 void tree_ens_destroy(tree_ens_t *h);

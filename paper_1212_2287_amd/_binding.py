@@ -26,6 +26,8 @@ TREE_ENS_E_DEVICE = -4
 TREE_ENS_E_NOMEM = -5
 TREE_ENS_RIGHT_IF_GE = 0
 TREE_ENS_RIGHT_IF_GT = 1
+(TREE_ENS_PATH_NONE, TREE_ENS_PATH_WALK, TREE_ENS_PATH_UNIFORM, TREE_ENS_PATH_TERMINAL, TREE_ENS_PATH_ROWS,
+ TREE_ENS_PATH_CODEGEN) = range(6)
 TREE_ENS_CODEGEN = 2  # also compile a kernel specialised for the model (hiprtc)
 
 _CODE_NAMES = {0: "OK", -1: "E_ARG", -2: "E_MODEL", -3: "E_SHAPE", -4: "E_DEVICE", -5: "E_NOMEM"}
@@ -72,6 +74,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.tree_ens_kernel_timing.argtypes = [P, i32]
     lib.tree_ens_kernel_time.restype = ctypes.c_int
     lib.tree_ens_kernel_time.argtypes = [P, P, P]
+    lib.tree_ens_last_path.restype = ctypes.c_int
+    lib.tree_ens_last_path.argtypes = [P, P]
     lib.tree_ens_predict.restype = ctypes.c_int
     lib.tree_ens_predict.argtypes = [P, P, P, i64, i32, P]
     lib.tree_ens_predict_noalloc.restype = ctypes.c_int
@@ -190,6 +194,13 @@ def tree_ens_kernel_time(h) -> tuple[float, int]:
     ms, n = ctypes.c_double(), ctypes.c_int32()
     _check(load_library().tree_ens_kernel_time(h, ctypes.byref(ms), ctypes.byref(n)), "tree_ens_kernel_time")
     return ms.value, n.value
+
+
+def tree_ens_last_path(h) -> int:
+    """Which kernels the handle's last call enqueued (TREE_ENS_PATH_*)."""
+    path = ctypes.c_int32()
+    _check(load_library().tree_ens_last_path(h, ctypes.byref(path)), "tree_ens_last_path")
+    return path.value
 
 
 def _stream_of(t, stream) -> Optional[int]:
@@ -429,6 +440,9 @@ class TreeEnsemble:
 
     def kernel_time(self) -> tuple[float, int]:
         return tree_ens_kernel_time(self.handle)
+
+    def last_path(self) -> int:
+        return tree_ens_last_path(self.handle)
 
     def close(self) -> None:
         if self._h is not None:

@@ -5,6 +5,7 @@
 #include <hip/hiprtc.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstring>
@@ -355,6 +356,7 @@ struct tree_ens {
     mutable std::mutex shape_mu;
     mutable Shape shapes[8];
     mutable unsigned next_shape = 0;
+    mutable std::atomic<int32_t> last_path{TREE_ENS_PATH_NONE};
 };
 
 namespace {
@@ -949,6 +951,7 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
         h->scratch_stream = stream;
         h->scratch_used = true;
     }
+    h->last_path.store(given.leaf_pos ? TREE_ENS_PATH_ROWS : TREE_ENS_PATH_WALK, std::memory_order_relaxed);
     if (e != hipSuccess)
         return hip_fail(e, "kernel launch");
     return TREE_ENS_OK;
@@ -1007,6 +1010,7 @@ int launch_coded_predict(const tree_ens *h, hipStream_t stream, const float *X, 
         return TREE_ENS_OK;
     (void)hipGetLastError();
     *taken = true;
+    h->last_path.store(uniform ? TREE_ENS_PATH_UNIFORM : TREE_ENS_PATH_TERMINAL, std::memory_order_relaxed);
     uint16_t *codes = reinterpret_cast<uint16_t *>(buf);
     double *partials = reinterpret_cast<double *>(buf + codes_bytes);
     const double scale = 1.0 / double(h->n_bags);
@@ -1314,6 +1318,7 @@ int tree_ens_predict(const tree_ens_t *h, void *stream, const float *X, int64_t 
         if (blocks > 0x7fffffff)
             return fail(TREE_ENS_E_ARG, "too many documents for one launch");
         (void)hipGetLastError();
+        h->last_path.store(TREE_ENS_PATH_CODEGEN, std::memory_order_relaxed);
         hipError_t e = hipModuleLaunchKernel(h->cg_fn, unsigned(blocks), 1, 1, treeens::kCodegenThreads,
                                              1, 1, 0, s, args, nullptr);
         return e == hipSuccess ? TREE_ENS_OK : hip_fail(e, "specialised kernel launch");
@@ -1493,6 +1498,14 @@ int tree_ens_kernel_time(const tree_ens_t *h, double *total_ms, int32_t *launche
         *total_ms = sum;
     if (launches)
         *launches = h->t_used;
+    return TREE_ENS_OK;
+}
+
+int tree_ens_last_path(const tree_ens_t *h, int32_t *path) {
+    g_err.clear();
+    if (!h || !path)
+        return fail(TREE_ENS_E_ARG, "handle or path is NULL");
+    *path = h->last_path.load(std::memory_order_relaxed);
     return TREE_ENS_OK;
 }
 

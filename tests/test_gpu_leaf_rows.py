@@ -17,7 +17,7 @@ M = 1 << 20  # ids at which the path changes: 2 M from 256 trees on, 4 M from 12
 
 # (trees, documents, features, leaves): direct below 128 trees and up to the limit, rows past it;
 # trees and documents off the 64-wide tiles; 64-, 32-, 16- and 8-document blocks (136, 500, 1,200
-# and 2,000 features); compact packets (700 features, 150 leaves)
+# and 2,000 features; the last stored directly: fewer than 512 trees); compact packets (700 features, 150 leaves)
 CASES = [
     (127, 4 * M // 127 + 70, 20, 8), (128, 4 * M // 128, 20, 8), (128, 4 * M // 128 + 1, 20, 8),
     (255, 4 * M // 255 + 65, 20, 8), (256, 2 * M // 256, 20, 8), (256, 2 * M // 256 + 1, 20, 8),

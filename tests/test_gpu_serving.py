@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 # trees, features, smallest and largest tree, depth, outputs, documents
 SCORES = [
     (1_000, 25, 8, 8, 3, 1, 99_999), (1_000, 25, 8, 8, 3, 1, 100_000), (1_000, 25, 8, 8, 3, 1, 300_001),  # uniform from 1e8 walks
-    (1_640, 41, 1, 4, 2, 1, 61_001),
-    (304, 450, 100, 255, None, 1, 6_570), (304, 450, 100, 255, None, 1, 6_600),  # terminal packets from 2e6 walks
+    (1_640, 41, 1, 8, 3, 1, 121_954),
+    (304, 450, 100, 255, None, 1, 8_223), (304, 450, 100, 255, None, 1, 8_224),  # terminal packets from 2.5e6 walks
     (304, 450, 100, 255, None, 1, 17_001),
     (160, 500, 400, 512, None, 1, 65), (160, 500, 400, 512, None, 1, 16_449),      # no compact packets: always
     (200, 20, 8, 8, None, 6, 4_095), (200, 20, 8, 8, None, 6, 4_096), (200, 20, 8, 8, None, 5, 30_001),  # one walk

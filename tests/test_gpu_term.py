@@ -1,5 +1,6 @@
-"""Terminal packets on the GPU against the oracle: tree sizes on both sides of a window, cut trees, the widest document tile, partial groups and blocks, split
-batches, both tie rules, IEEE corner values, bags, and the calls that keep the other packets."""
+"""Coded models of one output on the GPU against the oracle, most of them by terminal packets
+(test_gpu_routes.py asserts which): tree sizes on both sides of a window, cut trees, the widest document
+tile, partial groups and blocks, split batches, both tie rules, IEEE corner values, bags."""
 from __future__ import annotations
 
 import numpy as np

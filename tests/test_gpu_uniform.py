@@ -1,6 +1,7 @@
-"""Uniform evaluation of shallow models on the GPU against the oracle: every width of the document
-tile, both depths, partial blocks and chunks, whole rounds of blocks with a split tail, batches split
-over their trees, both tie rules, bags, and the calls that keep the walk."""
+"""Shallow models on the GPU against the oracle, in sizes of 40 trees per feature and 1e8 walks, scored by
+uniform evaluation or the walk (test_gpu_routes.py asserts which): every width of the document tile,
+both depths, partial blocks and chunks, whole rounds of blocks with a split tail, batches split over
+their trees, both tie rules, bags, allocation-free calls, and batches too small for it."""
 from __future__ import annotations
 
 import numpy as np
@@ -20,7 +21,7 @@ def T():
     return T
 
 
-# depth, trees, features, documents: at least 40 trees per feature and 1e8 walks
+# depth, trees, features, documents
 @pytest.mark.parametrize("depth,trees,features,docs,bags", [
     (3, 1_000, 25, 100_001, 1),   # 512-document blocks, split over the trees
     (3, 5_761, 144, 17_921, 3),   # the widest 512-document tile; rows of whole 16 bytes; 35 blocks + 1 doc
@@ -46,14 +47,14 @@ def test_uniform_scores(T, depth, trees, features, docs, bags):
         x = dev(X)
         s = m.predict(x)
         again = m.predict(x)
-        walked = m.predict_noalloc(x, torch.empty_like(s))  # the walk
+        walked = m.predict_noalloc(x, torch.empty_like(s))  # the same kernels, while their scratch fits 16 MiB
         few = m.predict(x[:700].contiguous())               # too small a batch: the walk
         torch.cuda.synchronize()
         assert torch.equal(s, again)
         s, walked, few = s.cpu().numpy(), walked.cpu().numpy(), few.cpu().numpy()
     ref, _, _ = oracle.score(ens, X, rule=flags)
     assert_scores_close(s, ref / bags, "uniform")
-    assert_scores_close(walked, ref / bags, "walk")
+    assert_scores_close(walked, ref / bags, "allocation-free")
     assert_scores_close(few, ref[:700] / bags, "walk, small batch")
 
 
