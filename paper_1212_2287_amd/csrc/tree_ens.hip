@@ -333,7 +333,6 @@ struct tree_ens {
     double *d_scratch = nullptr;
     hipEvent_t scratch_done = nullptr;
     mutable std::mutex scratch_mu;
-    mutable hipStream_t scratch_stream = nullptr;
     mutable bool scratch_used = false;
     // Calls captured into a HIP graph take none of the above (a replay is ordered with nothing
     // the handle records): each captured call gets a buffer of its own for its partial sums and
@@ -878,7 +877,9 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
     if (source == ScratchSource::kHandle && pb > 0 && pb <= kScratchDoubles * sizeof(double) && codes_bytes == 0 &&
         !capturing(stream)) {
         scratch_lock = std::unique_lock<std::mutex>(h->scratch_mu);
-        if (h->scratch_used && h->scratch_stream != stream) {
+        // also where the last call named the same stream: one handle value can stand for several (each
+        // thread's own default stream, a destroyed stream's)
+        if (h->scratch_used) {
             e = hipStreamWaitEvent(stream, h->scratch_done, 0);
             if (e != hipSuccess)
                 return hip_fail(e, "hipStreamWaitEvent");
@@ -945,10 +946,9 @@ int launch_predict(const tree_ens *h, hipStream_t stream, const float *X, int64_
         }
     }
     if (shared_scratch) {
-        // the next eager call from another stream waits for this one's reduction
+        // the next eager call waits for this one's reduction
         if (e == hipSuccess)
             e = hipEventRecord(h->scratch_done, stream);
-        h->scratch_stream = stream;
         h->scratch_used = true;
     }
     h->last_path.store(given.leaf_pos ? TREE_ENS_PATH_ROWS : TREE_ENS_PATH_WALK, std::memory_order_relaxed);

@@ -152,3 +152,36 @@ def test_room_for_the_codes_alone_is_enough(T, n_out):
         call(x, out)  # and with room again
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
+
+
+def test_each_threads_own_default_stream(T):
+    """hipStreamPerThread is one value for a stream of each thread: split batches of one handle from four
+    threads share the handle's scratch one after another."""
+    import threading
+
+    import torch
+    per_thread = 2  # hipStreamPerThread
+    ens = W.random_ensemble(21, 1_000, 136, 32, 32)
+    n = 60
+    with T.TreeEnsemble.from_ensemble(ens) as m:
+        xs = [dev(W.random_docs(100 + i, n, 136)) for i in range(4)]
+        refs = [m.predict(x).clone() for x in xs]
+        outs = [torch.zeros((40, n), device="cuda") for _ in xs]
+        torch.cuda.synchronize()
+        errors = []
+
+        def work(i):
+            try:
+                for o in outs[i]:
+                    m.predict(xs[i], o, stream=per_thread)
+            except Exception as e:  # noqa: BLE001
+                errors.append(e)
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join(60)
+        assert not errors and not any(t.is_alive() for t in threads)
+        torch.cuda.synchronize()
+        for o, r in zip(outs, refs):
+            assert all(torch.equal(row, r) for row in o)
