@@ -12,12 +12,14 @@ Prints ONE JSON line on stdout (progress goes to stderr):
   latency_100doc_us   one 100-document batch: host wall clock of predict + stream sync
   rerank       per-query top-20 of the headline workload's query groups (Section 6's reranking)
   kernel_ms    device time per step (HIP events between steps: every kernel of the call)
-  score_kernel_ms  the scoring kernel's mean launch duration (HIP events the library records
-               right before and after each scoring launch, tree_ens_kernel_timing)
-  roofline     the scoring kernel against the LDS byte roofline (node bytes: 8 per comparison
-               and 4 per leaf, over 256 B/clk/CU), per score_kernel_ms
+  score_kernel_ms  the scoring launches' time per step (HIP events the library records
+               right before and after each, tree_ens_kernel_timing)
+  path         the scoring kernel that ran (tree_ens_last_path): walk, uniform or terminal
+  roofline     the scoring kernel against the LDS byte roofline (256 B/clk/CU), per score_kernel_ms:
+               the node bytes of a walk (8 per comparison, 4 per leaf); for the other kernels
+               the bytes that they read from LDS (lds_read), next to the walk's as a work rate
   roofline_hbm the same kernel against HBM (feature + score bytes)
-  roofline_lds_issue  the node bytes against the LDS instruction ceiling of the walk
+  roofline_lds_issue  the node bytes against the LDS instruction ceiling of the walk (walks only)
   cpu_baseline the oracle on the host cores, same workload
   workloads_extra the other workloads (1M-document ones included), same measurements
 """
@@ -51,7 +53,10 @@ HBM_PEAK_GBS = 8000.0
 LDS_CLK_PER_INSTR = 2.2
 LDS_ISSUE_NODE_GBS = N_CU * CLOCK_HZ * 64 * 8 / (2 * LDS_CLK_PER_INSTR) / 1e9  # 71,494 GB/s
 CSRC = os.path.join(ROOT, "paper_1212_2287_amd", "csrc")
-KERNEL_SRC = [os.path.join(CSRC, n) for n in ("tree_ens.hip", "score.hip", "score.hpp", "uniform.hip", "term.hip", "pack.cpp", "pack.hpp")]
+KERNEL_SRC = [os.path.join(CSRC, n) for n in ("tree_ens.hip", "score.hip", "score.hpp", "uniform.hip", "term.hip",
+                                              "planner.hpp", "pack.cpp", "pack.hpp")]
+PATHS = {1: "walk", 2: "uniform", 3: "terminal", 4: "rows", 5: "codegen"}
+PROBE_CALLS = 3  # of --pmc-probe
 SCORING_KERNELS = ("score_kernel", "uniform_kernel", "term_kernel")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
@@ -74,28 +79,33 @@ def kernel_hash() -> str:
     return h.hexdigest()[:16]
 
 
-def node_depths(ens):
-    """Depth (edges from the root) of every flat node, read off the tree structure."""
+def node_depths(ens, above_height=0):
+    """Depth (edges from the root) of every flat node, read off the tree structure; with
+    ``above_height`` only the ancestors whose subtree is higher than that count."""
     import numpy as np
     depth = np.zeros(ens.n_nodes, dtype=np.int32)
     for t in range(ens.n_trees):
         a = int(ens.tree_offsets[t])
         fe, _, le, ri, _ = ens.tree(t)
-        stack = [0]
-        while stack:
-            n = stack.pop()
+        order, height = [0], {}
+        for n in order:
             if fe[n] >= 0:
-                depth[a + le[n]] = depth[a + ri[n]] = depth[a + n] + 1
-                stack += [int(le[n]), int(ri[n])]
+                order += [int(le[n]), int(ri[n])]
+        for n in reversed(order):
+            height[n] = 1 + max(height[int(le[n])], height[int(ri[n])]) if fe[n] >= 0 else 0
+        for n in order:
+            if fe[n] >= 0:
+                depth[a + le[n]] = depth[a + ri[n]] = depth[a + n] + (height[n] > above_height)
     return depth
 
 
-def count_visits(model, ens, Xd, max_docs=None):
+def count_visits(model, ens, Xd, max_docs=None, above_height=0):
     """Internal nodes visited over all (document, tree) pairs, from the leaves the GPU reaches
-    (leaf depth = comparisons made). With max_docs, counted on a prefix and scaled."""
+    (leaf depth = comparisons made), those of subtrees higher than ``above_height`` only. With
+    max_docs, counted on a prefix and scaled."""
     import torch
     n = Xd.shape[0] if max_docs is None else min(max_docs, Xd.shape[0])
-    depth = torch.from_numpy(node_depths(ens)).to(Xd.device).to(torch.int64)
+    depth = torch.from_numpy(node_depths(ens, above_height)).to(Xd.device).to(torch.int64)
     offs = torch.from_numpy(ens.tree_offsets[:-1]).to(Xd.device)
     total = 0
     chunk = max(1, 50_000_000 // ens.n_trees)
@@ -127,9 +137,9 @@ def step_stats(samples_s):
 def time_steps(model, Xd, out, steps, warmup):
     """Host wall time per step over the timed region, mean device time per step from HIP events
     on the launch stream, the per-step event times (an event between consecutive steps), and the
-    scoring kernel's own mean launch duration (HIP events the library records on the same stream
+    scoring launches' own time per step (HIP events the library records on the same stream
     right before and after each scoring launch: the dominant kernel alone, without the coding
-    pass, the split reduction or launch gaps) with its launch count per step. The launch events
+    pass, the split reduction or launch gaps) with their number per step. The launch events
     come from a second pass of the same steps: recording them between the kernels of a call
     adds gaps to the stream, so the timed steps run without them."""
     import torch
@@ -152,7 +162,19 @@ def time_steps(model, Xd, out, steps, warmup):
     launch_ms, launches = model.kernel_time()
     per = [evs[i].elapsed_time(evs[i + 1]) / 1e3 for i in range(steps)]
     return (wall / steps, evs[0].elapsed_time(evs[steps]) / 1e3 / steps, per,
-            launch_ms / 1e3 / max(launches, 1), launches / steps)
+            launch_ms / 1e3 / steps, launches / steps)
+
+
+def lds_read(path, visits, inner_visits, doc_trees, depth):
+    """Bytes the scoring kernel reads from LDS for what the path needs. uniform: a 2-byte code per node of
+    the tree, an 8-byte leaf. terminal: a 2-byte code and an 8-byte pair of records per comparison above
+    the terminals (subtrees of depth 2, whose splits come from device memory), two 2-byte codes at
+    them. Walks: the node bytes (8-byte record per comparison, 4-byte leaf), without the features."""
+    if path == "uniform":
+        return doc_trees * (2 * (2 ** depth - 1) + 8)
+    if path == "terminal":
+        return inner_visits * 10 + doc_trees * 4
+    return visits * 8 + doc_trees * 4
 
 
 def roofline(kernel_s, lds_bytes, hbm_bytes, traffic):
@@ -167,7 +189,7 @@ def roofline(kernel_s, lds_bytes, hbm_bytes, traffic):
 
 
 def load_traffic(workload: str):
-    """HBM bytes per launch measured with rocprofv3 FETCH_SIZE / WRITE_SIZE (scaled by a copy
+    """HBM bytes of a call's scoring launches measured with rocprofv3 FETCH_SIZE / WRITE_SIZE (scaled by a copy
     kernel of known size), if taken on the current kernel source; else None."""
     try:
         with open(TRAFFIC_FILE) as fh:
@@ -196,21 +218,27 @@ def measure_workload(T, W, wl, steps, warmup, n_docs=None, visits_sample=None):
     del X
     wall_s, kern_s, per_step, launch_s, launches = time_steps(model, Xd, out, steps, warmup)
     doc_trees = cfg.n_docs * cfg.n_trees
+    path = PATHS[model.last_path()]
     visits, sampled = count_visits(model, ens, Xd, visits_sample)
-    lds_bytes = visits * 8 + doc_trees * 4
+    inner = count_visits(model, ens, Xd, visits_sample, above_height=2)[0] if path == "terminal" else visits
+    walk_bytes = visits * 8 + doc_trees * 4
+    lds_bytes = lds_read(path, visits, inner, doc_trees, model.info()["max_depth"])
     hbm_bytes = cfg.n_docs * cfg.n_features * 4 + cfg.n_docs * 4 + model.info()["packed_bytes"]
-    # the roofline of the dominant kernel: one scoring launch per step walks the whole batch
+    # the roofline of the dominant kernel: the scoring launches of a step take the whole batch
     rl, rl_hbm, rl_issue = roofline(launch_s, lds_bytes, hbm_bytes, load_traffic(cfg.name))
+    if path != "walk":
+        rl_issue = None  # its comparisons do not take two LDS instructions
+        rl["walk_equivalent"] = round(walk_bytes / launch_s / 1e9, 1)
     rec = {"workload": cfg.name, "n_trees": cfg.n_trees, "n_leaves": cfg.n_leaves,
            "n_features": cfg.n_features, "n_docs": cfg.n_docs,
            "value": doc_trees / wall_s, "ms_per_step": wall_s * 1e3, "kernel_ms": kern_s * 1e3,
            "score_kernel_ms": launch_s * 1e3, "score_launches_per_step": launches,
            "ns_per_doc": wall_s * 1e9 / cfg.n_docs, "step_stats": step_stats(per_step),
-           "visits": int(visits), "visits_sampled": sampled,
+           "visits": int(visits), "visits_sampled": sampled, "path": path,
            "roofline": rl, "roofline_hbm": rl_hbm, "roofline_lds_issue": rl_issue,
            "model": model.info()}
     log(f"{wl}: {rec['ms_per_step']:.3f} ms/step, {rec['value']:.3e} doc*tree/s, "
-        f"LDS frac {rl['frac']:.3f} (issue ceiling {rl_issue['frac']:.3f})")
+        f"{path}, LDS frac {rl['frac']:.3f}" + (f" (issue ceiling {rl_issue['frac']:.3f})" if rl_issue else ""))
     return rec, model, ens, Xd, out
 
 
@@ -414,7 +442,7 @@ def cpu_baseline(W, wl, budget_s=10.0):
 
 def pmc_probe(T, W, workload: str = HEADLINE) -> int:
     """Copy the workload's feature matrix once (reads and writes exactly its bytes: the
-    calibration for the FETCH_SIZE / WRITE_SIZE counters), then score it three times."""
+    calibration for the FETCH_SIZE / WRITE_SIZE counters), then score it PROBE_CALLS times."""
     import torch
     cfg = W.WORKLOADS[workload]
     ens = W.make_ensemble(cfg)
@@ -425,7 +453,7 @@ def pmc_probe(T, W, workload: str = HEADLINE) -> int:
     torch.cuda.synchronize()
     with T.TreeEnsemble.from_ensemble(ens) as m:
         out = torch.empty(cfg.n_docs, dtype=torch.float32, device="cuda")
-        for _ in range(3):
+        for _ in range(PROBE_CALLS):
             m.predict(Xd, out)
         torch.cuda.synchronize()
     log(f"pmc probe: copied {Xd.numel() * 4} bytes, scored {cfg.n_docs} docs x3")
@@ -434,7 +462,7 @@ def pmc_probe(T, W, workload: str = HEADLINE) -> int:
 
 def write_traffic(fetch_csv: str, write_csv: str, workload: str = HEADLINE,
                   out_path: str = TRAFFIC_FILE) -> int:
-    """Per-launch HBM traffic of the scoring kernel from two rocprofv3 --pmc runs of
+    """HBM traffic of a call's scoring launches from two rocprofv3 --pmc runs of
     --pmc-probe WORKLOAD (FETCH_SIZE, then WRITE_SIZE; KiB per dispatch), each scaled by what
     the same counter reads for the probe's plain device copy of the feature matrix (a kernel
     that reads and writes exactly that many bytes). Runs on the host; adds the workload's entry
@@ -457,7 +485,8 @@ def write_traffic(fetch_csv: str, write_csv: str, workload: str = HEADLINE,
                     scores.append(v)
         if not copies or not scores:
             raise SystemExit(f"{path}: no copy or scoring dispatch with {counter}")
-        return max(copies), statistics.mean(scores), len(scores)
+        per_call = max(1, round(len(scores) / PROBE_CALLS))
+        return max(copies), statistics.mean(scores) * per_call, len(scores)
 
     f_copy, f_score, n_f = per_kernel(fetch_csv, "FETCH_SIZE")
     w_copy, w_score, n_w = per_kernel(write_csv, "WRITE_SIZE")
@@ -473,7 +502,7 @@ def write_traffic(fetch_csv: str, write_csv: str, workload: str = HEADLINE,
         rec = {}
     if rec.get("kernel_hash") != kernel_hash():
         rec = {"kernel_hash": kernel_hash(), "workloads": {}}
-    rec["note"] = ("HBM bytes per launch of the scoring kernel, mean over the probe's dispatches; "
+    rec["note"] = ("HBM bytes of the scoring launches of one call, mean over the probe's calls; "
                    "FETCH_SIZE and WRITE_SIZE each scaled by their reading on a plain device copy "
                    "of the workload's feature matrix (a kernel that moves exactly its bytes).")
     rec["workloads"][cfg.name] = {
@@ -599,7 +628,7 @@ def main() -> int:
                    "n_trees": cfg.n_trees, "n_docs": cfg.n_docs, "n_features": cfg.n_features,
                    "docs_per_block": rec["model"]["docs_per_block"]},
         "ns_per_doc": rec["ns_per_doc"], "kernel_ms": rec["kernel_ms"],
-        "score_kernel_ms": rec["score_kernel_ms"], "step_stats": rec["step_stats"],
+        "score_kernel_ms": rec["score_kernel_ms"], "path": rec["path"], "step_stats": rec["step_stats"],
         "latency_100doc_us": lat, "rerank": rr, "feature_usage": fu,
         "multi_output": mo, "codegen": cg, "visits": rec["visits"],
         "roofline": rec["roofline"], "roofline_hbm": rec["roofline_hbm"],

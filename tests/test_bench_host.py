@@ -72,3 +72,29 @@ def test_roofline_fractions():
     assert rl["frac"] == pytest.approx(0.5, abs=1e-4) and rl["bound"] == "lds"
     assert rl_hbm["frac"] == pytest.approx(0.25, abs=1e-4)
     assert rl_issue["peak"] == pytest.approx(256 * 2.4e9 * 512 / 4.4 / 1e9, rel=1e-6)
+
+
+def test_lds_bytes_of_each_kernel():
+    assert bench.lds_read("walk", 300, 300, 100, 3) == 300 * 8 + 100 * 4
+    assert bench.lds_read("uniform", 300, 300, 100, 3) == 100 * (7 * 2 + 8)   # all nodes, whatever is visited
+    assert bench.lds_read("uniform", 200, 200, 100, 2) == 100 * (3 * 2 + 8)
+    assert bench.lds_read("terminal", 600, 400, 100, 16) == 400 * 10 + 100 * 4
+
+
+def test_depths_above_terminals():
+    import workloads as W
+    ens = W.random_ensemble(3, 20, 5, 1, 40)
+    all_, inner = bench.node_depths(ens), bench.node_depths(ens, 2)
+    for t in range(ens.n_trees):
+        a = int(ens.tree_offsets[t])
+        fe, _, le, ri, _ = ens.tree(t)
+
+        def height(n):
+            return 0 if fe[n] < 0 else 1 + max(height(le[n]), height(ri[n]))
+
+        def walk(n, d, k):
+            assert all_[a + n] == d and inner[a + n] == k
+            if fe[n] >= 0:
+                for c in (le[n], ri[n]):
+                    walk(c, d + 1, k + (height(n) > 2))
+        walk(0, 0, 0)
