@@ -243,7 +243,10 @@ int tree_ens_predict_topk(const tree_ens_t *h, void *stream, const float *X, int
  *                  groups of trees fit, the per-wave packets (one more copy of the records;
  *                  for threshold-coded models of trees up to 511 nodes, compact packets of
  *                  4-byte records with two 4-byte arrays of leaf values and node ids of the
- *                  same shape).
+ *                  same shape; for threshold-coded models of one output also terminal packets of
+ *                  4-byte records with 32 bytes of splits and values per record place, 42 MB on 5,000
+ *                  trees of 256 leaves; for models of depth 2 and 3 also 4 bytes per node and 8 per
+ *                  leaf of the trees padded to that depth, with the coding tables).
  *   n_tiles        LDS tiles the tiled trees are streamed in for a large batch (trees too
  *                  large for one tile are walked from device memory and not counted).
  *   docs_per_block documents a workgroup stages in LDS (a power of two from 8 to 64).
@@ -275,7 +278,10 @@ int tree_ens_outputs(const tree_ens_t *h, int32_t *n_outputs, int32_t *n_bags);
  * HIP events (the paper reports its timings as means over repeated trials, Section 4). enable !=
  * 0 starts a new record: every later eager predict call of h (every mode; calls captured into a
  * HIP graph are not timed) records an event on its stream right before and right after each
- * launch of the scoring kernel, for the first 1,024 such launches; enable == 0 stops recording.
+ * launch of the scoring kernel (a batch that goes in chunks has several), for the first 1,024 such
+ * launches; enable == 0 stops recording. Other kernels of a call are not in it: the coding pass, the
+ * reduction of split sums, and the second kernel of large leaf-id outputs and of leaf vectors of more
+ * than four outputs, which takes about as long as the walk before it.
  * The events are created on the handle's device by the first enabling call (no device memory is
  * allocated) and live until destroy. Returns TREE_ENS_E_ARG for a NULL handle,
  * TREE_ENS_E_DEVICE if an event cannot be created.

@@ -169,10 +169,9 @@ constexpr int kLdsPerCu = 160 * 1024; // gfx950 LDS per compute unit
 // depth D (2 or 3; a leaf above depth D becomes a node that never sends right, with the leaf's
 // value below it) and all its nodes are evaluated for every document (uniform.hip). A chunk holds
 // uniform_trees(D) trees (the last one padded with trees of value 0):
-//   nodes   [tree][2^D][2] words: the threshold code in both halves, the LDS address of the
-//           feature's column; node n's children are 2n + 1 (left) and 2n + 2, the last pair is
-//           unused. A document goes right iff its code >= the threshold code (kUniformNeverRight:
-//           never).
+//   nodes   [tree][2^D] words: threshold code << 16 | LDS address of the feature's column / 64; node n's
+//           children are 2n + 1 (left) and 2n + 2, the last word is unused. A document goes right iff
+//           its code >= the threshold code (kUniformNeverRight: never).
 //   leaves  [tree][2^D] doubles, at the place whose bits say "left" from the root (highest bit) on.
 // The LDS of a workgroup: each wave's leaf tables of one chunk, then the document tile,
 // [column][docs_per_block] codes.

@@ -666,9 +666,10 @@ int check_predict_args(const tree_ens *h, const float *X, int64_t n_docs, int32_
 // 16 bits of each): up to 4 * NV outputs in one pass over the trees. A workgroup takes 64 documents
 // (lanes), each of its waves a run of trees; kRowTrees trees' rows load together, their positions
 // while the trees before them are summed. Waves' sums are added in wave order.
-// Bound by the texture addresser, 96% busy with the gathers of the rows (26 cycles per 16-byte gather
-// of a wave): 50,000 documents, 1,000 trees, 8 outputs in 95 us, against 137 us for each of the two
-// walks it replaces, next to one walk of 101 us that stores the rows.
+// Bound by the texture addresser: 25 cycles per 16-byte gather of a wave keep it 96% busy while a CU
+// has waves, and that is 69% of the launch (782 workgroups, 512 at a time): 50,000 documents, 1,000
+// trees, 8 outputs in 95 us, against 110 us for each of the two walks it replaces, next to one
+// walk of 83 us that stores the rows.
 constexpr int kRowThreads = 1024;
 constexpr int kRowTrees = 4;
 template <int DL, int NV>

@@ -185,3 +185,29 @@ def test_each_threads_own_default_stream(T):
         torch.cuda.synchronize()
         for o, r in zip(outs, refs):
             assert all(torch.equal(row, r) for row in o)
+
+
+def test_eager_calls_during_a_capture(T):
+    """A call on another stream that makes the pool grow while a graph is being captured: it runs at once and
+    leaves the capture whole."""
+    import torch
+    ens = W.random_ensemble(31, 300, 20, 8, 8)
+    x, big = torch.rand((20_000, 20), device="cuda"), torch.rand((30_000, 20), device="cuda")
+    with T.TreeEnsemble.from_ensemble(ens) as m:
+        ref, ids_ref = m.predict(x), m.predict_leaves(big)
+        torch.cuda.synchronize()
+    with T.TreeEnsemble.from_ensemble(ens) as m:  # a new pool
+        m.predict(x[:100].contiguous())
+        out, ids, other = torch.zeros_like(ref), torch.zeros_like(ids_ref), torch.cuda.Stream()
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            m.predict(x, out)
+            m.predict_leaves(big, ids, stream=other)
+            m.predict(x, out)
+        for _ in range(2):
+            out.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, ref)
+        assert torch.equal(ids, ids_ref)
