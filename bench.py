@@ -521,7 +521,7 @@ def write_traffic(fetch_csv: str, write_csv: str, workload: str = HEADLINE,
     }
     with open(out_path, "w") as fh:
         json.dump(rec, fh, indent=1)
-    log(f"wrote {out_path}: {read_b / 1e6:.1f} MB read + {write_b / 1e6:.2f} MB written per launch")
+    log(f"wrote {out_path}: {read_b / 1e6:.1f} MB read + {write_b / 1e6:.2f} MB written per call")
     return 0
 
 
