@@ -160,3 +160,34 @@ def test_leaf_vector_paths(T, trees, features, leaves, n_out, docs, path):
     ref = oracle.score_multi(ens, vals, X, n_bags=2)
     for c in range(n_out):
         assert_scores_close(got[:, c], ref[:, c], f"output {c}")
+
+
+@pytest.mark.parametrize("trees,features,least,most,depth,docs,n_out,path", [
+    (1_000, 25, 1, 8, 3, 100_001, 1, UNIFORM), (1_003, 25, 1, 4, 2, 99_703, 1, UNIFORM),
+    (90, 650, 230, 400, None, 20_001, 1, TERMINAL), (300, 20, 1, 8, None, 5_001, 6, ROWS), (300, 20, 1, 8, None, 2_001, 6, WALK),
+])
+def test_leaf_values_that_are_not_finite(T, trees, features, least, most, depth, docs, n_out, path):
+    """Infinities and NaN among the leaves: each document's score is that of the leaves it reaches, whatever the
+    padding, the cut trees' other pieces and the split sums hold."""
+    import torch
+    ens = _ensemble(trees, features, least, most, depth, False)
+    vals = W.make_leaf_vectors(ens, n_out, "dense", seed=docs) if n_out > 1 else ens.value.reshape(-1, 1)
+    rng = np.random.default_rng(docs)
+    leaves = np.setdiff1d(np.nonzero(ens.feature < 0)[0], ens.tree_offsets[:-1])  # not a whole tree
+    rows = rng.choice(leaves, 6, replace=False)
+    for c in range(n_out):
+        vals[rows, c] = np.array([np.inf, -np.inf, np.nan], np.float32)[(np.arange(6) + c) % 3]
+    X = W.random_docs(docs, docs, features)
+    with T.TreeEnsemble.from_ensemble(ens, leaf_values=vals if n_out > 1 else None) as m:
+        got = m.predict(dev(X))
+        assert m.last_path() == path
+        torch.cuda.synchronize()
+        got = got.cpu().numpy().reshape(docs, n_out)
+    with np.errstate(invalid="ignore"):
+        ref = (oracle.score_multi(ens, vals, X) if n_out > 1 else oracle.score(ens, X)[0].reshape(-1, 1)).astype(np.float32)
+    assert (~np.isfinite(ref)).any() and np.isfinite(ref).any()
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.array_equal(np.isposinf(got), np.isposinf(ref))
+    assert np.array_equal(np.isneginf(got), np.isneginf(ref))
+    for c in range(n_out):
+        f = np.isfinite(ref[:, c])
+        assert_scores_close(got[f, c], ref[f, c], f"output {c}")
