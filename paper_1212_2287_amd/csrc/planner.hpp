@@ -99,7 +99,8 @@ inline PlanFacts plan_facts(const Packed &p) {
 // Two workgroups on a CU with four trees per lane keep both its pipes busy, so they take twice as long
 // as one would: the CU is one place, 350 cycles a step, and the second one's staging is mostly hidden.
 // With fewer trees per lane they wait for latency and run side by side. Gathers of leaf vectors
-// lie between: a lone workgroup takes a little longer than one of two.
+// lie between: a lone workgroup takes a fifth longer than one of two (4 outputs, 4,096 trees of 16
+// leaves, 256 blocks: 135 us whole, 121 in halves; 1,000 trees of 32 leaves: 45.2, 47.7).
 // The other plans' steps and staging take longer than these figures say, both by about the same
 // factor: 0.15 to 0.3 us a step and 5 to 18 us. Their ratio is what chooses. Over 542 batches of 40
 // models, each measured in all its shapes, the shapes picked take 1 to 3% longer than the fastest on
@@ -119,7 +120,7 @@ inline PlanTimes plan_times(const PlanFacts &f, Work work) {
     t.places = f.pairs && !f.full && work != Work::kTerminal ? 2 * kNumCus : kNumCus;
     t.round_us = f.mean_steps * (vector ? 0.17 : 0.147);
     t.next_us = full_pairs ? 1.75 : 4.5;
-    t.lone = vector ? 1.1 : 1.0;
+    t.lone = vector ? 1.2 : 1.0;
     t.reduce_us = work == Work::kPositions ? 0.0 : 3.75;
     t.average = work == Work::kTerminal ? 0.2 : 0.0;
     return t;

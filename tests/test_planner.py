@@ -88,12 +88,14 @@ def _forest(trees, features, least, most, depth=None):
     (5_000, 700, 256, 256, TERMINAL, 6_700, [(0, 2)]), (1_000, 700, 512, 512, TERMINAL, 6_700, [(0, 2)]),
     # 80 packets, 8 blocks: 51.3 us in 32 shares of 2 or 3, 58.9 in 27
     (5_000, 700, 256, 256, TERMINAL, 500, [(0, 32)]),
+    # leaf vectors, 256 blocks: 121 us in halves, 135 whole; 45.2 whole, 47.7 in halves
+    (4_096, 136, 16, 16, VECTOR, 16_383, [(0, 2)]), (1_000, 136, 32, 32, VECTOR, 16_383, [(0, 1)]),
     # 300 trees, 63 blocks of 8 documents: 13.5 us whole, 15.7 in three shares
     (300, 2_000, 30, 30, SCORES, 500, [(0, 1)]),
 ])
 def test_measured_shapes(lib, trees, features, least, most, work, docs, shapes):
     ens = _forest(trees, features, least, most)
-    _, head, splits, _, _ = _plan(lib, ens, [(work, docs)])[0]
+    _, head, splits, _, _ = _plan(lib, ens, [(work, docs)], 4 if work == VECTOR else 1)[0]
     assert (head, splits) in shapes or (splits == 1 and (0, 1) in shapes)
 
 
