@@ -71,6 +71,16 @@ public:
         b->lent = false;
     }
 
+    // Blocks that are not lent go back, for an allocation elsewhere that found no memory; false if
+    // there were none.
+    bool trim() {
+        std::lock_guard<std::mutex> lock(mu_);
+        bool any = false;
+        while (drop_one())
+            any = true;
+        return any;
+    }
+
     // Handles of the device: the last one gives the memory back.
     void add_user() {
         std::lock_guard<std::mutex> lock(mu_);

@@ -591,6 +591,8 @@ public:
         if (pool_ && (block_ = pool_->lend(bytes, stream_)))
             return static_cast<unsigned char *>(block_->p);
         error = hipMallocAsync(&async_, bytes, stream_);
+        if (error != hipSuccess && pool_ && pool_->trim())
+            error = hipMallocAsync(&async_, bytes, stream_);
         if (error != hipSuccess) {
             async_ = nullptr;
             (void)hipGetLastError();
@@ -609,6 +611,8 @@ private:
             return nullptr;
         }
         void *buf = HipScratch().allocate(bytes);
+        if (!buf && pool_ && pool_->trim())
+            buf = HipScratch().allocate(bytes);
         if (!buf) {
             error = hipErrorOutOfMemory;
             return nullptr;
@@ -1267,6 +1271,10 @@ int tree_ens_create_multi(tree_ens_t **out, int32_t n_trees, const int64_t *tree
         }
         if (e == hipSuccess)
             e = arrays.upload(&h->d_model);
+        if (e == hipErrorOutOfMemory && !h->d_model && pool_of(h->device) && pool_of(h->device)->trim()) {
+            (void)hipGetLastError();
+            e = arrays.upload(&h->d_model);
+        }
     } catch (const std::bad_alloc &) {
         e = hipErrorOutOfMemory;
     }

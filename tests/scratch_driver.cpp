@@ -137,7 +137,12 @@ void failures() {
     log.refuse_record = false;
     auto *b = pool.lend(60 * MB, 2); // room is made
     CHECK(b && pool.kept() == 60 * MB && log.live == 60 * MB);
+    CHECK(!pool.trim() && log.live == 60 * MB); // lent: stays
     pool.give(b);
+    CHECK(pool.trim() && log.live == 0 && !pool.trim());
+    auto *c = pool.lend(10 * MB, 1);
+    CHECK(c);
+    pool.give(c);
     pool.drop_user();
     CHECK(log.live == 0);
 }

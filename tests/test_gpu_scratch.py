@@ -111,6 +111,21 @@ def test_streams_do_not_share_memory(T, what, trees, features, leaves, depth, do
                 assert_scores_close(got, oracle.score(ens, v)[0], what)
 
 
+def _fill_up_to(left, what):
+    """Tensors that leave `left` bytes of the device's memory free (8 MiB more or less)."""
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    fill, slack = [], 8 << 20
+    for _ in range(4):  # the first figure can lag behind memory given back
+        free = torch.cuda.mem_get_info()[0]
+        if free > left + slack:
+            fill.append(torch.empty(free - left, dtype=torch.uint8, device="cuda"))
+    print(f"[scratch] {what}, {free >> 20} MiB free", flush=True)
+    assert left - slack <= free <= left + slack
+    return fill
+
+
 @pytest.mark.parametrize("n_out", [1, 6])
 def test_room_for_the_codes_alone_is_enough(T, n_out):
     """A coded model on a device with room for its codes, but not for positions and codes: the walk
@@ -132,15 +147,7 @@ def test_room_for_the_codes_alone_is_enough(T, n_out):
         out = torch.zeros_like(ref)
         few = call(small)  # kernels loaded, 29 MiB in the pool
         call(small[:500].contiguous())
-        torch.cuda.synchronize()
-        torch.cuda.empty_cache()
-        fill = []
-        for _ in range(4):  # the first figure can lag behind memory given back
-            free = torch.cuda.mem_get_info()[0]
-            if free > 88 * mib:
-                fill.append(torch.empty(free - 80 * mib, dtype=torch.uint8, device="cuda"))
-        print(f"[scratch] {n_out} outputs, {free / mib:.0f} MiB free", flush=True)
-        assert 72 * mib <= free <= 88 * mib
+        fill = _fill_up_to(80 * mib, f"{n_out} outputs")
         call(x, out)
         torch.cuda.synchronize()
         del fill, few
@@ -211,3 +218,50 @@ def test_eager_calls_during_a_capture(T):
             torch.cuda.synchronize()
             assert torch.equal(out, ref)
         assert torch.equal(ids, ids_ref)
+
+
+@pytest.mark.parametrize("what", ["larger than the pool keeps", "captured", "a new model"])
+def test_memory_the_pool_holds_is_there_for_others(T, what):
+    """256 MiB idle in the pool and 400 MiB free: allocations of about 550 MiB outside the pool get both."""
+    import torch
+    mib = 1 << 20
+    ids = W.random_ensemble(41, 2_000, 30, 3, 3)
+    coded = W.random_ensemble(42, 64, 500, 250, 250)
+    docs = 575_000  # 548 MiB of codes
+    x = torch.rand((docs, 500), device="cuda")
+    out = torch.zeros(docs, device="cuda")
+    if what == "a new model":  # 960,000 leaf rows of 116 floats, 425 MiB, and its records
+        base, n = W.random_ensemble(43, 100, 20, 64, 64), 15_000
+        each = [base.tree(t % 100) for t in range(n)]
+        wide = W.Ensemble(np.arange(n + 1, dtype=np.int64) * 127,
+                          *[np.concatenate([t[k] for t in each]) for k in range(5)], 20)
+        vals = np.zeros((wide.n_nodes, 116), np.float32)
+        vals[:, 3] = wide.value
+    with T.TreeEnsemble.from_ensemble(ids) as m, T.TreeEnsemble.from_ensemble(coded) as c:
+        ref = c.predict(x).clone()
+        big = torch.rand((70_000, 30), device="cuda")
+        got = m.predict_leaves(big)  # 256 MiB of positions
+        assert m.last_path() == T.TREE_ENS_PATH_ROWS
+        torch.cuda.synchronize()
+        del got
+        fill = _fill_up_to(400 * mib, what)
+        if what == "larger than the pool keeps":
+            c.predict(x, out)
+        elif what == "captured":
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g):
+                c.predict(x, out)
+            g.replay()
+        else:
+            w = T.TreeEnsemble.from_ensemble(wide, leaf_values=vals)
+            del fill
+            few = big[:100, :20].contiguous()
+            scores = w.predict(few)
+            torch.cuda.synchronize()
+            assert_scores_close(scores[:, 3].cpu().numpy(), oracle.score(wide, few.cpu().numpy())[0], what)
+            w.close()
+            return
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+        del fill
+        torch.cuda.empty_cache()
