@@ -100,7 +100,7 @@ int tree_ens_create(tree_ens_t **out, int32_t n_trees, const int64_t *tree_offse
  * n_outputs = n_bags = 1). With n_outputs > 1 the leaf rows live in a device table of
  * one row per leaf (and one of zeros) of ceil(n_outputs / 4) * 4 floats. A predict makes one pass
  * over the trees per four outputs. With more than four outputs, at most 4,096 trees and enough
- * documents (4,096, and 4 or 5 per tree; fewer than 18,432 if many shallow trees make the passes cheap)
+ * documents (4,096, and 4 or 5 per tree; at most 32,768 if many shallow trees make the passes cheap)
  * it makes one pass that stores each leaf's row in
  * borrowed memory (2 bytes per document and tree, at most 256 MiB:
  * larger batches go in chunks) and one reading of it per eight outputs.

@@ -262,16 +262,17 @@ inline bool leaves_direct(const PlanFacts &f, int64_t n_docs) {
 // 1,000 trees: 4,096 documents 342, 368, 6,000 488, 378).
 // Nor do models whose chunks hold fewer than kRowDocs documents (64 of them fill a workgroup; 10,000
 // trees of 8 leaves, 6 outputs, 50,000 documents in chunks of 6,500: 1,474, 2,194), and many trees of few
-// steps, whose walks cost less than the gathers of the rows (8 leaves, 50,000 documents: 4,000 trees,
-// 6 outputs 483, 601, 16 outputs 1,011, 1,188; 3,000 trees, 6 outputs 362, 395, 12 outputs 544, 522;
-// 2,000 trees 256, 248; 4,000 trees, 16,384 documents, two full rounds of workgroups: 205, 162).
+// steps, whose walks cost less than the gathers of the rows, beyond one chunk of documents (8 leaves,
+// 50,000 documents: 4,000 trees, 6 outputs 483, 601, 16 outputs 1,011, 1,188; 3,000 trees, 6 outputs 362,
+// 395, 12 outputs 544, 522; 2,000 trees 256, 248; 4,000 trees, 6 outputs, 16,384 documents 205, 162,
+// 24,000 240, 246, 32,000 327, 282).
 constexpr int64_t kRowDocs = 32768;
 constexpr double kCheapSteps = 6.0; // 8 leaves: 5.3, 16: 6.8
 inline bool rows_pay(const PlanFacts &f, int64_t n_docs) {
     if (f.n_outputs <= 4 || f.n_trees * kRowDocs * int64_t(sizeof(uint16_t)) > kPositionBytes)
         return false;
     const bool cheap_walks = f.pairs && f.full && f.mean_steps < kCheapSteps;
-    if (cheap_walks && f.n_trees > (f.n_outputs <= 8 ? 2048 : 3072) && n_docs > kRowDocs / 2 + 2048)
+    if (cheap_walks && f.n_trees > (f.n_outputs <= 8 ? 2048 : 3072) && n_docs > kRowDocs)
         return false;
     return n_docs >= std::max<int64_t>(4096, (f.n_outputs <= 32 ? 4 : 5) * int64_t(f.n_trees));
 }

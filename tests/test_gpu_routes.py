@@ -131,8 +131,8 @@ def test_leaf_id_paths(T, trees, features, leaves, docs, path):
 @pytest.mark.parametrize("trees,features,leaves,n_out,docs,path", [
     (17, 20, 8, 8, 4_095, WALK), (17, 20, 8, 8, 4_097, ROWS), (17, 20, 8, 4, 5_000, WALK), (1, 20, 1, 9, 5_000, ROWS),
     (1_100, 20, 8, 5, 4_399, WALK), (1_100, 20, 8, 5, 4_400, ROWS), (1_100, 20, 8, 33, 5_499, WALK),
-    (1_100, 20, 8, 33, 5_500, ROWS), (4_097, 5, 3, 5, 16_400, WALK), (2_100, 5, 3, 5, 18_432, ROWS),
-    (2_100, 5, 3, 5, 18_433, WALK), (60, 500, 10, 16, 5_002, ROWS), (60, 1_200, 10, 13, 5_003, ROWS),
+    (1_100, 20, 8, 33, 5_500, ROWS), (4_097, 5, 3, 5, 16_400, WALK), (2_100, 5, 3, 5, 32_768, ROWS),
+    (2_100, 5, 3, 5, 32_769, WALK), (60, 500, 10, 16, 5_002, ROWS), (60, 1_200, 10, 13, 5_003, ROWS),
     (60, 2_000, 10, 6, 5_001, ROWS), (70, 700, 150, 7, 5_005, ROWS),
 ])
 def test_leaf_vector_paths(T, trees, features, leaves, n_out, docs, path):

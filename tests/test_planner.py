@@ -125,7 +125,7 @@ def test_terminal_packets_where_they_pay(lib, trees, features, least, most, walk
 
 @pytest.mark.parametrize("trees,features,leaves,outputs,walked,rows", [
     (1_000, 136, 32, 8, [500, 2_000], [6_000, 16_384, 200_000]), (1_000, 136, 32, 64, [2_000, 4_096], [6_000, 50_000]),
-    (4_000, 30, 8, 6, [4_096, 8_192, 24_000, 50_000, 200_000], [16_384]),  # walks cheaper than gathers
+    (4_000, 30, 8, 6, [4_096, 8_192, 33_000, 50_000, 200_000], [16_384, 32_000]),  # walks cheaper than gathers
     (4_000, 30, 8, 16, [8_192, 50_000], [16_384]), (3_000, 30, 8, 6, [50_000], [16_384]),
     (3_000, 30, 8, 12, [6_000], [16_384, 50_000]), (2_000, 30, 8, 6, [6_000], [12_000, 16_384, 50_000]),
     (10, 20, 8, 5, [], [4_096, 200_000]), (4_096, 136, 16, 24, [8_192], [16_384, 100_000]),
